@@ -69,28 +69,35 @@ typedef enum {
     FSIC_ENOTAPE = 9      /* backward without a forward pass run with FSIC_KEEP_TAPE */
 } fsic_status;
 
-/* Precision of the Poisson solves (c).  FSIC_FP64: FP64 conjugate
- * gradients.  FSIC_MIXED: FP32 stencil and CG sweeps whose accumulated
- * solution is corrected in FP64 against the FP64 residual until the same
- * FP64 relative-residual tolerance is met; overlap, S^{-1/2}, residuals and
- * energies stay FP64. */
+/* Precision of the Poisson solves (c).  FSIC_FP64: FP64 throughout.
+ * FSIC_MIXED: iterative solves run FP32 stencil and CG sweeps whose
+ * accumulated solution is corrected in FP64 against the FP64 residual until
+ * the same FP64 relative-residual tolerance is met; overlap, S^{-1/2},
+ * residuals and energies stay FP64.  The direct solver of FSIC_PCG is FP64
+ * under both. */
 enum { FSIC_FP64 = 0, FSIC_MIXED = 1 };
 
 /* Poisson solver (c) for -L v = 4 pi rho + boundary term:
  *   FSIC_CG   plain conjugate gradients;
- *   FSIC_PCG  conjugate gradients preconditioned by the inverse of the same
- *             stencil with odd-reflection faces, applied with type-I sine
- *             transforms along each axis (a few iterations instead of
- *             hundreds); a batch with a grid axis above 256 nodes is solved
- *             with plain CG instead.  The default.
+ *   FSIC_PCG  conjugate gradients preconditioned by the inverse of the
+ *             operator itself: the eigenvectors of its one-axis factors
+ *             diagonalise it, so the first iteration is the solution up to
+ *             FP64 rounding and the FP64 residual only has to confirm it
+ *             (tolerances near the rounding level take a second one).  An
+ *             orbital that does not get there (non-finite data) goes to
+ *             conjugate gradients preconditioned by type-I sine transforms.
+ *             A batch with a grid axis above 192 nodes is solved with plain
+ *             CG instead.  The default.
  *   FSIC_AAR  alternating Anderson-Richardson (the solver of the paper's
- *             real-space code, Sec. II.A) with the same preconditioner:
+ *             real-space code, Sec. II.A) with the inverse of the same
+ *             stencil under odd reflection at the faces, applied with type-I
+ *             sine transforms along each axis, as preconditioner:
  *             Richardson steps x += f, f = M^{-1}(b + L x), and every third
  *             iteration an Anderson extrapolation over the last 7
  *             differences of x and f (weights 1 and 1).  Needs precision
  *             FSIC_FP64 (the iterate and residual are FP64, f is FP32) and
  *             12 extra bytes per orbital node per history column (84 B).
- *             Batches with an axis above 256 nodes use plain CG.
+ *             Batches with an axis above 192 nodes use plain CG.
  * All stop on the same FP64 relative residual. */
 enum { FSIC_CG = 0, FSIC_PCG = 1, FSIC_AAR = 2 };
 
@@ -99,9 +106,10 @@ enum { FSIC_CG = 0, FSIC_PCG = 1, FSIC_AAR = 2 };
 #define FSIC_KEEP_TAPE       2u  /* keep what fsic_backward needs */
 #define FSIC_ALLOW_NONORTHO  4u  /* accept non-orthonormal psi (S = T G T^T is exact anyway) */
 #define FSIC_PROFILE         8u  /* time sampled CG launches with HIP events (fsic_stats.sweep_*) */
-#define FSIC_GRAPHS         32u  /* FSIC_PCG with FSIC_MIXED: capture each restart cycle (its CG
-                                    iterations and the FP64 residual check) as a HIP graph once per
-                                    batch layout and buffers, and replay it; ignored with FSIC_PROFILE */
+#define FSIC_GRAPHS         32u  /* FSIC_PCG with FSIC_MIXED: capture the direct solve and its FP64
+                                    residual check (where restart cycles run: each cycle) as HIP graphs
+                                    once per batch layout and buffers, and replay them; ignored with
+                                    FSIC_PROFILE */
 #define FSIC_FP32_ORBITALS  16u  /* Fermi-Loewdin orbitals phi = (Z T) psi from an fp32 GEMM on the
                                     matrix cores (fp32 operands and accumulation); costs about 1e-7
                                     relative in phi, more than the 1e-8 Ha energy budget allows */
@@ -176,11 +184,11 @@ typedef struct {
     int32_t update_launches;  /* sampled pointwise updates (x += alpha p, r -= alpha q) */
     double  sweep_ms, sweep_bytes;
     double  update_ms, update_bytes;
-    /* FSIC_PCG with FSIC_PROFILE: iterations are sampled every other one, and
-     * each sampled preconditioner application (three transform passes with
-     * the in-plane pair fused, else five) is timed as one unit with its
-     * algorithmic bytes (each array of an active orbital read or written
-     * once per pass) and flops */
+    /* FSIC_PCG with FSIC_PROFILE: the first application of the direct solver
+     * (three passes with the in-plane pair fused, else five), and, where the
+     * sine-transform preconditioner runs, every other of its applications,
+     * timed as one unit with its algorithmic bytes (each array of an active
+     * orbital read or written once per pass) and flops */
     int32_t precond_launches;
     double  precond_ms, precond_bytes, precond_flops;
     /* stencil shape of the CG sweeps: tiles of 32 x 8*stencil_cpt columns,
@@ -194,14 +202,18 @@ typedef struct {
     int32_t stencil_cpt, stencil_depth;
     int64_t stencil_blocks;
     double  tune_ms;
-    /* FSIC_PCG in FSIC_MIXED with FSIC_PROFILE: the FP64 residual pass that
-     * closes each restart cycle (every cycle but the first is sampled) */
+    /* FSIC_PCG with FSIC_PROFILE: the FP64 residual pass after the direct
+     * solver's first application (in restart cycles: the one that closes
+     * each cycle but the first) */
     int32_t resid_launches;
     double  resid_ms, resid_bytes;
     /* FSIC_GRAPHS: restart-cycle graphs captured so far by this context
      * (a replayed graph is not counted again) */
     int32_t graph_captures;
-    /* FSIC_PCG / FSIC_AAR: layout of the sine-transform preconditioner, bits
+    /* FSIC_PCG: layout of the direct solver, bit 1 fused in-plane passes (for
+     * the orbitals whose plane fits; else one pass per axis), plus 16 x the
+     * class of the longest axis (1: up to 128 nodes, 2: 160, 3: 192).
+     * FSIC_AAR: layout of the sine-transform preconditioner, bits
      * 1 fused in-plane passes (else five per-axis passes), 2 two fused-pass
      * blocks per compute unit, 4 two-block z pass, 8 inverse pass reads p_old
      * before its products, plus 16 x the transform variant (1-3; 0: solved

@@ -41,7 +41,9 @@ struct OrbDesc {
     int nt9, base9;                     // spectral-preconditioner partial-sum slots (x-pass panels)
     int dst_s[3];                       // sine-matrix offsets (x, y, z) in the spectral table
     int dst_g[3];                       // eigenvalue-symbol offsets (x, y, z) in the spectral table
-    int pad;
+    int fd_t[3];                        // axis-table offsets (x, y, z) of the direct solver (fdm.hip)
+    int fd_n[3];                        // 16-row tiles of those tables
+    int fd_fused;                       // direct solver: fused in-plane passes (spectral layout [kx][ky])
 };
 
 
@@ -66,6 +68,24 @@ struct DstItems {
     int zocc2;       // z pass: 64-column panels, two blocks per compute unit
     int xyocc2;      // fused x-y passes two blocks per compute unit (where the plane fits)
     int pv;          // the inverse pass reads p_old before its products (else at the store)
+};
+
+// Direct solver (fdm.hip): passes, the contiguous unit range of one block
+// (every unit of a range uses the same axis tables), and the launches of a
+// pass: one per tile count T (and, in-plane, per one or two axis tables).
+enum { kFdmPassXY = 0, kFdmPassZ = 1, kFdmPassX = 2, kFdmPassY = 3, kFdmPasses = 4 };
+struct FdmRange {
+    int u0, u1;
+};
+struct FdmClass {
+    int pass, T, two;
+    int blocks, range0;  // ranges[range0 .. range0 + blocks)
+};
+struct FdmPlan {
+    const Item *units[kFdmPasses];  // device: (orbital, z plane) or (orbital, 64-line panel)
+    const FdmRange *ranges;         // device
+    const FdmClass *cls;            // host
+    int ncls;
 };
 
 // Output of the last transform pass when it forms the next search

@@ -197,6 +197,31 @@ hipError_t launch_reduce_partials(int norb, const OrbDesc *orb, const double *pa
                                   int stencil_layout, double *out, hipStream_t s);
 
 // ----------------------------------------------------------------------------
+// fdm.hip: direct Poisson solver by fast diagonalisation (FP64)
+// ----------------------------------------------------------------------------
+
+// out (+)= K^{-1} b, b = scale src^2 (square) or src, for every orbital with
+// done == 0 (done null: all).  work: one field array; src, work and out may
+// not overlap.
+hipError_t launch_fdm(const FdmPlan &p, const OrbDesc *orb, const int *done, const double *tab, const double *src,
+                      int square, double scale, double *work, double *out, int accumulate, hipStream_t s);
+// LDS limits of the kernels on the current device (once per device)
+hipError_t fdm_setup();
+// whether the fused in-plane passes serve planes of nx x ny nodes
+bool fdm_xy_fits(int nx, int ny, size_t lds_limit);
+// blocks of a pass that one compute unit holds
+int fdm_occupancy(int pass, int T, int two);
+
+// FP64 residual of the direct solver: res = b + L x with its res.res
+// partials, written to res (null: only the partials; res may be b itself)
+hipError_t launch_residual64(int radius, const Coeffs &c, const Item *items7, int nitems7, const OrbDesc *orb,
+                             const int *done, const double *x, const double *b, double *res, double *partRU,
+                             hipStream_t s);
+// x += d for the orbitals with done == 0
+hipError_t launch_add_fields(int nitems8, const Item *items8, const OrbDesc *orb, const int *done, double *x,
+                             const double *d, hipStream_t s);
+
+// ----------------------------------------------------------------------------
 // aar.hip: alternating Anderson-Richardson iteration
 // ----------------------------------------------------------------------------
 

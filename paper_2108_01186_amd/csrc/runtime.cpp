@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/fsic.h"
+#include "fdm_basis.h"
 #include "kernels.h"
 
 using namespace fsic;
@@ -168,6 +169,13 @@ struct Batch {
     bool dst_zocc2 = false;  // z pass in 64-column panels, two blocks per compute unit
     bool dst_xyocc2 = true;  // fused x-y passes two blocks per compute unit where the plane fits
     bool dst_pv = true;      // inverse pass reads p_old before its products
+    // direct solver: units per pass, block ranges, launches, axis tables
+    bool direct = false;
+    std::vector<Item> fu[kFdmPasses];
+    std::vector<FdmRange> fr;
+    std::vector<FdmClass> fcls;
+    std::vector<double> ftab;
+    bool fd_any_fused = false;  // some orbital takes the fused in-plane passes
     int max_group = 0;  // most orbitals in one channel
     // harmonic contractions over grid nodes (moments) and ghosts (adjoint
     // boundary): block items, channel ranges, partial-tile elements
@@ -247,6 +255,9 @@ struct fsic_ctx {
     DBuf<float> Fprev, Fh;               // AAR: previous f, f-difference history
     DBuf<double> Xh, aar_gamma, partD;  // AAR: step history, weights, Gram partials
     DBuf<Item> d_dx, d_dy, d_dz, d_dxy;
+    DBuf<Item> d_fu[kFdmPasses];  // direct solver: units, block ranges, axis tables
+    DBuf<FdmRange> d_fr;
+    DBuf<double> d_ftab;
     DBuf<double> Gh;  // ghost values
     DBuf<double> part7, part8, partRU, partH;  // partH: harmonic-contraction partial tiles
     DBuf<HcItem> d_hcN, d_hcG, d_hcNx, d_hcGx;
@@ -285,7 +296,7 @@ struct fsic_ctx {
     DBuf<double> d_chk;  // the host checks' inputs, packed (forward pass)
     DBuf<double> d_grad;  // dE/da of every channel, packed (backward pass)
     std::vector<ProfRec> recs;
-    bool pend_prof = false, pend_aar = false, pend_pcg = false, pend_mixed = false;
+    bool pend_prof = false, pend_aar = false, pend_pcg = false, pend_mixed = false, pend_direct = false;
     bool pend_dst_xy = false;
     int pend_dst_fast = 0;
     // device status word of the forward pass, copied once the Loewdin step
@@ -426,6 +437,13 @@ int pcg_first_chunk(int variant) {
     return pcg_chunk(variant);
 }
 
+// FSIC_PCG_CHUNK / FSIC_PCG_FIRST ask for restart cycles of a given length:
+// the mixed solve then runs them in place of the direct solver
+bool cycles_forced() {
+    static const bool v = getenv("FSIC_PCG_CHUNK") || getenv("FSIC_PCG_FIRST");
+    return v;
+}
+
 // AAR parameters (the paper does not state them): Richardson weight omega,
 // Anderson mixing beta, an Anderson step every kAarPeriod iterations over
 // the last kAarM differences; with the sine-transform preconditioner these
@@ -506,6 +524,19 @@ const std::vector<float> &dst_block(int n, int radius) {
     return cache.emplace(std::make_pair(n, radius), std::move(v)).first->second;
 }
 
+// Axis table of the direct solver (fdm_basis.h), cached per process; at most
+// 32 axes are kept (a new one then drops the others).
+std::vector<double> fdm_block(int n, int radius) {
+    static std::mutex mu;
+    static std::map<std::pair<int, int>, std::vector<double>> cache;
+    std::lock_guard<std::mutex> lk(mu);
+    auto f = cache.find({n, radius});
+    if (f != cache.end()) return f->second;
+    if (cache.size() >= 32) cache.clear();
+    const Coeffs cw = fd_weights(radius);
+    return cache.emplace(std::make_pair(n, radius), fdm_axis_table(n, radius, cw.c)).first->second;
+}
+
 // LDS bytes one workgroup may use on the current device
 size_t device_lds_limit() {
     int dev = 0, v = 0;
@@ -523,7 +554,137 @@ struct DstTune {
     bool xy = true, xyocc2 = true, zocc2 = true, pv = true;
 };
 
-void build_batch(const std::vector<Group> &groups, int radius, const Shape &sh, Batch &b,
+// blocks of a direct-solver pass that the current device holds at once
+int fdm_slots(int pass, int T, int two) {
+    static std::mutex mu;
+    static std::map<std::array<int, 4>, int> cache;
+    int dev = 0, cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    std::lock_guard<std::mutex> lk(mu);
+    const std::array<int, 4> key{dev, pass, T, two};
+    const auto f = cache.find(key);
+    if (f != cache.end()) return f->second;
+    if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cu < 1) cu = 256;
+    return cache[key] = cu * std::max(1, fdm_occupancy(pass, T, two));
+}
+
+// Work units, launches and axis tables of the direct solver for the orbitals
+// of b.  An orbital whose plane fits (fdm_xy_fits) takes the fused in-plane
+// passes (48 B per node), the others one pass per axis (80 B); xy = false or
+// FSIC_DST_XY=0: one pass per axis for all.
+void build_direct(Batch &b, int radius, bool xy) {
+    const size_t ldsmax = device_lds_limit();
+    const char *env = std::getenv("FSIC_DST_XY");
+    if (env && std::atoi(env) == 0) xy = false;
+    std::map<int, int> at;  // axis length -> table offset
+    auto table = [&](int n) {
+        auto f = at.find(n);
+        if (f != at.end()) return f->second;
+        const int o = (int)b.ftab.size();
+        const std::vector<double> t = fdm_block(n, radius);
+        b.ftab.insert(b.ftab.end(), t.begin(), t.end());
+        return at[n] = o;
+    };
+    // runs of units that share a launch (T, two) and axis tables (t0, t1)
+    typedef std::array<int, 4> Key;
+    std::map<Key, std::vector<Item>> runs[kFdmPasses];
+    for (int o = 0; o < (int)b.orb.size(); ++o) {
+        OrbDesc &od = b.orb[o];
+        const int n[3] = {od.nx, od.ny, od.nz};
+        for (int d = 0; d < 3; ++d) {
+            od.fd_t[d] = table(n[d]);
+            od.fd_n[d] = fdm_tiles(n[d]);
+        }
+        od.fd_fused = xy && fdm_xy_fits(od.nx, od.ny, ldsmax);
+        b.fd_any_fused = b.fd_any_fused || od.fd_fused;
+        auto panels = [&](std::vector<Item> &v, long long lines) {
+            for (int t = 0; t < (int)((lines + 63) / 64); ++t) v.push_back(Item{o, t});
+        };
+        if (od.fd_fused) {
+            std::vector<Item> &v = runs[kFdmPassXY][Key{std::max(od.fd_n[0], od.fd_n[1]), od.nx != od.ny, od.fd_t[0], od.fd_t[1]}];
+            for (int z = 0; z < od.nz; ++z) v.push_back(Item{o, z});
+        } else {
+            panels(runs[kFdmPassX][Key{od.fd_n[0], 0, od.fd_t[0], 0}], (long long)od.ny * od.nz);
+            panels(runs[kFdmPassY][Key{od.fd_n[1], 0, od.fd_t[1], 0}], (long long)od.nx * od.nz);
+        }
+        panels(runs[kFdmPassZ][Key{od.fd_n[2], 0, od.fd_t[2], 0}], (long long)od.nx * od.ny);
+    }
+    for (int pass = 0; pass < kFdmPasses; ++pass) {
+        for (auto it = runs[pass].begin(); it != runs[pass].end();) {
+            // one launch: the runs of this (T, two)
+            auto end = it;
+            long long total = 0;
+            while (end != runs[pass].end() && end->first[0] == it->first[0] && end->first[1] == it->first[1]) {
+                total += (long long)end->second.size();
+                ++end;
+            }
+            FdmClass cl{pass, it->first[0], it->first[1], 0, (int)b.fr.size()};
+            const long long slots = fdm_slots(pass, cl.T, cl.two);
+            for (; it != end; ++it) {
+                const long long nu = (long long)it->second.size();
+                const long long nb = std::max(1LL, std::min(nu, (slots * nu + total / 2) / total));
+                const int u0 = (int)b.fu[pass].size();
+                for (long long i = 0; i < nb; ++i)
+                    b.fr.push_back(FdmRange{u0 + (int)(nu * i / nb), u0 + (int)(nu * (i + 1) / nb)});
+                b.fu[pass].insert(b.fu[pass].end(), it->second.begin(), it->second.end());
+            }
+            cl.blocks = (int)b.fr.size() - cl.range0;
+            b.fcls.push_back(cl);
+        }
+    }
+}
+
+// Work units of the sine-transform preconditioner for the orbitals of b
+// (b.dst_fast != 0): panels or planes, sine matrices and symbols.
+void build_sine(Batch &b, int radius, const DstTune &dt) {
+    const size_t ldsmax = device_lds_limit();
+    const int npx = (b.max_n + 31) & ~31;
+    // fused x-y passes: in-plane axes of at most 128 nodes and LDS for the
+    // plane plus one sine matrix (two when some grid has nx != ny);
+    // FSIC_DST_XY=0 keeps five separate passes
+    const char *env = std::getenv("FSIC_DST_XY");
+    b.dst_xy = b.npxy <= 128 && dst_xy_lds(b.npxy, b.dst_two) <= ldsmax && !(env && std::atoi(env) == 0) && dt.xy;
+    b.dst_zocc2 = b.dst_xy && b.dst_fast == 1 && dst_z_occ2(npx) && dt.zocc2;
+    b.dst_xyocc2 = dt.xyocc2;
+    const char *epv = std::getenv("FSIC_DST_PV");
+    b.dst_pv = dt.pv && !(epv && std::atoi(epv) == 0);
+    std::map<int, std::pair<int, int>> done;  // n -> (sine offset, symbol offset)
+    auto entry = [&](int n) -> const std::pair<int, int> & {
+        auto f = done.find(n);
+        if (f != done.end()) return f->second;
+        const int np = (n + 31) & ~31;
+        const std::vector<float> &blk = dst_block(n, radius);  // np x np sines, then n symbols
+        const int so = (int)b.dtab.size();
+        b.dtab.insert(b.dtab.end(), blk.begin(), blk.end());
+        // pad the table to a multiple of 4 floats
+        while (b.dtab.size() % 4) b.dtab.push_back(0.f);
+        return done[n] = {so, so + np * np};
+    };
+    const int pc = dst_panel_cols(b.dst_fast);
+    for (int o = 0; o < (int)b.orb.size(); ++o) {
+        OrbDesc &od = b.orb[o];
+        const int n[3] = {od.nx, od.ny, od.nz};
+        for (int d = 0; d < 3; ++d) {
+            const auto &e = entry(n[d]);
+            od.dst_s[d] = e.first;
+            od.dst_g[d] = e.second;
+        }
+        // persistent kernels take contiguous unit ranges: orbital order, so
+        // one sine matrix serves a whole range
+        if (b.dst_xy) {
+            for (int z = 0; z < od.nz; ++z) b.dxy.push_back(Item{o, z});
+        } else {
+            for (int t = 0; t < (int)(((long long)od.ny * od.nz + pc - 1) / pc); ++t) b.dx.push_back(Item{o, t});
+            for (int t = 0; t < (int)(((long long)od.nx * od.nz + pc - 1) / pc); ++t) b.dy.push_back(Item{o, t});
+        }
+        for (int t = 0; t < od.nt9; ++t) b.dz.push_back(Item{o, t});
+    }
+}
+
+// what a batch's solver needs beside the stencil items
+enum Precond { kNoPrecond = 0, kSine = 1, kDirect = 2 };
+
+void build_batch(const std::vector<Group> &groups, int radius, const Shape &sh, Batch &b, Precond pre,
                  const DstTune &dt = DstTune{}, int lmax = 6) {
     const int cpt = sh.cpt;
     b = Batch{};
@@ -539,37 +700,11 @@ void build_batch(const std::vector<Group> &groups, int radius, const Shape &sh, 
     if (npx <= dst_variant_npmax(1) && dst_fast_lds(npx, 128, true) <= ldsmax) variant = 1;
     else if (npx <= dst_variant_npmax(2) && dst_fast_lds(npx, 64, true) <= ldsmax) variant = 2;
     else if (npx <= dst_variant_npmax(3) && dst_fast_lds(npx, 64, false) <= ldsmax) variant = 3;
-    const bool fast = variant != 0;
     b.dst_fast = variant;
-    // fused x-y passes: in-plane axes of at most 128 nodes and LDS for the
-    // plane plus one sine matrix (two when some grid has nx != ny);
-    // FSIC_DST_XY=0 keeps five separate passes
     for (const Group &g : groups) b.dst_two = b.dst_two || g.n[0] != g.n[1];
     for (const Group &g : groups) b.npxy = std::max(b.npxy, std::max(g.n[0], g.n[1]));
     b.npxy = (b.npxy + 31) & ~31;
-    {
-        const char *env = std::getenv("FSIC_DST_XY");
-        b.dst_xy = fast && b.npxy <= 128 && dst_xy_lds(b.npxy, b.dst_two) <= ldsmax &&
-                   !(env && std::atoi(env) == 0) && dt.xy;
-        b.dst_zocc2 = b.dst_xy && variant == 1 && dst_z_occ2(npx) && dt.zocc2;
-        b.dst_xyocc2 = dt.xyocc2;
-        const char *epv = std::getenv("FSIC_DST_PV");
-        b.dst_pv = dt.pv && !(epv && std::atoi(epv) == 0);
-    }
-    std::vector<std::pair<int, int>> nat7, nat8, natx, naty, natz;
-    std::map<int, std::pair<int, int>> dst_done;  // n -> (sine offset, symbol offset)
-    auto dst_entry = [&](Batch &bb, int n, int radius_) -> const std::pair<int, int> & {
-        auto f = dst_done.find(n);
-        if (f != dst_done.end()) return f->second;
-        const int np = (n + 31) & ~31;
-        const std::vector<float> &blk = dst_block(n, radius_);  // np x np sines, then n symbols
-        const int so = (int)bb.dtab.size();
-        bb.dtab.insert(bb.dtab.end(), blk.begin(), blk.end());
-        const int go = so + np * np;
-        // pad the table to a multiple of 4 floats
-        while (bb.dtab.size() % 4) bb.dtab.push_back(0.f);
-        return dst_done[n] = {so, go};
-    };
+    std::vector<std::pair<int, int>> nat7, nat8;
     // harmonic contractions and expansions: one group per run of
     // consecutive groups on one grid whose fields follow each other (the two
     // spins of a system), at most kMaxOrb orbitals, so the harmonics of a
@@ -622,22 +757,12 @@ void build_batch(const std::vector<Group> &groups, int radius, const Shape &sh, 
                 od.centre[d] = g.origin[d] + 0.5 * g.h * (g.n[d] - 1);
             }
             od.chan = g.chan;
-            // preconditioner units: panels of 128 columns (fast) or 32
-            auto nitem = [&](long long ncol) {
-                const int pc = dst_panel_cols(variant);
-                return (int)((ncol + pc - 1) / pc);
-            };
             // r.z partial slots: one per z-pass panel (the z pass forms r.z
             // from the spectral coefficients)
             const int zpc = 64;  // z-pass panel columns (every variant)
             od.nt9 = (int)(((long long)g.n[0] * g.n[1] + zpc - 1) / zpc);
             od.base9 = b.tot9;
             b.tot9 += od.nt9;
-            for (int d = 0; d < 3; ++d) {
-                const auto &e = dst_entry(b, g.n[d], radius);
-                od.dst_s[d] = e.first;
-                od.dst_g[d] = e.second;
-            }
             const int o = (int)b.orb.size();
             b.orb.push_back(od);
             // the z-chunks of one column tile next to each other: their
@@ -649,16 +774,6 @@ void build_batch(const std::vector<Group> &groups, int radius, const Shape &sh, 
                     for (int bz = 0; bz < od.tiles_z; ++bz)
                         nat7.push_back({o, bx + od.tiles_x * (by + od.tiles_y * bz)});
             for (int t = 0; t < od.nt8; ++t) nat8.push_back({o, t});
-            if (b.dst_xy) {
-                for (int z = 0; z < g.n[2]; ++z) b.dxy.push_back(Item{o, z});
-            } else {
-                const int nx_t = nitem((long long)g.n[1] * g.n[2]);  // x-pass panels
-                for (int t = 0; t < nx_t; ++t) natx.push_back({o, t});
-                const int ny_t = nitem((long long)g.n[0] * g.n[2]);
-                for (int t = 0; t < ny_t; ++t) naty.push_back({o, t});
-            }
-            const int nz_t = (int)(((long long)g.n[0] * g.n[1] + zpc - 1) / zpc);
-            for (int t = 0; t < nz_t; ++t) natz.push_back({o, t});
             b.fields = std::max(b.fields, od.off + M);
         }
     }
@@ -690,12 +805,10 @@ void build_batch(const std::vector<Group> &groups, int radius, const Shape &sh, 
                 dst.push_back(e);
             }
     }
-    // persistent kernels take contiguous unit ranges: keep orbital order so
-    // one sine matrix serves a whole range
-    for (auto *pr : {&natx, &naty, &natz}) {
-        std::vector<Item> &dst = pr == &natx ? b.dx : (pr == &naty ? b.dy : b.dz);
-        dst.clear();
-        for (const auto &q : *pr) dst.push_back(Item{q.first, q.second});
+    if (variant && pre == kSine) build_sine(b, radius, dt);
+    if (variant && pre == kDirect) {
+        b.direct = true;
+        build_direct(b, radius, dt.xy);
     }
 }
 
@@ -714,11 +827,19 @@ fsic_status upload(fsic_ctx *c, DBuf<T> &d, const std::vector<T> &h) {
     return FSIC_OK;
 }
 
-// The spectral preconditioner serves batches whose longest axis fits one of
-// the transform variants (about 208 nodes); larger batches are solved with
-// plain CG.
+// The direct solver and the spectral preconditioner serve batches whose
+// longest axis is at most 192 nodes; larger batches are solved with plain CG.
 bool use_pcg(const fsic_ctx *c, const Batch &b) {
     return c->opts.solver == FSIC_PCG && b.dst_fast != 0;
+}
+
+// What the context's solver builds on: the direct solver serves FSIC_PCG
+// (unless restart cycles of a given length are asked for), the sine
+// transforms AAR.
+Precond precond_of(const fsic_ctx *c, int precision) {
+    if (c->opts.solver == FSIC_AAR) return kSine;
+    if (c->opts.solver != FSIC_PCG) return kNoPrecond;
+    return precision == FSIC_MIXED && cycles_forced() ? kSine : kDirect;
 }
 
 // AAR uses the same preconditioner, so the same limit (larger batches: plain CG)
@@ -740,7 +861,14 @@ fsic_status prepare_batch(fsic_ctx *c, const Batch &b, int precision) {
     if ((st = upload(c, c->d_hcGx, b.hcGx))) return st;
     if ((st = upload(c, c->d_hchN, b.hchN))) return st;
     if ((st = upload(c, c->d_hchG, b.hchG))) return st;
-    if (use_pcg(c, b) || use_aar(c, b)) {
+    if (b.direct) {
+        for (int q = 0; q < kFdmPasses; ++q)
+            if ((st = upload(c, c->d_fu[q], b.fu[q]))) return st;
+        if ((st = upload(c, c->d_fr, b.fr))) return st;
+        if ((st = upload(c, c->d_ftab, b.ftab))) return st;
+        HIPCHK(c, fdm_setup());
+        HIPCHK(c, c->R.ensure(F));  // the passes' work array
+    } else if (use_pcg(c, b) || use_aar(c, b)) {
         if ((st = upload(c, c->d_dx, b.dx))) return st;
         if ((st = upload(c, c->d_dy, b.dy))) return st;
         if ((st = upload(c, c->d_dz, b.dz))) return st;
@@ -762,7 +890,8 @@ fsic_status prepare_batch(fsic_ctx *c, const Batch &b, int precision) {
         HIPCHK(c, c->partD.ensure((size_t)b.tot8 * kAarD));
     }
     HIPCHK(c, c->B.ensure(F));
-    if (precision == FSIC_FP64) {
+    if (b.direct) {
+    } else if (precision == FSIC_FP64) {
         HIPCHK(c, c->R.ensure(F));
         HIPCHK(c, c->P0.ensure(F));
         HIPCHK(c, c->Q.ensure(F));
@@ -814,6 +943,15 @@ fsic_status prepare_batch(fsic_ctx *c, const Batch &b, int precision) {
         *c->h_stat = 0;
     }
     return FSIC_OK;
+}
+
+FdmPlan fdm_plan(const fsic_ctx *c, const Batch &b) {
+    FdmPlan p{};
+    for (int q = 0; q < kFdmPasses; ++q) p.units[q] = c->d_fu[q].p;
+    p.ranges = c->d_fr.p;
+    p.cls = b.fcls.data();
+    p.ncls = (int)b.fcls.size();
+    return p;
 }
 
 // The forward pass's device status (copied asynchronously once the
@@ -880,16 +1018,23 @@ fsic_status time_shapes(fsic_ctx *c, const std::vector<Group> &groups, int preci
                         const std::vector<Shape> &cands, Shape &best) {
     hipStream_t s = c->stream;
     Batch b0;
-    build_batch(groups, c->radius, cands[0], b0);
+    build_batch(groups, c->radius, cands[0], b0, precond_of(c, precision));
     fsic_status st = prepare_batch(c, b0, precision);
     if (st) return st;
-    const bool mixed = precision == FSIC_MIXED;
+    const bool mixed = precision == FSIC_MIXED, direct = b0.direct;
     const size_t F = (size_t)b0.fields;
+    if (direct) {
+        // the direct solver's only sweep: the FP64 residual pass
+        HIPCHK(c, hipMemsetAsync(c->B.p, 0, F * sizeof(double), s));
+        HIPCHK(c, hipMemsetAsync(c->R.p, 0, F * sizeof(double), s));
+    }
     T *R = mixed ? (T *)(void *)c->R32.p : (T *)(void *)c->R.p;
     T *P = mixed ? (T *)(void *)c->P32a.p : (T *)(void *)c->P0.p;
     T *Q = mixed ? (T *)(void *)c->Q32.p : (T *)(void *)c->Q.p;
-    HIPCHK(c, hipMemsetAsync(R, 0, F * sizeof(T), s));
-    HIPCHK(c, hipMemsetAsync(P, 0, F * sizeof(T), s));
+    if (!direct) {
+        HIPCHK(c, hipMemsetAsync(R, 0, F * sizeof(T), s));
+        HIPCHK(c, hipMemsetAsync(P, 0, F * sizeof(T), s));
+    }
     const int norb = (int)b0.orb.size();
     HIPCHK(c, hipMemsetAsync(c->done.p, 0, norb * sizeof(int), s));
     HIPCHK(c, hipMemsetAsync(c->part8.p, 0, 2 * (size_t)b0.tot8 * sizeof(double), s));
@@ -903,7 +1048,7 @@ fsic_status time_shapes(fsic_ctx *c, const std::vector<Group> &groups, int preci
     fsic_status res = FSIC_OK;
     for (const Shape &sh : cands) {
         Batch b;
-        build_batch(groups, c->radius, sh, b);
+        build_batch(groups, c->radius, sh, b, kNoPrecond);
         if ((res = upload(c, c->d_orb, b.orb))) break;
         if ((res = upload(c, c->d_items7, b.items7))) break;
         if (c->part7.ensure(3 * (size_t)b.tot7) != hipSuccess) { res = FSIC_ENOMEM; break; }
@@ -917,14 +1062,21 @@ fsic_status time_shapes(fsic_ctx *c, const std::vector<Group> &groups, int preci
         a.part7 = c->part7.p; a.tot7 = b.tot7; a.part8 = c->part8.p; a.tot8 = b.tot8;
         a.partRU = c->partRU.p; a.done = c->done.p; a.iters = c->iters.p; a.rrfin = c->rrfin.p;
         a.bb = c->bb.p; a.nact = c->nact.p; a.norb = norb; a.tol2 = 0.0;
-        hipError_t he = launch_cg_stencil<T>(c->radius, cf, a, 0, 0, 0, s);
+        if (direct && c->partRU.ensure((size_t)b.tot7) != hipSuccess) { res = FSIC_ENOMEM; break; }
+        auto sweep = [&]() {
+            if (direct)
+                return launch_residual64(c->radius, cf, c->d_items7.p, (int)b.items7.size(), c->d_orb.p, nullptr,
+                                         c->R.p, c->B.p, nullptr, c->partRU.p, s);
+            return launch_cg_stencil<T>(c->radius, cf, a, 0, 0, 0, s);
+        };
+        hipError_t he = sweep();
         if (he == hipSuccess) he = hipEventRecord(e0, s);
-        for (int r = 0; r < 3 && he == hipSuccess; ++r) he = launch_cg_stencil<T>(c->radius, cf, a, 0, 0, 0, s);
+        for (int r = 0; r < 3 && he == hipSuccess; ++r) he = sweep();
         if (he == hipSuccess) he = hipEventRecord(e1, s);
         if (he == hipSuccess) he = hipEventSynchronize(e1);
         float ms = 0.f;
         if (he == hipSuccess) he = hipEventElapsedTime(&ms, e0, e1);
-        if (he == hipSuccess && mixed) {
+        if (he == hipSuccess && mixed && !direct) {
             // the FP64 residual pass that closes each mixed restart cycle of
             // two FP32 sweeps (three operand arrays: its best shape differs);
             // it reads B and the FP32 field and writes scratch buffers the
@@ -965,7 +1117,7 @@ fsic_status choose_shape(fsic_ctx *c, const std::vector<Group> &groups, int prec
     c->tune_ms = 0.0;
     if (fixed_shape(c->radius, precision, sh)) return FSIC_OK;
     std::string key = std::to_string(c->device) + ":" + std::to_string(precision) + ":" +
-                      std::to_string(c->radius);
+                      std::to_string(c->radius) + ":" + std::to_string((int)precond_of(c, precision));
     for (const Group &g : groups)
         key += ":" + std::to_string(g.n[0]) + "x" + std::to_string(g.n[1]) + "x" +
                std::to_string(g.n[2]) + "*" + std::to_string(g.count);
@@ -998,12 +1150,27 @@ fsic_status time_dst_layout(fsic_ctx *c, const std::vector<Group> &groups, int p
                             const DstTune &dt, hipEvent_t e0, hipEvent_t e1, float &ms) {
     hipStream_t s = c->stream;
     Batch b;
-    build_batch(groups, c->radius, sh, b, dt);
+    build_batch(groups, c->radius, sh, b, precond_of(c, precision), dt);
     fsic_status st = prepare_batch(c, b, precision);
     if (st) return st;
     const bool mixed = precision == FSIC_MIXED;
     const size_t F = (size_t)b.fields;
     const int norb = (int)b.orb.size();
+    if (b.direct) {
+        // (b is overwritten: its values do not matter to the time)
+        HIPCHK(c, hipMemsetAsync(c->B.p, 0, F * sizeof(double), s));
+        auto solve = [&]() {
+            return launch_fdm(fdm_plan(c, b), c->d_orb.p, nullptr, c->d_ftab.p, c->B.p, 0, 1.0, c->R.p, c->B.p, 0, s);
+        };
+        hipError_t he = solve();
+        if (he == hipSuccess) he = hipEventRecord(e0, s);
+        for (int r = 0; r < 3 && he == hipSuccess; ++r) he = solve();
+        if (he == hipSuccess) he = hipEventRecord(e1, s);
+        if (he == hipSuccess) he = hipEventSynchronize(e1);
+        if (he == hipSuccess) he = hipEventElapsedTime(&ms, e0, e1);
+        if (he != hipSuccess) return set_err(c, FSIC_EHIP, hipGetErrorString(he));
+        return FSIC_OK;
+    }
     HIPCHK(c, hipMemsetAsync(c->done.p, 0, norb * sizeof(int), s));
     // r = 0 and r.z partials of a nonzero pattern (beta finite): the transform
     // passes take the same time for any values
@@ -1038,6 +1205,7 @@ fsic_status time_dst_layout(fsic_ctx *c, const std::vector<Group> &groups, int p
 // 2 two fused-pass blocks per compute unit, 4 two-block z pass, 8 early
 // p_old read, and the transform variant (1-3) times 16
 int dst_layout_bits(const Batch &b) {
+    if (b.direct) return (b.fd_any_fused ? 1 : 0) | 16 * b.dst_fast;
     const bool o2 = b.dst_xy && b.dst_vec && b.dst_xyocc2 && dst_xy_occ2(b.npxy, b.dst_two);
     return (b.dst_xy ? 1 : 0) | (o2 ? 2 : 0) | (b.dst_zocc2 ? 4 : 0) | (b.dst_xy && b.dst_pv ? 8 : 0) |
            16 * b.dst_fast;
@@ -1056,13 +1224,13 @@ fsic_status choose_dst(fsic_ctx *c, const std::vector<Group> &groups, int precis
     if (const char *ea = getenv("FSIC_AUTOTUNE"))
         if (atoi(ea) == 0) return FSIC_OK;
     Batch b0;
-    build_batch(groups, c->radius, sh, b0, dt);
+    build_batch(groups, c->radius, sh, b0, precond_of(c, precision), dt);
     if (!b0.dst_fast) return FSIC_OK;  // solved without the preconditioner
-    // which choices change anything here
-    const bool can_xy = b0.dst_xy;
-    const bool can_xyocc2 = can_xy && b0.dst_vec && dst_xy_occ2(b0.npxy, b0.dst_two);
+    // which choices change anything here (direct solver: the in-plane passes only)
+    const bool can_xy = b0.direct ? b0.fd_any_fused : b0.dst_xy;
+    const bool can_xyocc2 = can_xy && !b0.direct && b0.dst_vec && dst_xy_occ2(b0.npxy, b0.dst_two);
     const bool can_zocc2 = b0.dst_zocc2;
-    const bool can_pv = can_xy && b0.dst_pv && precision == FSIC_MIXED && c->opts.solver == FSIC_PCG;
+    const bool can_pv = can_xy && !b0.direct && b0.dst_pv && precision == FSIC_MIXED && c->opts.solver == FSIC_PCG;
     std::vector<DstTune> cands;
     for (int xy = can_xy ? 1 : 0; xy >= 0; --xy)
         for (int o2 = (xy && can_xyocc2) ? 1 : 0; o2 >= 0; --o2)
@@ -1074,7 +1242,7 @@ fsic_status choose_dst(fsic_ctx *c, const std::vector<Group> &groups, int precis
                 }
     if (cands.size() <= 1) return FSIC_OK;
     std::string key = std::to_string(c->device) + ":" + std::to_string(precision) + ":" +
-                      std::to_string(c->radius) + ":" + std::to_string(c->opts.solver);
+                      std::to_string(c->radius) + ":" + std::to_string((int)precond_of(c, precision));
     for (const char *ev : {"FSIC_DST_XY", "FSIC_DST_PV", "FSIC_DST_BLOCKS"}) {
         const char *e = getenv(ev);
         key += std::string(":") + (e ? e : "-");
@@ -1167,27 +1335,188 @@ fsic_status run_captured(fsic_ctx *c, bool graphs, const GraphKey &key, Body &bo
     return FSIC_OK;
 }
 
-fsic_status solve_batch(fsic_ctx *c, const Batch &b, const double *src, int square, double scale,
-                        bool with_bc, double *X, int precision, double tol, int max_iter,
-                        SolveReport &rep, const double *qlm_in = nullptr) {
+fsic_status solve_krylov(fsic_ctx *c, const Batch &b, const double *src, int square, double scale,
+                         bool with_bc, double *X, int precision, double tol, int max_iter,
+                         SolveReport &rep, const double *qlm_in);
+
+// Boundary term of the right-hand side into Gh: from the moments of the
+// source, or (qlm_in) from given moments (the unit-moment basis solves).
+fsic_status boundary_term(fsic_ctx *c, const Batch &b, const double *src, int square, const double *qlm_in) {
     hipStream_t s = c->stream;
     const int norb = (int)b.orb.size();
-    const int nlm = (c->opts.lmax + 1) * (c->opts.lmax + 1);
+    if (!qlm_in)
+        HIPCHK(c, launch_harm_contract(0, c->opts.lmax, c->ht, c->cf, c->radius, c->d_orb.p, c->d_gcount.p,
+                                       c->d_hcN.p, (int)b.hcN.size(), c->d_hchN.p, (int)b.hchN.size(),
+                                       b.max_group, src, square, c->partH.p, c->Qlm.p, s));
+    HIPCHK(c, launch_harm_expand(0, c->opts.lmax, c->ht, c->radius, c->d_orb.p, c->d_gcount.p, c->d_hcGx.p,
+                                 (int)b.hcGx.size(), qlm_in ? qlm_in : c->Qlm.p, c->Gh.p, s));
+    HIPCHK(c, launch_bterm(c->radius, c->cf, norb, c->d_orb.p, b.max_ghost / c->radius, c->Gh.p, s));
+    return FSIC_OK;
+}
+
+// the statistics of a solve to pinned memory, read by finish_solve
+fsic_status copy_stage(fsic_ctx *c, int norb) {
+    HIPCHK(c, hipMemcpyAsync(c->h_stage, c->d_stage.p, 6 * (size_t)norb * sizeof(double), hipMemcpyDeviceToHost,
+                             c->stream));
+    c->h_si = reinterpret_cast<int *>(c->h_stage);
+    c->h_sd = c->h_stage + 4 * (size_t)norb;
+    return FSIC_OK;
+}
+
+// rounds of the direct solver: the solve and at most two corrections
+constexpr int kDirectRounds = 3;
+
+// FSIC_PCG by the direct solver: x = K^{-1} b, then the FP64 residual.  One
+// application leaves about 1e-13 (40^3) to 1e-12 (192^3) of ||b||; an
+// orbital still above tol gets x += K^{-1} r and the residual recursion
+// r += L d, as in conjugate gradients.  all: every orbital met tol.
+fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int square, double scale, bool with_bc,
+                         double *X, int precision, double tol, int max_iter, SolveReport &rep, const double *qlm_in,
+                         bool &all) {
+    hipStream_t s = c->stream;
+    const int norb = (int)b.orb.size();
+    const int nit7 = (int)b.items7.size(), nit8 = (int)b.items8.size();
+    const bool mixed = precision == FSIC_MIXED, prof = (c->opts.flags & FSIC_PROFILE) != 0;
+    const bool graphs = mixed && (c->opts.flags & FSIC_GRAPHS) && !prof;
+    const double tol2 = tol * tol;
+    all = false;
+    if (with_bc) {
+        const fsic_status st = boundary_term(c, b, src, square, qlm_in);
+        if (st) return st;
+    }
+    HIPCHK(c, launch_rhs(c->radius, c->cf, c->d_items8.p, nit8, c->d_orb.p, src, square, scale,
+                         with_bc ? c->Gh.p : nullptr, c->B.p, nullptr, nullptr, nullptr, c->part8.p, s));
+    HIPCHK(c, launch_reduce_partials(norb, c->d_orb.p, c->part8.p, 0, c->bb.p, s));
+    {
+        const IntFills f{{c->done.p, c->iters.p, c->nact.p, c->ndone.p}, {norb, norb, 6 * norb, 1}, {0, 0, 0, 0}, 4};
+        HIPCHK(c, launch_fill_ints(f, s));
+    }
+    std::vector<ProfRec> &recs = c->recs;
+    recs.clear();
+    if (prof)
+        while (c->ev.size() < 4) {
+            hipEvent_t e;
+            HIPCHK(c, hipEventCreate(&e));
+            c->ev.push_back(e);
+        }
+    const FdmPlan plan = fdm_plan(c, b);
+    auto key_of = [&](int v) {
+        GraphKey key;
+        key.add((long long)(1000 + v));
+        for (const void *p : {(const void *)c->d_orb.p, (const void *)c->d_ftab.p, (const void *)c->B.p,
+                              (const void *)c->R.p, (const void *)X, (const void *)c->d_fr.p,
+                              (const void *)c->d_items7.p, (const void *)c->partRU.p, (const void *)c->bb.p,
+                              (const void *)c->done.p, (const void *)c->iters.p, (const void *)c->rrfin.p,
+                              (const void *)c->ndone.p})
+            key.add(p);
+        for (int q = 0; q < kFdmPasses; ++q) key.add((const void *)c->d_fu[q].p);
+        for (const FdmClass &cl : b.fcls)
+            for (int x : {cl.pass, cl.T, cl.two, cl.blocks, cl.range0}) key.add((long long)x);
+        for (long long x : {(long long)nit7, (long long)norb, (long long)c->radius, (long long)c->cf.cpt,
+                            (long long)c->cf.depth})
+            key.add(x);
+        for (int q = 0; q <= kMaxRadius; ++q) key.add(c->cf.c[q]);
+        key.add(tol2);
+        return key;
+    };
+    // one application, then the residual check (each captured on its own
+    // under FSIC_GRAPHS)
+    auto apply = [&](hipStream_t st) -> fsic_status {
+        HIPCHK(c, launch_fdm(plan, c->d_orb.p, nullptr, c->d_ftab.p, c->B.p, 0, 1.0, c->R.p, X, 0, st));
+        return FSIC_OK;
+    };
+    auto check = [&](hipStream_t st) -> fsic_status {
+        HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, nullptr, X, c->B.p, nullptr,
+                                    c->partRU.p, st));
+        HIPCHK(c, launch_ru_check(norb, c->d_orb.p, c->partRU.p, c->bb.p, tol2, 1, c->done.p, c->iters.p, c->rrfin.p,
+                                  nullptr, c->ndone.p, nullptr, 0, nullptr, 0, st));
+        return FSIC_OK;
+    };
+    auto timed = [&](int kind, int v, auto &body) -> fsic_status {
+        if (prof) {
+            recs.push_back(ProfRec{kind, 0, 0, c->ev[2 * v], c->ev[2 * v + 1]});
+            HIPCHK(c, hipEventRecord(recs.back().a, s));
+        }
+        const fsic_status st = run_captured(c, graphs, graphs ? key_of(v) : GraphKey{}, body, s);
+        if (st) return st;
+        if (prof) HIPCHK(c, hipEventRecord(recs.back().b, s));
+        return FSIC_OK;
+    };
+    fsic_status st = timed(2, 0, apply);
+    if (!st) st = timed(3, 1, check);
+    if (st) return st;
+    auto count = [&]() -> fsic_status {
+        HIPCHK(c, hipMemcpyAsync(c->h_nd, c->ndone.p, sizeof(int), hipMemcpyDeviceToHost, s));
+        HIPCHK(c, hipEventRecord(c->evc[0], s));
+        HIPCHK(c, hipEventSynchronize(c->evc[0]));
+        all = c->h_nd[0] >= norb;
+        return FSIC_OK;
+    };
+    if ((st = count())) return st;
+    int rounds = 1;
+    for (; !all && rounds < std::min(kDirectRounds, max_iter) && !status_error(c); ++rounds) {
+        const size_t F = (size_t)b.fields;
+        HIPCHK(c, c->Q.ensure(F));   // r
+        HIPCHK(c, c->P0.ensure(F));  // d = K^{-1} r
+        if (rounds == 1)
+            HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, c->done.p, X, c->B.p,
+                                        c->Q.p, c->partRU.p, s));
+        HIPCHK(c, launch_fdm(plan, c->d_orb.p, c->done.p, c->d_ftab.p, c->Q.p, 0, 1.0, c->R.p, c->P0.p, 0, s));
+        HIPCHK(c, launch_add_fields(nit8, c->d_items8.p, c->d_orb.p, c->done.p, X, c->P0.p, s));
+        HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, c->done.p, c->P0.p, c->Q.p,
+                                    c->Q.p, c->partRU.p, s));
+        HIPCHK(c, launch_ru_check(norb, c->d_orb.p, c->partRU.p, c->bb.p, tol2, rounds + 1, c->done.p, c->iters.p,
+                                  c->rrfin.p, nullptr, c->ndone.p, nullptr, 0, nullptr, 0, s));
+        if ((st = count())) return st;
+    }
+    if (!all && !status_error(c)) return FSIC_OK;
+    all = true;
+    if (mixed) rep.refinements += rounds;
+    if (rounds > 1)  // the residual that is reported is that of x, not of the recursion
+        HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, nullptr, X, c->B.p, nullptr,
+                                    c->partRU.p, s));
+    HIPCHK(c, launch_reduce_partials(norb, c->d_orb.p, c->partRU.p, 1, c->ptrue.p, s));
+    HIPCHK(c, c->d_stage.ensure(6 * (size_t)std::max(norb, 1)));
+    HIPCHK(c, launch_stage_stats(norb, c->iters.p, c->nact.p, c->done.p, c->ptrue.p, c->bb.p, c->d_stage.p, s));
+    if ((st = copy_stage(c, norb))) return st;
+    c->pend_prof = prof;
+    c->pend_aar = false;
+    c->pend_pcg = true;
+    c->pend_mixed = mixed;
+    c->pend_direct = true;
+    return FSIC_OK;
+}
+
+fsic_status solve_batch(fsic_ctx *c, const Batch &b, const double *src, int square, double scale, bool with_bc,
+                        double *X, int precision, double tol, int max_iter, SolveReport &rep,
+                        const double *qlm_in = nullptr) {
+    if (!b.direct) return solve_krylov(c, b, src, square, scale, with_bc, X, precision, tol, max_iter, rep, qlm_in);
+    bool all = false;
+    fsic_status st = solve_direct(c, b, src, square, scale, with_bc, X, precision, tol, max_iter, rep, qlm_in, all);
+    if (st || all) return st;
+    // an orbital the direct solver does not bring to tol (non-finite data):
+    // conjugate gradients with the sine-transform preconditioner decide
+    Batch bk = b;
+    bk.direct = false;
+    build_sine(bk, c->radius, DstTune{});
+    if ((st = prepare_batch(c, bk, precision))) return st;
+    if ((st = solve_krylov(c, bk, src, square, scale, with_bc, X, precision, tol, max_iter, rep, qlm_in))) return st;
+    HIPCHK(c, hipStreamSynchronize(c->stream));  // bk's tables are in flight until here
+    return FSIC_OK;
+}
+
+fsic_status solve_krylov(fsic_ctx *c, const Batch &b, const double *src, int square, double scale,
+                         bool with_bc, double *X, int precision, double tol, int max_iter,
+                         SolveReport &rep, const double *qlm_in) {
+    hipStream_t s = c->stream;
+    const int norb = (int)b.orb.size();
     const int nit7 = (int)b.items7.size(), nit8 = (int)b.items8.size();
     const bool mixed = precision == FSIC_MIXED;
     bool staged = false;  // statistics staged by the solve's own last launch
     if (with_bc) {
-        // boundary values from the moments of the source, or (qlm_in) from
-        // given moments (the unit-moment basis solves, src null)
-        if (!qlm_in)
-            HIPCHK(c, launch_harm_contract(0, c->opts.lmax, c->ht, c->cf, c->radius, c->d_orb.p, c->d_gcount.p,
-                                           c->d_hcN.p, (int)b.hcN.size(), c->d_hchN.p, (int)b.hchN.size(),
-                                           b.max_group, src, square, c->partH.p, c->Qlm.p, s));
-        HIPCHK(c, launch_harm_expand(0, c->opts.lmax, c->ht, c->radius, c->d_orb.p, c->d_gcount.p, c->d_hcGx.p,
-                                     (int)b.hcGx.size(), qlm_in ? qlm_in : c->Qlm.p, c->Gh.p, s));
-        HIPCHK(c, launch_bterm(c->radius, c->cf, norb, c->d_orb.p, b.max_ghost / c->radius, c->Gh.p, s));
+        const fsic_status bst = boundary_term(c, b, src, square, qlm_in);
+        if (bst) return bst;
     }
-    (void)nlm;
     // b, r0 = b, x64 = 0 (mixed), ||b||^2 partials in part8 slot 0
     HIPCHK(c, launch_rhs(c->radius, c->cf, c->d_items8.p, nit8, c->d_orb.p, src, square, scale,
                          with_bc ? c->Gh.p : nullptr, c->B.p, mixed ? nullptr : c->R.p,
@@ -1607,9 +1936,9 @@ fsic_status solve_batch(fsic_ctx *c, const Batch &b, const double *src, int squa
     HIPCHK(c, c->d_stage.ensure(6 * (size_t)std::max(norb, 1)));
     if (!staged)
         HIPCHK(c, launch_stage_stats(norb, c->iters.p, c->nact.p, c->done.p, c->ptrue.p, c->bb.p, c->d_stage.p, s));
-    HIPCHK(c, hipMemcpyAsync(c->h_stage, c->d_stage.p, 6 * (size_t)norb * sizeof(double), hipMemcpyDeviceToHost, s));
-    c->h_si = reinterpret_cast<int *>(c->h_stage);
-    c->h_sd = c->h_stage + 4 * (size_t)norb;
+    const fsic_status cst = copy_stage(c, norb);
+    if (cst) return cst;
+    c->pend_direct = false;
     c->pend_prof = prof;
     c->pend_aar = use_aar(c, b);
     c->pend_pcg = pcg;
@@ -1631,7 +1960,7 @@ fsic_status finish_solve(fsic_ctx *c, const Batch &b, SolveReport &rep) {
     for (int o = 0; o < norb; ++o) {
         // stencil sweeps that did work for this orbital (AAR: residual
         // evaluations before convergence)
-        const int itv = c->pend_aar ? it[o] : na[o];
+        const int itv = c->pend_aar || c->pend_direct ? it[o] : na[o];
         rep.max_iters = std::max(rep.max_iters, itv);
         rep.total_iters += itv;
         const double rr = bbh[o] > 0 ? std::sqrt(pt[o] / bbh[o]) : 0.0;
@@ -1664,7 +1993,15 @@ fsic_status finish_solve(fsic_ctx *c, const Batch &b, SolveReport &rep) {
             const OrbDesc &od = b.orb[o];
             const double Mo = (double)od.nx * od.ny * od.nz;
             const double ns = na[2 * (size_t)norb + o], nu = na[3 * (size_t)norb + o];
-            if (pcg && mixed) {
+            if (c->pend_direct) {
+                // one application and one residual pass: the fused passes read
+                // and write a value three times, the one-axis passes five
+                // times; each axis is transformed forward and back, n flops a
+                // value; the residual pass reads x and b
+                c->precond_bytes += Mo * (od.fd_fused ? 48.0 : 80.0);
+                c->precond_flops += Mo * 2.0 * (od.nx + od.ny + od.nz);
+                c->resid_bytes += Mo * 16.0;
+            } else if (pcg && mixed) {
                 // restart cycles (sampled: the last iteration of every cycle
                 // but the first, and its residual pass): the sweep reads p and
                 // writes q; the update reads r, q and writes r; the
@@ -1785,6 +2122,8 @@ void fsic_destroy(fsic_ctx *c) {
     c->Z32.release(); c->T32.release(); c->dtab.release(); c->partRZ.release();
     c->Fprev.release(); c->Fh.release(); c->Xh.release(); c->aar_gamma.release(); c->partD.release();
     c->d_dx.release(); c->d_dy.release(); c->d_dz.release(); c->d_dxy.release();
+    for (auto &d : c->d_fu) d.release();
+    c->d_fr.release(); c->d_ftab.release();
     c->Gh.release(); c->part7.release(); c->part8.release(); c->partRU.release();
     c->partH.release(); c->d_hcN.release(); c->d_hcG.release(); c->d_hcNx.release(); c->d_hcGx.release(); c->d_hchN.release(); c->d_hchG.release();
     c->bb.release(); c->rrfin.release();
@@ -1834,7 +2173,7 @@ static fsic_status boundary_basis(fsic_ctx *c, const Chan &ch, const Shape &sh, 
     for (int d = 0; d < 3; ++d) { g.n[d] = ch.n[d]; g.origin[d] = ch.origin[d]; }
     g.h = ch.h; g.count = nlm; g.off = 0; g.chan = 0;
     Batch bb;
-    build_batch({g}, c->radius, sh, bb, dt, c->opts.lmax);
+    build_batch({g}, c->radius, sh, bb, precond_of(c, FSIC_FP64), dt, c->opts.lmax);
     fsic_status st = prepare_batch(c, bb, FSIC_FP64);
     if (st) return st;
     std::vector<double> ident((size_t)nlm * nlm, 0.0);
@@ -1978,7 +2317,7 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
         if (use_basis)
             for (int ci = 0; ci < nchan; ++ci)
                 if ((tst = boundary_basis(c, chans[ci], sh, dt, &basisU[ci]))) return tst;
-        build_batch(groups, P, sh, b, dt, o.lmax);
+        build_batch(groups, P, sh, b, precond_of(c, o.precision), dt, o.lmax);
         c->dst_layout = dst_layout_bits(b);
     }
     // channel descriptors for the average pass
@@ -2293,7 +2632,7 @@ fsic_status fsic_op_laplacian(const int32_t *n, double h, int32_t fd_order, int3
     for (int d = 0; d < 3; ++d) { groups[0].n[d] = n[d]; groups[0].origin[d] = 0.0; }
     groups[0].h = h; groups[0].count = count; groups[0].off = 0; groups[0].chan = 0;
     Batch b;
-    build_batch(groups, P, Shape{2, 2, 4096}, b);  // fd_weights: cpt 2, depth 2
+    build_batch(groups, P, Shape{2, 2, 4096}, b, kNoPrecond);  // fd_weights: cpt 2, depth 2
     hipStream_t s = (hipStream_t)hip_stream;
     DBuf<OrbDesc> dorb;
     DBuf<Item> dit;
@@ -2319,7 +2658,7 @@ fsic_status fsic_op_hamiltonian(const int32_t *n, double h, int32_t fd_order, in
     for (int d = 0; d < 3; ++d) { groups[0].n[d] = n[d]; groups[0].origin[d] = 0.0; }
     groups[0].h = h; groups[0].count = count; groups[0].off = 0; groups[0].chan = 0;
     Batch b;
-    build_batch(groups, P, Shape{2, 2, 4096}, b);  // fd_weights: cpt 2, depth 2
+    build_batch(groups, P, Shape{2, 2, 4096}, b, kNoPrecond);  // fd_weights: cpt 2, depth 2
     hipStream_t s = (hipStream_t)hip_stream;
     DBuf<OrbDesc> dorb;
     DBuf<Item> dit;
@@ -2345,7 +2684,7 @@ fsic_status fsic_op_laplacian_f32(const int32_t *n, double h, int32_t fd_order, 
     for (int d = 0; d < 3; ++d) { groups[0].n[d] = n[d]; groups[0].origin[d] = 0.0; }
     groups[0].h = h; groups[0].count = count; groups[0].off = 0; groups[0].chan = 0;
     Batch b;
-    build_batch(groups, P, Shape{2, 2, 4096}, b);  // fd_weights: cpt 2, depth 2
+    build_batch(groups, P, Shape{2, 2, 4096}, b, kNoPrecond);  // fd_weights: cpt 2, depth 2
     hipStream_t s = (hipStream_t)hip_stream;
     DBuf<OrbDesc> dorb;
     DBuf<Item> dit;
@@ -2398,7 +2737,7 @@ fsic_status fsic_op_poisson(const fsic_grid *grid, int32_t fd_order, int32_t lma
     c->cf.depth = sh.depth;
     DstTune dt;
     if ((st = choose_dst(c, groups, precision, sh, dt))) return st;
-    build_batch(groups, c->radius, sh, b, dt, lmax);
+    build_batch(groups, c->radius, sh, b, precond_of(c, precision), dt, lmax);
     st = prepare_batch(c, b, precision);
     if (st) return st;
     SolveReport rep;

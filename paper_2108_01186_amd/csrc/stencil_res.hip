@@ -83,6 +83,45 @@ hipError_t launch_true_residual(int radius, const Coeffs &c, const Item *items7,
     return hipGetLastError();
 }
 
+hipError_t launch_residual64(int radius, const Coeffs &c, const Item *items7, int nitems7, const OrbDesc *orb,
+                             const int *done, const double *x, const double *b, double *res, double *partRU,
+                             hipStream_t s) {
+    if (nitems7 <= 0) return hipSuccess;
+    if (res) {
+        PolRes64<true> pol{items7, orb, done, x, b, res, partRU, false};
+#define CALL(P, C, DD) hipLaunchKernelGGL((k_zmarch<double, P, C, DD, PolRes64<true>>), dim3(nitems7), dim3(256), 0, s, pol, c)
+        FSIC_RADIUS_SWITCH(radius, CALL)
+#undef CALL
+    } else {
+        PolRes64<false> pol{items7, orb, done, x, b, res, partRU, false};
+#define CALL(P, C, DD) hipLaunchKernelGGL((k_zmarch<double, P, C, DD, PolRes64<false>>), dim3(nitems7), dim3(256), 0, s, pol, c)
+        FSIC_RADIUS_SWITCH(radius, CALL)
+#undef CALL
+    }
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void k_add_fields(const Item *items8, const OrbDesc *orb, const int *done, double *x,
+                                                    const double *d) {
+    const Item it = items8[blockIdx.x];
+    if (it.orb < 0 || done[it.orb] == 1) return;
+    const OrbDesc od = orb[it.orb];
+    const long long M = (long long)od.nx * od.ny * od.nz;
+    const long long base = (long long)it.tile * kPW;
+#pragma unroll
+    for (int e = 0; e < kPW / 256; ++e) {
+        const long long i = base + e * 256 + threadIdx.x;
+        if (i < M) x[od.off + i] += d[od.off + i];
+    }
+}
+
+hipError_t launch_add_fields(int nitems8, const Item *items8, const OrbDesc *orb, const int *done, double *x,
+                             const double *d, hipStream_t s) {
+    if (nitems8 <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_add_fields, dim3(nitems8), dim3(256), 0, s, items8, orb, done, x, d);
+    return hipGetLastError();
+}
+
 hipError_t launch_reduce_partials(int norb, const OrbDesc *orb, const double *part,
                                   int stencil_layout, double *out, hipStream_t s) {
     if (norb <= 0) return hipSuccess;

@@ -597,6 +597,41 @@ struct PolRes {  // res = b + L x, x = x64 (+ x32); X64 null (with x32): x64 = 0
     }
 };
 
+// res = b + L x of the direct solver, FP64 throughout; res null: only the
+// partial sums.  res may be b: a block reads b at its own nodes only.
+template <bool WR>
+struct PolRes64 {
+    const Item *items;
+    const OrbDesc *orb;
+    const int *done;
+    const double *x, *b;
+    double *res, *partRU;
+    struct Raw { double a; };
+    typedef double Ext;
+    typedef double Acc;
+    bool tile0;
+    Rsrc rx, rb, rr;
+    __device__ bool setup(int o, const OrbDesc &, double *) { return done == nullptr || done[o] != 1; }
+    __device__ void init(const OrbDesc &od) {
+        const unsigned bytes = (unsigned)((long long)od.nx * od.ny * od.nz * 8);
+        rx = make_rsrc(x + od.off, bytes);
+        rb = make_rsrc(b + od.off, bytes);
+        if constexpr (WR) rr = make_rsrc(res + od.off, bytes);
+    }
+    __device__ Raw raw(unsigned i, int zo) const { return Raw{bld<double>(rx, i, zo)}; }
+    __device__ Ext ext(unsigned i, int zo) const { return bld<double>(rb, i, zo); }
+    __device__ double combine(const Raw &v) const { return v.a; }
+    __device__ void epilogue(unsigned i, int zo, double, double lap, const Ext &bv, Acc &s) const {
+        const double r = bv + lap;
+        if constexpr (WR) bst(rr, i, zo, r);
+        s += r * r;
+    }
+    __device__ void finish(const Item &it, const OrbDesc &od, const Acc &s, double *sred) const {
+        const double t = block_sum256(s, sred);
+        if (threadIdx.x == 0) partRU[od.base7 + it.tile] = t;
+    }
+};
+
 // ---------------------------------------------------------------------------
 // pointwise CG update
 // ---------------------------------------------------------------------------

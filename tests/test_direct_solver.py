@@ -1,0 +1,131 @@
+"""The direct Poisson solver (fast diagonalisation, csrc/fdm.hip): its axis
+tables on the CPU, and its solutions at the sizes where the kernels change
+shape (edges of the 16-row tiles, the longest axis of each instantiation, odd
+and unequal axes) against the oracle."""
+import math
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2108_01186_amd", "csrc")
+
+
+def _weights(p):
+    f = math.factorial
+    c = [0.0] + [2.0 * (-1.0) ** (k + 1) * f(p) ** 2 / (k * k * f(p - k) * f(p + k)) for k in range(1, p + 1)]
+    c[0] = -2.0 * sum(c[1:])
+    return c
+
+
+@pytest.fixture(scope="module")
+def table_program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("fdm")
+    src = d / "t.cpp"
+    src.write_text('#include "fdm_basis.h"\n#include <cstdio>\n#include <cstdlib>\n'
+                   "int main(int, char **a) { int p = atoi(a[2]); std::vector<double> c;\n"
+                   "for (int i = 0; i <= p; ++i) c.push_back(atof(a[3 + i]));\n"
+                   "auto t = fsic::fdm_axis_table(atoi(a[1]), p, c.data());\n"
+                   "fwrite(t.data(), 8, t.size(), stdout); }\n")
+    exe = str(d / "t")
+    subprocess.run(["g++", "-O2", "-I" + CSRC, str(src), "-o", exe], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("n,p", [(8, 6), (9, 1), (32, 6), (33, 6), (40, 4), (96, 6), (161, 6), (192, 6)])
+def test_axis_tables_diagonalise_the_axis_operator(table_program, n, p):
+    """The table holds orthonormal even and odd eigenvectors of the band
+    matrix, each rounded once to FP64: the products below differ from the
+    identity and the eigenvalues by a sum of n rounding errors."""
+    c = _weights(p)
+    t = np.frombuffer(subprocess.run([table_program, str(n), str(p)] + ["%.17g" % x for x in c], check=True,
+                                     capture_output=True).stdout)
+    he, ho = (n + 1) // 2, n // 2
+    L = 16 * ((he + 15) // 16)
+    assert t.size == 2 * L * L + 2 * L
+    C, lam = t[:2 * L * L].reshape(2, L, L), t[2 * L * L:].reshape(2, L)
+    assert not C[0, he:].any() and not C[0, :, he:].any() and not C[1, ho:].any() and not C[1, :, ho:].any()
+    assert np.all(lam[0, he:] == 1) and np.all(lam[1, ho:] == 1)
+    Q = np.zeros((n, n))
+    Q[:he, :he] = C[0, :he, :he]
+    Q[:he, n - he:] = C[0, :he, :he][:, ::-1]
+    Q[he:, :ho] = C[1, :ho, :ho]
+    Q[he:, n - ho:] = -C[1, :ho, :ho][:, ::-1]
+    ev = np.concatenate([lam[0, :he], lam[1, :ho]])
+    K = np.zeros((n, n))
+    for k in range(p + 1):
+        if k < n:
+            K -= c[k] * (np.eye(n, k=k) + np.eye(n, k=-k)) * (0.5 if k == 0 else 1.0)
+    eps = np.finfo(float).eps
+    assert np.abs(Q @ Q.T - np.eye(n)).max() < n * eps
+    assert np.abs(Q @ K @ Q.T - np.diag(ev)).max() < n * eps * ev.max()
+    assert ev.min() > 0
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,fd_order", [((8, 9, 10), 2), ((32, 33, 31), 12), ((31, 32, 64), 8), ((65, 64, 33), 12),
+                                        ((96, 96, 17), 12), ((97, 95, 16), 12), ((128, 128, 9), 12),
+                                        ((127, 127, 34), 12), ((128, 100, 12), 12), ((129, 20, 18), 12),
+                                        ((160, 12, 161), 12), ((14, 192, 12), 6), ((12, 13, 192), 12),
+                                        ((192, 161, 9), 12)])
+def test_direct_solution_vs_oracle(torch_cuda, oracle, n, fd_order):
+    """Three off-centre charges per grid, both precisions: the FP64 residual
+    meets 1e-11 in one application (iterations = 1) where FP64 allows it, and
+    the potentials match the oracle's to 1e-9 of their largest value (relative
+    residuals of 1e-11 and 1e-13 leave that much at these sizes)."""
+    from paper_2108_01186_amd import fsic as F
+    torch = torch_cuda
+    print(f"direct solver {n} order {fd_order}", flush=True)
+    h = 0.28
+    origin = np.array([-h * (m - 1) / 2 for m in n])
+    ax = [origin[d] + h * np.arange(n[d]) for d in range(3)]
+    rhos = []
+    for f, s in ((0.1, 0.7), (-0.15, 0.5), (0.02, 0.9)):
+        r2 = sum(((ax[d] - f * h * n[d]).reshape([-1 if e == 2 - d else 1 for e in range(3)])) ** 2 for d in range(3))
+        rhos.append((np.exp(-r2 / (2 * s * s)) / (2 * np.pi * s * s) ** 1.5).reshape(-1))
+    rho = np.stack(rhos)
+    refs = [oracle.poisson(r, n, h, origin, p=fd_order // 2)[0] for r in rhos]
+    for precision in ("fp64", "mixed"):
+        v, it, rr = F.op_poisson(torch.tensor(rho, device="cuda"), n, h, origin, fd_order=fd_order, tol=1e-11,
+                                 precision=precision, solver="pcg")
+        assert np.all(rr <= 1e-11) and np.all(it <= 2), (rr, it)
+        v = v.cpu().numpy()
+        for f in range(3):
+            assert np.abs(v[f] - refs[f]).max() < 1e-9 * np.abs(refs[f]).max(), (precision, f)
+
+
+@pytest.mark.gpu
+def test_nonfinite_density_does_not_reach_other_orbitals(torch_cuda):
+    """A density with a NaN fails to converge; the others, solved in the same
+    launches (and the same blocks), come out as without it."""
+    from paper_2108_01186_amd import fsic as F
+    torch = torch_cuda
+    print("direct solver with a NaN density", flush=True)
+    n, h = (24, 22, 20), 0.3
+    origin = np.array([-h * (m - 1) / 2 for m in n])
+    rng = np.random.default_rng(3)
+    rho = rng.random((6, n[0] * n[1] * n[2]))
+    good = F.op_poisson(torch.tensor(rho, device="cuda"), n, h, origin, solver="pcg")[0].cpu().numpy()
+    bad = rho.copy()
+    bad[2, 777] = np.nan
+    import ctypes
+    t = torch.tensor(bad, device="cuda")
+    v = torch.empty_like(t)
+    g = F.make_grid(n, h, origin)
+    st = F.fsic_op_poisson(ctypes.byref(g), 12, 6, 6, ctypes.c_void_p(t.data_ptr()), ctypes.c_void_p(v.data_ptr()),
+                           1e-10, 20, F.FSIC_FP64, F.FSIC_PCG, None, None,
+                           ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert st == F.FSIC_ENOCONV
+    v = v.cpu().numpy()
+    for k in (0, 1, 3, 4, 5):
+        assert np.abs(v[k] - good[k]).max() < 1e-8 * np.abs(good[k]).max(), k
