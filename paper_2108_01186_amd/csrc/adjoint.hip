@@ -23,13 +23,14 @@ namespace fsic {
 
 
 // Small N (at most two 16-row tiles): B[i][a] = sum_m Gam_i(m) psi_a(m),
-// Gam formed on the fly; block b sums the node range [b chunk, (b+1) chunk)
+// Gam given (in place of PHI) or formed on the fly; block b sums the node range [b chunk, (b+1) chunk)
 // (chunk a multiple of 64).  Every wave forms all the tiles over its own
 // 16-node groups; lane (row r = l % 16, q = l / 16) holds nodes g + 4q ..
 // g + 4q + 3 of row r (32 contiguous bytes: the four lanes of a row read one
 // 128-byte line), and k-step j of a group contracts node g + 4q + j (any
 // assignment of nodes to k-steps splits the sum, as long as both operands
 // use the same one).  The four waves' tiles are added in LDS at the end.
+template <bool GIVEN>
 __global__ __launch_bounds__(256) void k_adj_contract_small(int N, long long M, long long chunk, double dV,
                                                             const double *PHI, const double *V,
                                                             const double *W, const double *psi,
@@ -67,12 +68,17 @@ __global__ __launch_bounds__(256) void k_adj_contract_small(int N, long long M, 
             if (a < Nt && i < N && mb < m1) {
                 double ph[4], vv[4], ww[4];
                 load4(PHI, i, mb, ph);
-                load4(V, i, mb, vv);
-                load4(W, i, mb, ww);
+                if constexpr (GIVEN) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const double om = -(0.5 * (vv[j] + ww[j]) + vxc_pol(ph[j] * ph[j], floor));
-                    gam[a][j] = 2.0 * dV * ph[j] * om;  // zero past m1 (ph = 0 there)
+                    for (int j = 0; j < 4; ++j) gam[a][j] = ph[j];
+                } else {
+                    load4(V, i, mb, vv);
+                    load4(W, i, mb, ww);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const double om = -(0.5 * (vv[j] + ww[j]) + vxc_pol(ph[j] * ph[j], floor));
+                        gam[a][j] = 2.0 * dV * ph[j] * om;  // zero past m1 (ph = 0 there)
+                    }
                 }
             }
         }
@@ -258,6 +264,26 @@ hipError_t launch_lowdin_backward_batch(const LowdinBwdBatch &lb, const double *
     return hipGetLastError();
 }
 
+hipError_t launch_gamma_contract(int N, long long M, const double *Gam, const double *psi, double *partB, size_t cap,
+                                 double *Bm, hipStream_t s) {
+    if (N < 1 || N > kMaxOrb) return hipErrorInvalidValue;
+    const int nblk = grid_blocks(N, M, cap);
+    long long chunk = (M + nblk - 1) / nblk;
+    if (N <= 32) {
+        chunk = (chunk + 63) & ~63LL;
+        const int vec = (M & 1) == 0 && ((reinterpret_cast<uintptr_t>(Gam) | reinterpret_cast<uintptr_t>(psi)) & 15) == 0;
+        hipLaunchKernelGGL(k_adj_contract_small<true>, dim3(nblk), dim3(256), 0, s, N, M, chunk, 0.0, Gam, nullptr,
+                           nullptr, psi, 0.0, vec, partB);
+    } else {
+        chunk = (chunk + kTK - 1) / kTK * kTK;
+        const size_t lds = tsg_lds_bytes(N, 2);
+        if (lds > 65536) hipFuncSetAttribute((const void *)k_tsg_nt<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL(k_tsg_nt<false>, dim3(nblk), dim3(256), lds, s, N, M, chunk, Gam, psi, partB);
+    }
+    hipLaunchKernelGGL(k_adj_contract_final, dim3(N * N), dim3(256), 0, s, N, nblk, partB, Bm);
+    return hipGetLastError();
+}
+
 hipError_t launch_adjoint_contract(int N, long long M, double dV, const double *PHI, const double *V,
                                     const double *W, const double *psi, double floor, double *partB,
                                     size_t cap, double *Bm, double *Gam, hipStream_t s) {
@@ -272,7 +298,7 @@ hipError_t launch_adjoint_contract(int N, long long M, double dV, const double *
                                           15) == 0)
                             ? 1
                             : 0;
-        hipLaunchKernelGGL(k_adj_contract_small, dim3(nblk), dim3(256), 0, s, N, M, chunk, dV, PHI, V, W, psi,
+        hipLaunchKernelGGL(k_adj_contract_small<false>, dim3(nblk), dim3(256), 0, s, N, M, chunk, dV, PHI, V, W, psi,
                            floor, vec, partB);
         hipLaunchKernelGGL(k_adj_contract_final, dim3(N * N), dim3(256), 0, s, N, nblk, partB, Bm);
         return hipGetLastError();

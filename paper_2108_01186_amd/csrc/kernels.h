@@ -135,15 +135,6 @@ struct ResStep {
 hipError_t launch_res_steps(int radius, const Coeffs &c, const CGIter<float> &a, const ResStep &rs,
                             hipStream_t s);
 
-// v_o = w_o + sum_q Q[first + o][q] U_q (q < (lmax + 1)^2) for N
-// consecutive orbitals on one grid of n[0] x n[1] x n[2] nodes: U holds the
-// first octant of the grid's unit-moment boundary solutions (q-major,
-// ceil(n/2) per axis, x fastest; the rest follows from their parities under
-// the axis reflections); W and V point at the first orbital
-hipError_t launch_bc_combine(int N, const int *n, int lmax, const double *Q, int first, const double *U,
-                             const double *W, double *V, hipStream_t s);
-// Uc = the first octant of nlm full-grid fields U (the layout launch_bc_combine reads)
-hipError_t launch_octant_pack(int nlm, const int *n, const double *U, double *Uc, hipStream_t s);
 // The host checks' inputs of up to kChkPack channels, packed one after the
 // other for one copy to the host: channel e's G (N x N), info (2) and
 // rho(a) (N) from small + so[e] (+ oG, oI, oR) to out + q[e].
@@ -446,6 +437,57 @@ hipError_t launch_orb_gemm32(int N, long long M, const double *A, const double *
 // Nodes of one channel per block of the Slater average (its partial sums
 // come one per such block).
 constexpr int kSicTile = 1024;
+
+// ----------------------------------------------------------------------------
+// octant.hip: boundary coefficients and the Slater step on the first octant
+// ----------------------------------------------------------------------------
+
+constexpr int kOctMomentNodes = 32;
+// Consecutive channels on one grid whose fields follow each other.
+struct OctGroup {
+    int nx, ny, nz;
+    int n;             // orbitals of the group
+    int ot;            // their 16-orbital tiles in the moments
+    int chan0, nchan;  // channels (at most two)
+    int tile0[2];      // first 16-orbital fragment tile of each channel
+    long long off, M;
+    const double *U;   // octant fields [q][node]: unit-moment boundary solutions
+    const double *H;   // dV r^l Y_lm
+    size_t poff;       // partial sums of the moments
+};
+// a block's octant nodes (steps [t0, t1) of kOctMomentNodes in the moments,
+// of 16 in the Slater step), its orbital tile (moments) and partial-sum slot
+struct OctItem {
+    int group, ot0, t0, t1, slot;
+};
+// a 16-orbital fragment tile of a channel
+struct OctTile {
+    int n;       // orbitals in it
+    int gorb;    // group index of its first
+    int ot, nparts;
+    size_t poff;
+};
+// k steps of the fragments at an order
+int oct_steps(int lmax);
+// blocks the current device holds at once (kind 0 moments, 1 Slater step
+// with at most group_tiles fragment tiles in a group)
+int oct_slots(int kind, int lmax, int group_tiles);
+// Q_q,i = sum H_q phi_i^2 and zt_q,i = sum U_q phi_i^2 as operand fragments
+// frag[2][ntiles][oct_steps][64]
+hipError_t launch_oct_moments(int lmax, const OctItem *items, int nitems, const OctGroup *groups, const OctTile *tiles,
+                              int ntiles, const double *PHI, double *part, double *frag, hipStream_t s);
+// from phi and w (K w = 4 pi phi^2, zero boundary): U and X partials per
+// block and orbital, V_SIC (want_v), and w := Gam (the adjoint source)
+struct ChanDesc;
+hipError_t launch_sic_octant(int lmax, const OctItem *items, int nitems, const OctGroup *groups, const ChanDesc *chans,
+                             int ntiles, int group_tiles, const double *frag, const double *PHI, double *W,
+                             double floor, int want_v, double *partU, double *partX, hipStream_t s);
+// Uc = the first octant (ceil(n/2) nodes per axis, x fastest) of nlm full-grid fields
+hipError_t launch_octant_pack(int nlm, const int *n, const double *U, double *Uc, hipStream_t s);
+
+// B[i][a] = sum_m Gam_i(m) psi_a(m) for a given Gam (N x M)
+hipError_t launch_gamma_contract(int N, long long M, const double *Gam, const double *psi, double *partB, size_t cap,
+                                 double *Bm, hipStream_t s);
 
 // B[i][a] = sum_m Gam_i(m) psi_a(m) with Gam_i = 2 dV phi_i omega_i,
 // omega_i = -((v_i + w_i) / 2 + vxc(phi_i^2)), contracted on the matrix cores

@@ -325,11 +325,19 @@ struct fsic_ctx {
     Batch batch;
     int nsys = 0;
     bool tape = false;
-    // W holds the zero-boundary solutions of the last forward pass (the
-    // adjoint fields), until a backward pass overwrites it
+    // W holds the adjoint source Gam of the last forward pass, for the first
+    // backward pass
     bool w_ready = false;
-    // unit-moment boundary solutions per grid (n, h bits, lmax, radius):
-    // (lmax + 1)^2 fields of the grid's size, solved once
+    // the tape is of a forward pass with the boundary basis: its groups,
+    // blocks and fragments (octant.hip) are on the device
+    bool tape_basis = false;
+    DBuf<OctGroup> d_octg;
+    DBuf<OctItem> d_octm, d_octs;  // blocks of the moments and of the Slater step
+    DBuf<OctTile> d_octt;
+    DBuf<double> octpart, octfrag;
+    int n_octs = 0, n_octt = 0, oct_gtiles = 0;
+    // octants of the unit-moment boundary solutions and of the harmonics per
+    // grid (n, h bits, lmax, radius), solved once
     std::map<std::array<long long, 6>, DBuf<double>> bbasis;
     DBuf<double> qident;  // identity moments of the basis solves
     int basis_solves = 0;
@@ -2124,6 +2132,8 @@ void fsic_destroy(fsic_ctx *c) {
     c->d_dx.release(); c->d_dy.release(); c->d_dz.release(); c->d_dxy.release();
     for (auto &d : c->d_fu) d.release();
     c->d_fr.release(); c->d_ftab.release();
+    c->d_octg.release(); c->d_octm.release(); c->d_octs.release(); c->d_octt.release();
+    c->octpart.release(); c->octfrag.release();
     c->Gh.release(); c->part7.release(); c->part8.release(); c->partRU.release();
     c->partH.release(); c->d_hcN.release(); c->d_hcG.release(); c->d_hcNx.release(); c->d_hcGx.release(); c->d_hchN.release(); c->d_hchG.release();
     c->bb.release(); c->rrfin.release();
@@ -2147,6 +2157,10 @@ void fsic_destroy(fsic_ctx *c) {
         if (e) hipEventDestroy(e);
     c->ndone.release(); c->fin.release(); c->pz.release();
     delete c;
+}
+
+static size_t octant_nodes(const int *n) {
+    return (size_t)((n[0] + 1) / 2) * ((n[1] + 1) / 2) * ((n[2] + 1) / 2);
 }
 
 // The unit-moment boundary solutions U_q (q < (lmax + 1)^2) of a grid:
@@ -2192,11 +2206,17 @@ static fsic_status boundary_basis(fsic_ctx *c, const Chan &ch, const Shape &sh, 
         Ub.release();
         return st;
     }
-    // kept: the first octant (the solutions' reflection parities give the rest)
+    // kept: the first octant (the reflection parities give the rest), and
+    // behind it that of the harmonics, dV r^l Y_lm
     DBuf<double> Uc;
-    const size_t Mo = (size_t)((ch.n[0] + 1) / 2) * ((ch.n[1] + 1) / 2) * ((ch.n[2] + 1) / 2);
-    hipError_t he = Uc.ensure((size_t)nlm * Mo);
+    const size_t Mo = octant_nodes(ch.n);
+    hipError_t he = Uc.ensure(2 * (size_t)nlm * Mo);
     if (he == hipSuccess) he = launch_octant_pack(nlm, ch.n, Ub.p, Uc.p, c->stream);
+    if (he == hipSuccess) he = hipMemsetAsync(Ub.p, 0, (size_t)nlm * ch.M * sizeof(double), c->stream);
+    if (he == hipSuccess)
+        he = launch_harm_expand(1, lmax, c->ht, c->radius, c->d_orb.p, c->d_gcount.p, c->d_hcNx.p,
+                                (int)bb.hcNx.size(), c->qident.p, Ub.p, c->stream);
+    if (he == hipSuccess) he = launch_octant_pack(nlm, ch.n, Ub.p, Uc.p + (size_t)nlm * Mo, c->stream);
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
     Ub.release();
     if (he != hipSuccess) {
@@ -2227,6 +2247,87 @@ struct BwdState {
 static fsic_status backward_enqueue(fsic_ctx *c, bool fused, BwdState &bs);
 static fsic_status backward_finish(fsic_ctx *c, bool fused, const double *grad_e, double *const *dE_da,
                                    fsic_stats *st, BwdState &bs);
+
+// Groups, blocks and fragment tiles of the octant kernels for the channels of
+// a batch (the spins of a system share a grid and follow each other); sets
+// every channel's partial-sum slots and returns their number.
+static int build_octant(std::vector<Chan> &chans, const std::vector<const double *> &basisU, int lmax,
+                        std::vector<OctGroup> &groups, std::vector<OctItem> &mom, std::vector<OctItem> &sic,
+                        std::vector<OctTile> &tiles, size_t &part, int &gtiles) {
+    const int nlm = (lmax + 1) * (lmax + 1), nchan = (int)chans.size();
+    double wm = 0.0, ws = 0.0;
+    // the Slater step's cost at a node: orbitals in fours, and about as much as
+    // four for the products of each 16-orbital tile
+    auto sic_rows = [&](const OctGroup &g) {
+        int r = 0;
+        for (int q = 0; q < g.nchan; ++q) {
+            const int N = chans[g.chan0 + q].N;
+            r += 4 * ((N + 3) / 4) + 4 * ((N + 15) / 16);
+        }
+        return (double)r;
+    };
+    gtiles = 0;
+    for (int ci = 0; ci < nchan;) {
+        const Chan &ch = chans[ci];
+        OctGroup g{};
+        g.nx = ch.n[0]; g.ny = ch.n[1]; g.nz = ch.n[2];
+        g.chan0 = ci; g.off = ch.off; g.M = ch.M;
+        g.U = basisU[ci];
+        g.H = g.U + (size_t)nlm * octant_nodes(ch.n);
+        for (; ci < nchan && chans[ci].sys == ch.sys; ++ci) {
+            g.tile0[g.nchan++] = (int)tiles.size();
+            for (int i0 = 0; i0 < chans[ci].N; i0 += 16)
+                tiles.push_back(OctTile{std::min(16, chans[ci].N - i0), g.n + i0, (int)groups.size(), 0, 0});
+            g.n += chans[ci].N;
+        }
+        g.ot = (g.n + 15) / 16;
+        const double nodes = (double)octant_nodes(ch.n);
+        wm += nodes * g.ot;
+        ws += nodes * sic_rows(g);
+        gtiles = std::max(gtiles, (int)tiles.size() - g.tile0[0]);
+        groups.push_back(g);
+    }
+    // blocks: what the device holds at once, shared by work; the orbital
+    // tiles of one node range lie next to each other on an XCD (they read the
+    // same H and U)
+    const double sm = oct_slots(0, lmax, 0), ss = oct_slots(1, lmax, gtiles);
+    part = 0;
+    int slots = 0;
+    std::vector<int> nparts(groups.size());
+    std::vector<OctItem> nat;
+    for (size_t k = 0; k < groups.size(); ++k) {
+        OctGroup &g = groups[k];
+        const double nodes = (double)octant_nodes(chans[g.chan0].n);
+        int steps = (int)((nodes + kOctMomentNodes - 1) / kOctMomentNodes);
+        const int nb = (int)std::max(1.0, std::min((double)steps, std::floor(sm * nodes / wm + 0.5)));
+        for (int b = 0; b < nb; ++b)
+            for (int q = 0; q < g.ot; ++q)
+                nat.push_back(OctItem{(int)k, q, (int)((long long)steps * b / nb),
+                                      (int)((long long)steps * (b + 1) / nb), b});
+        g.poff = part;
+        part += (size_t)nb * g.ot * 2 * nlm * 16;
+        nparts[k] = nb;
+        steps = (int)((nodes + 15) / 16);
+        const int nsb = (int)std::max(1.0, std::min((double)steps, std::floor(ss * nodes * sic_rows(g) / ws + 0.5)));
+        for (int b = 0; b < nsb; ++b)
+            sic.push_back(OctItem{(int)k, 0, (int)((long long)steps * b / nsb),
+                                  (int)((long long)steps * (b + 1) / nsb), b});
+        for (int q = 0; q < g.nchan; ++q) {
+            chans[g.chan0 + q].nblk = nsb;
+            chans[g.chan0 + q].blk_base = slots;
+            slots += nsb;
+        }
+    }
+    while (nat.size() % 8) nat.push_back(OctItem{0, 0, 0, 0, -1});
+    for (int b = 0; b < (int)nat.size(); ++b) mom.push_back(nat[xcd_item_of_block(b, (int)nat.size())]);
+    for (OctTile &t : tiles) {
+        const int k = t.ot;
+        t.ot = groups[k].ot;
+        t.nparts = nparts[k];
+        t.poff = groups[k].poff;
+    }
+    return slots;
+}
 
 // The forward pass; with dE_da (fsic_forward_backward) the backward pass's
 // device work is enqueued behind it before the host waits, and read back
@@ -2324,12 +2425,19 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     std::vector<ChanDesc> cd(nchan);
     std::vector<int> blkchan;
     int nblk_total = 0;
+    std::vector<OctGroup> octg;
+    std::vector<OctItem> octm, octs;
+    std::vector<OctTile> octt;
+    size_t octpart = 0;
+    if (use_basis) nblk_total = build_octant(chans, basisU, o.lmax, octg, octm, octs, octt, octpart, c->oct_gtiles);
     for (int ci = 0; ci < nchan; ++ci) {
         Chan &ch = chans[ci];
-        ch.nblk = (int)((ch.M + kSicTile - 1) / kSicTile);
-        ch.blk_base = nblk_total;
-        nblk_total += ch.nblk;
-        for (int t = 0; t < ch.nblk; ++t) blkchan.push_back(ci);
+        if (!use_basis) {
+            ch.nblk = (int)((ch.M + kSicTile - 1) / kSicTile);
+            ch.blk_base = nblk_total;
+            nblk_total += ch.nblk;
+            for (int t = 0; t < ch.nblk; ++t) blkchan.push_back(ci);
+        }
         ChanDesc &d = cd[ci];
         d.N = ch.N; d.first_orb = ch.first_orb; d.M = ch.M; d.off = ch.off;
         d.nx = ch.n[0]; d.ny = ch.n[1]; d.nz = ch.n[2];
@@ -2340,7 +2448,8 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     // ---- buffers ----
     hipStream_t s = c->stream;
     HIPCHK(c, c->PHI.ensure(F));
-    HIPCHK(c, c->V.ensure(F));
+    if (use_basis) HIPCHK(c, c->W.ensure(F));
+    else HIPCHK(c, c->V.ensure(F));
     fsic_status pst = prepare_batch(c, b, o.precision);
     if (pst) return pst;
     HIPCHK(c, c->small.ensure((size_t)nchan * kSmallStride));
@@ -2360,6 +2469,16 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     if ((ust = upload(c, c->d_cells, cells))) return ust;
     if ((ust = upload(c, c->d_chan, cd))) return ust;
     if ((ust = upload(c, c->d_blkchan, blkchan))) return ust;
+    if (use_basis) {
+        if ((ust = upload(c, c->d_octg, octg))) return ust;
+        if ((ust = upload(c, c->d_octm, octm))) return ust;
+        if ((ust = upload(c, c->d_octs, octs))) return ust;
+        if ((ust = upload(c, c->d_octt, octt))) return ust;
+        HIPCHK(c, c->octpart.ensure(octpart));
+        HIPCHK(c, c->octfrag.ensure(2 * octt.size() * (size_t)oct_steps(o.lmax) * 64));
+        c->n_octs = (int)octs.size();
+        c->n_octt = (int)octt.size();
+    }
     HIPCHK(c, c->partU.ensure((size_t)nblk_total * kMaxOrb));
     HIPCHK(c, c->partX.ensure((size_t)nblk_total * kMaxOrb));
     const size_t neux = 2 * (size_t)norb + nchan;
@@ -2451,27 +2570,11 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     c->w_ready = false;
     fsic_status sst;
     if (use_basis) {
-        // moments of rho_i, zero-boundary solves into W, then
-        // v_i = w_i + sum_q Q_q,i U_q
-        HIPCHK(c, c->W.ensure(F));
-        HIPCHK(c, launch_harm_contract(0, o.lmax, c->ht, c->cf, c->radius, c->d_orb.p, c->d_gcount.p, c->d_hcN.p,
-                                       (int)b.hcN.size(), c->d_hchN.p, (int)b.hchN.size(), b.max_group, c->PHI.p,
-                                       1, c->partH.p, c->Qlm.p, s));
+        // both sets of boundary coefficients from rho_i, then the
+        // zero-boundary solves into W (the Slater step forms v_i from them)
+        HIPCHK(c, launch_oct_moments(o.lmax, c->d_octm.p, (int)octm.size(), c->d_octg.p, c->d_octt.p, c->n_octt,
+                                     c->PHI.p, c->octpart.p, c->octfrag.p, s));
         sst = solve_batch(c, b, c->PHI.p, 1, 4.0 * M_PI, false, c->W.p, o.precision, o.tol, o.max_iter, rep);
-        // one launch per run of consecutive channels on one grid (a system's
-        // spins: their orbitals are contiguous), so the basis is read once
-        for (int ci = 0; !sst && ci < nchan;) {
-            const Chan &ch = chans[ci];
-            int cj = ci + 1, n = ch.N;
-            while (cj < nchan && basisU[cj] == basisU[ci] && chans[cj].off == ch.off + (long long)n * ch.M &&
-                   chans[cj].first_orb == ch.first_orb + n) {
-                n += chans[cj].N;
-                ++cj;
-            }
-            HIPCHK(c, launch_bc_combine(n, ch.n, o.lmax, c->Qlm.p, ch.first_orb, basisU[ci], c->W.p + ch.off,
-                                        c->V.p + ch.off, s));
-            ci = cj;
-        }
     } else {
         sst = solve_batch(c, b, c->PHI.p, 1, 4.0 * M_PI, true, c->V.p, o.precision, o.tol, o.max_iter, rep);
     }
@@ -2480,8 +2583,13 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     const double t3 = now_ms();
 
     // ---- (d) XC, (e) Slater average and energies ----
-    HIPCHK(c, launch_sic_average(nchan, c->d_chan.p, nblk_total, c->d_blkchan.p, c->PHI.p, c->V.p,
-                                 o.rho_floor, c->partU.p, c->partX.p, s));
+    if (use_basis)
+        HIPCHK(c, launch_sic_octant(o.lmax, c->d_octs.p, c->n_octs, c->d_octg.p, c->d_chan.p, c->n_octt, c->oct_gtiles,
+                                    c->octfrag.p,
+                                    c->PHI.p, c->W.p, o.rho_floor, 1, c->partU.p, c->partX.p, s));
+    else
+        HIPCHK(c, launch_sic_average(nchan, c->d_chan.p, nblk_total, c->d_blkchan.p, c->PHI.p, c->V.p,
+                                     o.rho_floor, c->partU.p, c->partX.p, s));
     double *const dU = c->eux.p, *const dX = dU + norb, *const dE = dX + norb;
     HIPCHK(c, launch_sic_energy(nchan, c->d_chan.p, c->partU.p, c->partX.p, dU, dX, dE, s));
     HIPCHK(c, hipMemcpyAsync(c->h_eux, c->eux.p, (2 * (size_t)norb + nchan) * sizeof(double),
@@ -2490,6 +2598,7 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     c->chans = std::move(chans);
     c->batch = std::move(b);
     c->nsys = nsys;
+    c->tape_basis = use_basis;
     const std::vector<Chan> &chs = c->chans;
     const Batch &bt = c->batch;
     // fused backward pass: enqueued now, behind the forward pass's work
@@ -2498,7 +2607,7 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     if (fused) {
         c->w_ready = true;
         fsic_status bs = backward_enqueue(c, true, bws);
-        c->w_ready = false;  // the enqueued work turns W into Gam
+        c->w_ready = false;  // one backward pass per forward pass takes it
         if (bs) return bs;
     }
     HIPCHK(c, hipStreamSynchronize(s));
@@ -2937,8 +3046,9 @@ static fsic_status backward_enqueue(fsic_ctx *c, bool fused, BwdState &bs) {
     const bool eq9 = (o.flags & FSIC_EQ9_FORCES) != 0;
     bs.eq9 = eq9;
     const double *Wt = c->V.p;
-    // the forward pass left the adjoint fields in W (zero-boundary solves)
-    const bool reuse_w = !eq9 && c->w_ready;
+    // the forward pass left Gam in W (boundary basis, first backward pass)
+    const bool given = !eq9 && c->tape_basis;
+    const bool reuse_w = given && c->w_ready;
     bs.reuse_w = reuse_w;
     if (!eq9) {
         HIPCHK(c, c->W.ensure((size_t)b.fields));
@@ -2947,7 +3057,13 @@ static fsic_status backward_enqueue(fsic_ctx *c, bool fused, BwdState &bs) {
             fsic_status sst = solve_batch(c, b, c->PHI.p, 1, 4.0 * M_PI, false, c->W.p, o.precision, o.tol,
                                           o.max_iter, rep);
             if (sst) return sst;
+            if (given)
+                HIPCHK(c, launch_sic_octant(o.lmax, c->d_octs.p, c->n_octs, c->d_octg.p, c->d_chan.p, c->n_octt,
+                                            c->oct_gtiles, c->octfrag.p, c->PHI.p, c->W.p, o.rho_floor, 0, c->partU.p, c->partX.p,
+                                            s));
         }
+    }
+    if (!eq9 && !given) {
         // boundary part of A^T rho: zt = E_g^T C^T w' / (4 pi), then W += P^T zt
         HarmTables hta = c->ht;
         for (int q = 0; q < kMaxLM; ++q) hta.gfac[q] /= 4.0 * M_PI;
@@ -2994,10 +3110,15 @@ static fsic_status backward_enqueue(fsic_ctx *c, bool fused, BwdState &bs) {
         for (int q = 0; q < lb.n; ++q) {
             const Chan &ch = c->chans[c0 + q];
             const double dV = ch.h * ch.h * ch.h;
-            // Gam overwrites W (the adjoint field is not needed after it)
-            HIPCHK(c, launch_adjoint_contract(ch.N, ch.M, dV, c->PHI.p + ch.off, c->V.p + ch.off,
-                                              Wt + ch.off, ch.psi, o.rho_floor, c->partG.p, c->partG.cap,
-                                              c->bmat.p + (size_t)q * bstride, c->W.p + ch.off, s));
+            if (given) {
+                HIPCHK(c, launch_gamma_contract(ch.N, ch.M, c->W.p + ch.off, ch.psi, c->partG.p, c->partG.cap,
+                                                c->bmat.p + (size_t)q * bstride, s));
+            } else {
+                // Gam overwrites W (the adjoint field is not needed after it)
+                HIPCHK(c, launch_adjoint_contract(ch.N, ch.M, dV, c->PHI.p + ch.off, c->V.p + ch.off,
+                                                  Wt + ch.off, ch.psi, o.rho_floor, c->partG.p, c->partG.cap,
+                                                  c->bmat.p + (size_t)q * bstride, c->W.p + ch.off, s));
+            }
             lb.N[q] = ch.N;
             lb.so[q] = (long long)ch.so;
             lb.go[q] = (long long)goff[c0 + q];
