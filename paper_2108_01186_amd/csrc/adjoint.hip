@@ -17,114 +17,9 @@
 
 #include "kernels.h"
 #include "lsda.h"
-#include "tsgemm.h"
 
 namespace fsic {
 
-
-// Small N (at most two 16-row tiles): B[i][a] = sum_m Gam_i(m) psi_a(m),
-// Gam given (in place of PHI) or formed on the fly; block b sums the node range [b chunk, (b+1) chunk)
-// (chunk a multiple of 64).  Every wave forms all the tiles over its own
-// 16-node groups; lane (row r = l % 16, q = l / 16) holds nodes g + 4q ..
-// g + 4q + 3 of row r (32 contiguous bytes: the four lanes of a row read one
-// 128-byte line), and k-step j of a group contracts node g + 4q + j (any
-// assignment of nodes to k-steps splits the sum, as long as both operands
-// use the same one).  The four waves' tiles are added in LDS at the end.
-template <bool GIVEN>
-__global__ __launch_bounds__(256) void k_adj_contract_small(int N, long long M, long long chunk, double dV,
-                                                            const double *PHI, const double *V,
-                                                            const double *W, const double *psi,
-                                                            double floor, int vec, double *partB) {
-    const int Nt = (N + 15) >> 4;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int row = lane & 15, kk = lane >> 4;
-    dbl4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) acc[a][t] = dbl4{0.0, 0.0, 0.0, 0.0};
-    const long long m0 = (long long)blockIdx.x * chunk;
-    const long long m1 = min(M, m0 + chunk);
-    // four consecutive values of row i from node mb (zero past m1)
-    auto load4 = [&](const double *X, int i, long long mb, double (&v)[4]) {
-        const double *src = X + (long long)i * M + mb;
-        if (vec && mb + 4 <= m1) {
-            const double2 lo = *reinterpret_cast<const double2 *>(src);
-            const double2 hi = *reinterpret_cast<const double2 *>(src + 2);
-            v[0] = lo.x; v[1] = lo.y; v[2] = hi.x; v[3] = hi.y;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = mb + j < m1 ? src[j] : 0.0;
-        }
-    };
-    for (long long g = m0 + 16 * w; g < m1; g += 64) {
-        const long long mb = g + 4 * kk;
-        double gam[2][4], f[2][4];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            const int i = 16 * a + row;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) gam[a][j] = 0.0;
-            if (a < Nt && i < N && mb < m1) {
-                double ph[4], vv[4], ww[4];
-                load4(PHI, i, mb, ph);
-                if constexpr (GIVEN) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) gam[a][j] = ph[j];
-                } else {
-                    load4(V, i, mb, vv);
-                    load4(W, i, mb, ww);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const double om = -(0.5 * (vv[j] + ww[j]) + vxc_pol(ph[j] * ph[j], floor));
-                        gam[a][j] = 2.0 * dV * ph[j] * om;  // zero past m1 (ph = 0 there)
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int r = 16 * t + row;
-            if (t < Nt && r < N && mb < m1) load4(psi, r, mb, f[t]);
-            else
-#pragma unroll
-                for (int j = 0; j < 4; ++j) f[t][j] = 0.0;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-                if (a < Nt)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        if (t < Nt) acc[a][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(gam[a][j], f[t][j], acc[a][t], 0, 0, 0);
-    }
-    const int NP = Nt * 16;
-    double *out = partB + (size_t)blockIdx.x * NP * NP;
-    __shared__ double sacc[4][4][4][64];  // wave, tile (a, t), item, lane
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-            if (a < Nt && t < Nt)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) sacc[w][2 * a + t][j][lane] = acc[a][t][j];
-    __syncthreads();
-    if (w != 0) return;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-            if (a < Nt && t < Nt)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    // D layout of the f64 16x16x4 MFMA: lane l, item j -> row l/16 + 4 j, col l % 16
-                    const int r = 16 * a + kk + 4 * j;
-                    const int c = 16 * t + row;
-                    out[(size_t)r * NP + c] = (sacc[0][2 * a + t][j][lane] + sacc[1][2 * a + t][j][lane]) +
-                                              (sacc[2][2 * a + t][j][lane] + sacc[3][2 * a + t][j][lane]);
-                }
-}
 
 // Gam_i(m) = 2 dV phi_i omega_i, omega_i = -((v_i + w_i) / 2 + vxc(phi_i^2)),
 // over the channel's N x M values (Gam may be W: each value is read before
@@ -137,19 +32,6 @@ __global__ __launch_bounds__(256) void k_gamma(long long count, double dV, const
         const double om = -(0.5 * (V[i] + W[i]) + vxc_pol(ph * ph, floor));
         Gam[i] = 2.0 * dV * ph * om;
     }
-}
-
-// Bm[i][j] = sum of the blocks' partial tiles; one 256-thread block per element
-__global__ __launch_bounds__(256) void k_adj_contract_final(int N, int nblk, const double *partB,
-                                                            double *Bm) {
-    __shared__ double sred[4];
-    const int NP = ((N + 15) >> 4) * 16;
-    const int e = blockIdx.x;
-    const int i = e / N, j = e % N;
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += 256) s += partB[(size_t)b * NP * NP + (size_t)i * NP + j];
-    s = block_sum256(s, sred);
-    if (threadIdx.x == 0) Bm[e] = s;
 }
 
 // C = op(A) op(B) for N x N row-major matrices (flat pointers)
@@ -264,53 +146,11 @@ hipError_t launch_lowdin_backward_batch(const LowdinBwdBatch &lb, const double *
     return hipGetLastError();
 }
 
-hipError_t launch_gamma_contract(int N, long long M, const double *Gam, const double *psi, double *partB, size_t cap,
-                                 double *Bm, hipStream_t s) {
-    if (N < 1 || N > kMaxOrb) return hipErrorInvalidValue;
-    const int nblk = grid_blocks(N, M, cap);
-    long long chunk = (M + nblk - 1) / nblk;
-    if (N <= 32) {
-        chunk = (chunk + 63) & ~63LL;
-        const int vec = (M & 1) == 0 && ((reinterpret_cast<uintptr_t>(Gam) | reinterpret_cast<uintptr_t>(psi)) & 15) == 0;
-        hipLaunchKernelGGL(k_adj_contract_small<true>, dim3(nblk), dim3(256), 0, s, N, M, chunk, 0.0, Gam, nullptr,
-                           nullptr, psi, 0.0, vec, partB);
-    } else {
-        chunk = (chunk + kTK - 1) / kTK * kTK;
-        const size_t lds = tsg_lds_bytes(N, 2);
-        if (lds > 65536) hipFuncSetAttribute((const void *)k_tsg_nt<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(k_tsg_nt<false>, dim3(nblk), dim3(256), lds, s, N, M, chunk, Gam, psi, partB);
-    }
-    hipLaunchKernelGGL(k_adj_contract_final, dim3(N * N), dim3(256), 0, s, N, nblk, partB, Bm);
-    return hipGetLastError();
-}
-
-hipError_t launch_adjoint_contract(int N, long long M, double dV, const double *PHI, const double *V,
-                                    const double *W, const double *psi, double floor, double *partB,
-                                    size_t cap, double *Bm, double *Gam, hipStream_t s) {
-    if (N < 1 || N > kMaxOrb) return hipErrorInvalidValue;
-    const int nblk = grid_blocks(N, M, cap);
-    long long chunk = (M + nblk - 1) / nblk;
-    if (N <= 32) {  // Gam built on the fly
-        chunk = (chunk + 63) & ~63LL;
-        // 16-byte loads where every row start is 16-byte aligned
-        const int vec = ((M & 1) == 0 && ((reinterpret_cast<uintptr_t>(PHI) | reinterpret_cast<uintptr_t>(V) |
-                                           reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(psi)) &
-                                          15) == 0)
-                            ? 1
-                            : 0;
-        hipLaunchKernelGGL(k_adj_contract_small<false>, dim3(nblk), dim3(256), 0, s, N, M, chunk, dV, PHI, V, W, psi,
-                           floor, vec, partB);
-        hipLaunchKernelGGL(k_adj_contract_final, dim3(N * N), dim3(256), 0, s, N, nblk, partB, Bm);
-        return hipGetLastError();
-    }
-    const long long count = (long long)N * M;
-    const long long gblk = std::max(1LL, std::min((count + 255) / 256, 4096LL));
+hipError_t launch_gamma(long long count, double dV, const double *PHI, const double *V, const double *W, double floor,
+                        double *Gam, hipStream_t s) {
+    if (count < 1) return hipErrorInvalidValue;
+    const long long gblk = std::min((count + 255) / 256, 4096LL);
     hipLaunchKernelGGL(k_gamma, dim3((unsigned)gblk), dim3(256), 0, s, count, dV, PHI, V, W, floor, Gam);
-    chunk = (chunk + kTK - 1) / kTK * kTK;
-    const size_t lds = tsg_lds_bytes(N, 2);
-    if (lds > 65536) hipFuncSetAttribute((const void *)k_tsg_nt<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k_tsg_nt<false>, dim3(nblk), dim3(256), lds, s, N, M, chunk, Gam, psi, partB);
-    hipLaunchKernelGGL(k_adj_contract_final, dim3(N * N), dim3(256), 0, s, N, nblk, partB, Bm);
     return hipGetLastError();
 }
 

@@ -13,7 +13,6 @@
 #include <cstdint>
 
 #include "kernels.h"
-#include "tsgemm.h"
 
 namespace fsic {
 
@@ -170,131 +169,6 @@ hipError_t launch_interp(int K, int N, int nx, int ny, int nz, double h, const d
     else
         hipLaunchKernelGGL(k_interp<false>, dim3(K), dim3(128), 0, s, N, nx, ny, nz, h, psi, cells,
                            floor, u, du, rhoa, T, status);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Gram matrix G = dV psi psi^T on the matrix cores: k_tsg_nt<true>
-// (tsgemm.h) for more than 32 orbitals, below for at most 32
-// ---------------------------------------------------------------------------
-
-// Small N (at most two 16-row tiles): the tile pairs t1 <= t2 of
-// psi psi^T over the node range [b chunk, (b+1) chunk) of block b (chunk a
-// multiple of 64).  Every wave forms all pairs over its own 16-node groups;
-// lane (row r = l % 16, q = l / 16) holds nodes g + 4q .. g + 4q + 3 of row r
-// (32 contiguous bytes: the four lanes of a row read one 128-byte line) and
-// k-step j contracts node g + 4q + j; the four waves' tiles are added in
-// LDS.  partG[b] holds the block's sums.
-__global__ __launch_bounds__(256) void k_gram_small(int N, long long M, long long chunk, const double *psi,
-                                                    int vec, double *partG) {
-    const int Nt = (N + 15) >> 4;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int row = lane & 15, kk = lane >> 4;
-    const int np = Nt == 1 ? 1 : 3;  // pairs (0,0) [, (0,1), (1,1)]
-    dbl4 acc[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) acc[q] = dbl4{0.0, 0.0, 0.0, 0.0};
-    const long long m0 = (long long)blockIdx.x * chunk;
-    const long long m1 = min(M, m0 + chunk);
-    for (long long g = m0 + 16 * w; g < m1; g += 64) {
-        const long long mb = g + 4 * kk;
-        double f[2][4];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int r = 16 * t + row;
-            const double *src = psi + (long long)r * M + mb;
-            if (t < Nt && r < N && mb < m1) {
-                if (vec && mb + 4 <= m1) {
-                    const double2 lo = *reinterpret_cast<const double2 *>(src);
-                    const double2 hi = *reinterpret_cast<const double2 *>(src + 2);
-                    f[t][0] = lo.x; f[t][1] = lo.y; f[t][2] = hi.x; f[t][3] = hi.y;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) f[t][j] = mb + j < m1 ? src[j] : 0.0;
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) f[t][j] = 0.0;
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            acc[0] = mfma16x16x4(f[0][j], f[0][j], acc[0]);
-            if (np == 3) {
-                acc[1] = mfma16x16x4(f[0][j], f[1][j], acc[1]);
-                acc[2] = mfma16x16x4(f[1][j], f[1][j], acc[2]);
-            }
-        }
-    }
-    const int NP = Nt * 16;
-    double *out = partG + (size_t)blockIdx.x * NP * NP;
-    __shared__ double sacc[4][3][4][64];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-        if (q < np)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) sacc[w][q][j][lane] = acc[q][j];
-    __syncthreads();
-    if (w != 0) return;
-    const int pt1[3] = {0, 0, 1}, pt2[3] = {0, 1, 1};
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-        if (q < np)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                // D lane l, item j: row l / 16 + 4 j, column l % 16
-                const int r = 16 * pt1[q] + kk + 4 * j;
-                const int c = 16 * pt2[q] + row;
-                out[(size_t)r * NP + c] = (sacc[0][q][j][lane] + sacc[1][q][j][lane]) +
-                                          (sacc[2][q][j][lane] + sacc[3][q][j][lane]);
-            }
-}
-
-
-// G[i][j] = dV * sum over the blocks' partial tiles (the upper block triangle
-// holds the tile pairs); one 256-thread block per element, fixed order
-__global__ __launch_bounds__(256) void k_gram_final(int N, int nblk, double dV, const double *partG,
-                                                    double *G) {
-    __shared__ double sred[4];
-    const int NP = ((N + 15) >> 4) * 16;
-    const int e = blockIdx.x;
-    int i = e / N, j = e % N;
-    if ((i >> 4) > (j >> 4)) { const int t = i; i = j; j = t; }
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += 256) s += partG[(size_t)b * NP * NP + (size_t)i * NP + j];
-    s = block_sum256(s, sred);
-    if (threadIdx.x == 0) G[e] = dV * s;
-}
-
-// partial-sum blocks for a node range split within the partial buffer (cap
-// doubles): for the staged kernels four per compute unit (at most 1024) of
-// at least four 32-node tiles; for the small-N ones up to 4096 of 64 nodes
-int grid_blocks(int N, long long M, size_t cap) {
-    const size_t NP = (size_t)((N + 15) >> 4) * 16;
-    const bool small = NP <= 32;
-    long long nb = (long long)std::min<size_t>(small ? 4096 : 1024, cap / (NP * NP));
-    nb = std::min(nb, small ? (M + 63) / 64 : (M + 4 * kTK - 1) / (4 * kTK));
-    return (int)std::max(1LL, nb);
-}
-
-hipError_t launch_gram(int N, long long M, double dV, const double *psi, double *partG, size_t cap,
-                       double *G, hipStream_t s) {
-    if (N < 1 || N > kMaxOrb) return hipErrorInvalidValue;
-    const int nblk = grid_blocks(N, M, cap);
-    long long chunk = (M + nblk - 1) / nblk;
-    if (N <= 32) {
-        chunk = (chunk + 63) & ~63LL;
-        // 16-byte loads where every row start is 16-byte aligned
-        const int vec = ((M & 1) == 0 && (reinterpret_cast<uintptr_t>(psi) & 15) == 0) ? 1 : 0;
-        hipLaunchKernelGGL(k_gram_small, dim3(nblk), dim3(256), 0, s, N, M, chunk, psi, vec, partG);
-    } else {
-        chunk = (chunk + kTK - 1) / kTK * kTK;
-        const size_t lds = tsg_lds_bytes(N, 1);
-        if (lds > 65536)
-            hipFuncSetAttribute((const void *)k_tsg_nt<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL(k_tsg_nt<true>, dim3(nblk), dim3(256), lds, s, N, M, chunk, psi, psi, partG);
-    }
-    hipLaunchKernelGGL(k_gram_final, dim3(N * N), dim3(256), 0, s, N, nblk, dV, partG, G);
     return hipGetLastError();
 }
 
@@ -500,84 +374,10 @@ hipError_t launch_lowdin_batch(const LowdinBatch &lb, double *small, const Lowdi
 }
 
 // ---------------------------------------------------------------------------
-// out = A psi  (N x N times N x M) on the matrix cores: k_tsg_nn (tsgemm.h)
-// for more than 32 orbitals; for at most 32 each wave takes 16-node strips
-// and all output rows, A read through the cache
+// out = A psi in fp32 (FSIC_FP32_ORBITALS; the FP64 products: products.hip)
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(256) void k_orb_gemm(int N, long long M, const double *A,
-                                                  const double *psi, double *out) {
-    const int Nt = (N + 15) >> 4;
-    const int lane = threadIdx.x & 63;
-    const int row = lane & 15, kk = lane >> 4;
-    const long long nstrip = (M + 15) >> 4;
-    const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const long long nwave = ((long long)gridDim.x * blockDim.x) >> 6;
-    // N <= 16: the 16-row A fragments stay in registers and each pass takes
-    // two strips, whose psi loads are all issued before the products
-    if (Nt == 1) {
-        double af[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int a = 4 * q + kk;
-            af[q] = (row < N && a < N) ? A[row * N + a] : 0.0;
-        }
-        for (long long st = wave; st < nstrip; st += 2 * nwave) {
-            const long long ms[2] = {st * 16 + row, (st + nwave) * 16 + row};
-            double b[2][4];
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int a = 4 * q + kk;
-                    b[u][q] = (a < N && ms[u] < M) ? psi[(long long)a * M + ms[u]] : 0.0;
-                }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                dbl4 acc = dbl4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc = mfma16x16x4(af[q], b[u][q], acc);
-                if (ms[u] < M)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int i = kk + 4 * j;
-                        if (i < N) out[(long long)i * M + ms[u]] = acc[j];
-                    }
-            }
-        }
-        return;
-    }
-    for (long long st = wave; st < nstrip; st += nwave) {
-        const long long m = st * 16 + row;
-        dbl4 acc[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) acc[t] = dbl4{0.0, 0.0, 0.0, 0.0};
-        for (int a0 = 0; a0 < N; a0 += 4) {
-            const int a = a0 + kk;
-            const double b = (a < N && m < M) ? psi[(long long)a * M + m] : 0.0;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                if (t < Nt) {
-                    const int i = 16 * t + row;
-                    const double av = (i < N && a < N) ? A[i * N + a] : 0.0;
-                    acc[t] = mfma16x16x4(av, b, acc[t]);
-                }
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            if (t < Nt && m < M) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int i = 16 * t + kk + 4 * j;
-                    if (i < N) out[(long long)i * M + m] = acc[t][j];
-                }
-            }
-        }
-    }
-}
-
-// fp32 variant: A and psi rounded to fp32, products accumulated in fp32 on
+// A and psi rounded to fp32, products accumulated in fp32 on
 // v_mfma_f32_16x16x4f32 (D lane l, item j: row 4 (l/16) + j), out in fp64
 typedef float flt4 __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void k_orb_gemm32(int N, long long M, const double *A,
@@ -625,25 +425,6 @@ hipError_t launch_orb_gemm32(int N, long long M, const double *A, const double *
     long long nblk = (nstrip + 3) / 4;
     if (nblk > 8192) nblk = 8192;
     hipLaunchKernelGGL(k_orb_gemm32, dim3((unsigned)nblk), dim3(256), 0, s, N, M, A, psi, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_orb_gemm(int N, long long M, const double *A, const double *psi, double *out,
-                           hipStream_t s) {
-    if (N < 1 || N > kMaxOrb) return hipErrorInvalidValue;
-    if (N <= 32) {
-        const long long nstrip = (M + 15) / 16;
-        const long long nblk = std::max(1LL, std::min((nstrip + 3) / 4, 8192LL));
-        hipLaunchKernelGGL(k_orb_gemm, dim3((unsigned)nblk), dim3(256), 0, s, N, M, A, psi, out);
-        return hipGetLastError();
-    }
-    const long long ntile = (M + kTK - 1) / kTK;
-    const long long nblk = std::max(1LL, std::min(ntile, 512LL));  // two per compute unit
-    const size_t lds = (size_t)16 * ((N + 15) / 16) * kTKS * sizeof(double);  // at most 33 KiB
-    if (N <= 64)
-        hipLaunchKernelGGL((k_tsg_nn<1, 16>), dim3((unsigned)nblk), dim3(256), lds, s, N, M, A, psi, out);
-    else
-        hipLaunchKernelGGL((k_tsg_nn<2, 32>), dim3((unsigned)nblk), dim3(256), lds, s, N, M, A, psi, out);
     return hipGetLastError();
 }
 

@@ -398,12 +398,32 @@ hipError_t launch_interp(int K, int N, int nx, int ny, int nz, double h, const d
                          const FodCell *cells, double floor, double *u, double *du,
                          double *rhoa, double *T, int *status, bool fd_gradient, hipStream_t s);
 
-// G = dV psi psi^T (MFMA FP64), partial sums then reduction; nonortho = max|G - I|
-// blocks of a node-range split whose N x N partial tiles fit in cap doubles
-int grid_blocks(int N, long long M, size_t cap);
+// ----------------------------------------------------------------------------
+// products.hip: tall-skinny products over the grid, all channels of a batch
+// ----------------------------------------------------------------------------
 
-hipError_t launch_gram(int N, long long M, double dV, const double *psi, double *partG, size_t cap,
-                       double *G, hipStream_t s);
+constexpr int kProdBatch = 32;  // channels per launch
+struct ProdChan {
+    int N;             // orbitals, <= 128
+    long long M;       // nodes
+    const double *X;   // N x M
+    const double *Y;   // N x M (contraction)
+    const double *A;   // N x N (transform)
+    double *out;       // N x N (Gram, contraction) or N x M (transform)
+    double scale;      // of the Gram matrix and the contraction
+    int nblk, b0;      // set by the launchers: blocks and first block
+    size_t poff;       // and partial sums
+};
+struct ProdBatch {
+    int n;
+    ProdChan c[kProdBatch];
+};
+// out = scale X X^T; part: cap doubles of partial tiles
+hipError_t launch_gram(const ProdChan *chans, int n, double *part, size_t cap, hipStream_t s);
+// out = scale X Y^T
+hipError_t launch_contract(const ProdChan *chans, int n, double *part, size_t cap, hipStream_t s);
+// out = A X
+hipError_t launch_transform(const ProdChan *chans, int n, hipStream_t s);
 
 // Loewdin step on one block: S = T G T^T; S = U diag(lam) U^T (parallel
 // Jacobi); Z = S^{-1/2}; Q = Z T.  work: device scratch of >= 2 N^2 doubles.
@@ -427,10 +447,8 @@ hipError_t launch_lowdin_batch(const LowdinBatch &lb, double *small, const Lowdi
                                double *work, long long wstride, double eig_floor, int *status,
                                hipStream_t s);
 
-// out[i][m] = sum_a A[i][a] psi[a][m]  (MFMA FP64), N <= 128
-hipError_t launch_orb_gemm(int N, long long M, const double *A, const double *psi, double *out,
-                           hipStream_t s);
-// the same with fp32 operands and fp32 accumulation on the matrix cores
+// out[i][m] = sum_a A[i][a] psi[a][m] with fp32 operands and fp32 accumulation
+// on the matrix cores
 hipError_t launch_orb_gemm32(int N, long long M, const double *A, const double *psi, double *out,
                              hipStream_t s);
 
@@ -485,17 +503,10 @@ hipError_t launch_sic_octant(int lmax, const OctItem *items, int nitems, const O
 // Uc = the first octant (ceil(n/2) nodes per axis, x fastest) of nlm full-grid fields
 hipError_t launch_octant_pack(int nlm, const int *n, const double *U, double *Uc, hipStream_t s);
 
-// B[i][a] = sum_m Gam_i(m) psi_a(m) for a given Gam (N x M)
-hipError_t launch_gamma_contract(int N, long long M, const double *Gam, const double *psi, double *partB, size_t cap,
-                                 double *Bm, hipStream_t s);
-
-// B[i][a] = sum_m Gam_i(m) psi_a(m) with Gam_i = 2 dV phi_i omega_i,
-// omega_i = -((v_i + w_i) / 2 + vxc(phi_i^2)), contracted on the matrix cores
-// (FP64); for more than 32 orbitals Gam is first written to Gam (N x M; may
-// be W) by an elementwise pass, for at most 32 it is built on the fly
-hipError_t launch_adjoint_contract(int N, long long M, double dV, const double *PHI, const double *V,
-                                    const double *W, const double *psi, double floor, double *partB,
-                                    size_t cap, double *Bm, double *Gam, hipStream_t s);
+// Gam_i(m) = 2 dV phi_i omega_i, omega_i = -((v_i + w_i) / 2 + vxc(phi_i^2)),
+// for count values (Gam may be W)
+hipError_t launch_gamma(long long count, double dV, const double *PHI, const double *V, const double *W, double floor,
+                        double *Gam, hipStream_t s);
 
 // reverse mode through Q = S^{-1/2} T, S = T G T^T, T = u/|u|, u = psi(a):
 // dEda[i][d] = gscale * sum_a Gam_u[i][a] dpsi_a(a_i)/da_d

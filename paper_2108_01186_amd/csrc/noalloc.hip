@@ -93,11 +93,19 @@ hipError_t noalloc_flo(int N, const int n[3], double h, const double *psi, const
     if (e == hipSuccess)
         e = launch_interp(N, N, n[0], n[1], n[2], h, psi, dcells, rho_floor, small + oU, small + oDU,
                           small + oRHOA, small + oT, status, false, s);
-    if (e == hipSuccess) e = launch_gram(N, M, dV, psi, partG, kNaPartG, small + oG, s);
+    ProdChan pc{};
+    pc.N = N;
+    pc.M = M;
+    pc.X = psi;
+    pc.out = small + oG;
+    pc.scale = dV;
+    if (e == hipSuccess) e = launch_gram(&pc, 1, partG, kNaPartG, s);
     if (e == hipSuccess)
         e = launch_lowdin(N, small + oT, small + oG, small + oS, small + oLAM, small + oEV, small + oZ,
                           small + oQ, work, 0.0, status, small + oINFO, s);
-    if (e == hipSuccess && phi) e = launch_orb_gemm(N, M, small + oQ, psi, phi, s);
+    pc.A = small + oQ;
+    pc.out = phi;
+    if (e == hipSuccess && phi) e = launch_transform(&pc, 1, s);
     const size_t NN = (size_t)N * N * sizeof(double);
     if (e == hipSuccess && T) e = hipMemcpyAsync(T, small + oT, NN, hipMemcpyDeviceToDevice, s);
     if (e == hipSuccess && G) e = hipMemcpyAsync(G, small + oG, NN, hipMemcpyDeviceToDevice, s);

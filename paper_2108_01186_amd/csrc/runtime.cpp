@@ -2495,17 +2495,23 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
 
     // ---- (a) Fermi orbitals, (b) Loewdin: per channel ----
     int cell_base = 0;
+    std::vector<ProdChan> prod(nchan);
     for (int ci = 0; ci < nchan; ++ci) {
         const Chan &ch = chans[ci];
         double *sm = c->small.p + ch.so;
-        const double dV = ch.h * ch.h * ch.h;
         HIPCHK(c, launch_interp(ch.N, ch.N, ch.n[0], ch.n[1], ch.n[2], ch.h, ch.psi, c->d_cells.p + cell_base,
                                 o.rho_floor, sm + small_off(sU_), sm + small_off(sDU),
                                 sm + small_off(sRHOA), sm + small_off(sT), c->status.p,
                                 (o.flags & FSIC_PAPER_GRADIENT) != 0, s));
-        HIPCHK(c, launch_gram(ch.N, ch.M, dV, ch.psi, c->partG.p, c->partG.cap, sm + small_off(sG), s));
+        ProdChan &pc = prod[ci];
+        pc.N = ch.N;
+        pc.M = ch.M;
+        pc.X = ch.psi;
+        pc.out = sm + small_off(sG);
+        pc.scale = ch.h * ch.h * ch.h;
         cell_base += ch.N;
     }
+    HIPCHK(c, launch_gram(prod.data(), nchan, c->partG.p, c->partG.cap, s));
     // Loewdin steps of all channels, kLowdinBatch per launch (one workgroup each)
     const LowdinOffsets loff{(long long)small_off(sT), (long long)small_off(sG), (long long)small_off(sS),
                              (long long)small_off(sLAM), (long long)small_off(sEV), (long long)small_off(sZ),
@@ -2557,11 +2563,12 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     // phi = Q psi on the matrix cores
     for (int ci = 0; ci < nchan; ++ci) {
         const Chan &ch = chans[ci];
+        prod[ci].A = c->small.p + ch.so + small_off(sQ);
+        prod[ci].out = c->PHI.p + ch.off;
         if (o.flags & FSIC_FP32_ORBITALS)
-            HIPCHK(c, launch_orb_gemm32(ch.N, ch.M, c->small.p + ch.so + small_off(sQ), ch.psi, c->PHI.p + ch.off, s));
-        else
-            HIPCHK(c, launch_orb_gemm(ch.N, ch.M, c->small.p + ch.so + small_off(sQ), ch.psi, c->PHI.p + ch.off, s));
+            HIPCHK(c, launch_orb_gemm32(ch.N, ch.M, prod[ci].A, ch.psi, prod[ci].out, s));
     }
+    if (!(o.flags & FSIC_FP32_ORBITALS)) HIPCHK(c, launch_transform(prod.data(), nchan, s));
     const double t2 = now_ms();
 
     // ---- (c) Poisson solves for all orbitals at once ----
@@ -2998,11 +3005,19 @@ fsic_status fsic_op_flo(const fsic_grid *grid, int32_t N, const double *psi, con
     if (!e) e = launch_interp(N, N, grid->n[0], grid->n[1], grid->n[2], grid->h, psi, dc.p, rho_floor,
                               b + small_off(sU_), b + small_off(sDU), b + small_off(sRHOA),
                               b + small_off(sT), status.p, false, s);
-    if (!e) e = launch_gram(N, M, dV, psi, partG.p, partG.cap, b + small_off(sG), s);
+    ProdChan pc{};
+    pc.N = N;
+    pc.M = M;
+    pc.X = psi;
+    pc.out = b + small_off(sG);
+    pc.scale = dV;
+    if (!e) e = launch_gram(&pc, 1, partG.p, partG.cap, s);
     if (!e) e = launch_lowdin(N, b + small_off(sT), b + small_off(sG), b + small_off(sS),
                               b + small_off(sLAM), b + small_off(sEV), b + small_off(sZ),
                               b + small_off(sQ), work.p, 0.0, status.p, b + small_off(sINFO), s);
-    if (!e && phi) e = launch_orb_gemm(N, M, b + small_off(sQ), psi, phi, s);
+    pc.A = b + small_off(sQ);
+    pc.out = phi;
+    if (!e && phi) e = launch_transform(&pc, 1, s);
     const size_t NN = (size_t)N * N * sizeof(double);
     if (!e && T) e = hipMemcpyAsync(T, b + small_off(sT), NN, hipMemcpyDeviceToDevice, s);
     if (!e && G) e = hipMemcpyAsync(G, b + small_off(sG), NN, hipMemcpyDeviceToDevice, s);
@@ -3107,22 +3122,24 @@ static fsic_status backward_enqueue(fsic_ctx *c, bool fused, BwdState &bs) {
     for (int c0 = 0; c0 < nch; c0 += kLowdinBatch) {
         LowdinBwdBatch lb{};
         lb.n = std::min(kLowdinBatch, nch - c0);
+        ProdChan pc[kLowdinBatch] = {};
         for (int q = 0; q < lb.n; ++q) {
             const Chan &ch = c->chans[c0 + q];
-            const double dV = ch.h * ch.h * ch.h;
-            if (given) {
-                HIPCHK(c, launch_gamma_contract(ch.N, ch.M, c->W.p + ch.off, ch.psi, c->partG.p, c->partG.cap,
-                                                c->bmat.p + (size_t)q * bstride, s));
-            } else {
-                // Gam overwrites W (the adjoint field is not needed after it)
-                HIPCHK(c, launch_adjoint_contract(ch.N, ch.M, dV, c->PHI.p + ch.off, c->V.p + ch.off,
-                                                  Wt + ch.off, ch.psi, o.rho_floor, c->partG.p, c->partG.cap,
-                                                  c->bmat.p + (size_t)q * bstride, c->W.p + ch.off, s));
-            }
+            // Gam overwrites W (the adjoint field is not needed after it)
+            if (!given)
+                HIPCHK(c, launch_gamma((long long)ch.N * ch.M, ch.h * ch.h * ch.h, c->PHI.p + ch.off, c->V.p + ch.off,
+                                       Wt + ch.off, o.rho_floor, c->W.p + ch.off, s));
+            pc[q].N = ch.N;
+            pc[q].M = ch.M;
+            pc[q].X = c->W.p + ch.off;
+            pc[q].Y = ch.psi;
+            pc[q].out = c->bmat.p + (size_t)q * bstride;
+            pc[q].scale = 1.0;
             lb.N[q] = ch.N;
             lb.so[q] = (long long)ch.so;
             lb.go[q] = (long long)goff[c0 + q];
         }
+        HIPCHK(c, launch_contract(pc, lb.n, c->partG.p, c->partG.cap, s));
         HIPCHK(c, launch_lowdin_backward_batch(lb, c->bmat.p, bstride, c->small.p, lo, c->work.p, wstride,
                                                c->d_grad.p, s));
     }
