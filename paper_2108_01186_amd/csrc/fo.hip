@@ -1,30 +1,16 @@
-// Fermi orbitals and their Loewdin orthonormalisation (Eq. 6-8, Sec. I.B),
-// the cubic interpolation of the KS orbitals at the FODs (Sec. II.B), and the
-// reverse-mode derivative of that chain for the FOD gradient (Eq. 9-11).
-//
-// The two grid-sized contractions run on the FP64 matrix cores
-// (v_mfma_f64_16x16x4f64):
+// Fermi orbitals: the cubic interpolation of the KS orbitals at the FODs
+// (Sec. II.B) and its derivative for the FOD gradient (Eq. 9-11).  Of the
+// orbital-sized work that remains, products.hip does
 //   * the Gram matrix G = dV psi psi^T, from which the FO overlap follows
 //     exactly as S = dV F F^T = T G T^T (F = T psi), so F is never stored;
-//   * the Fermi-Loewdin orbitals phi = Q psi with Q = S^{-1/2} T.
-// Everything N x N (N <= 128) runs in one workgroup: S = T G T^T, a parallel
-// cyclic Jacobi eigen-decomposition (round-robin pairing), S^{-1/2}, Q.
+//   * the Fermi-Loewdin orbitals phi = Q psi with Q = S^{-1/2} T,
+// lowdin.hip everything N x N; the fp32 product of FSIC_FP32_ORBITALS is here.
 #include <algorithm>
 #include <cstdint>
 
 #include "kernels.h"
 
 namespace fsic {
-
-typedef double dbl4 __attribute__((ext_vector_type(4)));
-
-// MFMA f64 16x16x4 fragment layout (64 lanes):
-//   A (16 x 4):  lane l holds A[l % 16][l / 16]
-//   B (4 x 16):  lane l holds B[l / 16][l % 16]
-//   D (16 x 16): lane l holds D[l / 16 + 4 j][l % 16], j = 0..3 (rows interleaved)
-__device__ __forceinline__ dbl4 mfma16x16x4(double a, double b, dbl4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
 
 // ---------------------------------------------------------------------------
 // cubic interpolation at the FODs, T = u / |u|
@@ -169,207 +155,6 @@ hipError_t launch_interp(int K, int N, int nx, int ny, int nz, double h, const d
     else
         hipLaunchKernelGGL(k_interp<false>, dim3(K), dim3(128), 0, s, N, nx, ny, nz, h, psi, cells,
                            floor, u, du, rhoa, T, status);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Loewdin: S = T G T^T, Jacobi, Z = S^{-1/2}, Q = Z T (one workgroup)
-// ---------------------------------------------------------------------------
-
-// C = A B (+ transposes) for N x N row-major matrices held anywhere (flat).
-__device__ void small_gemm(int N, const double *A, int ta, const double *B, int tb, double *C,
-                           double alpha) {
-    for (int e = threadIdx.x; e < N * N; e += blockDim.x) {
-        const int i = e / N, j = e % N;
-        double s = 0.0;
-        for (int k = 0; k < N; ++k) {
-            const double a = ta ? A[k * N + i] : A[i * N + k];
-            const double b = tb ? B[j * N + k] : B[k * N + j];
-            s += a * b;
-        }
-        C[e] = alpha * s;
-    }
-}
-
-__device__ __forceinline__ void lowdin_one(int N, int Ne, const double *T, const double *G,
-                                           double *S, double *lam, double *U, double *Z,
-                                           double *Qm, double *work, int lds_mode,
-                                           double eig_floor, int *status, double *info) {
-    extern __shared__ double dsm[];
-    __shared__ double rc[kMaxOrb / 2], rs_[kMaxOrb / 2];
-    __shared__ int rp[kMaxOrb / 2], rq[kMaxOrb / 2];
-    __shared__ double sred[4];
-    __shared__ int sflag;
-    // A (Ne x Ne) and V (Ne x Ne) in LDS or in work
-    double *A = (lds_mode >= 1) ? dsm : work;
-    double *V = (lds_mode >= 2) ? dsm + Ne * Ne : work + Ne * Ne;
-    double *TG = work + 2 * Ne * Ne;  // N x N scratch
-    // TG = T G
-    small_gemm(N, T, 0, G, 0, TG, 1.0);
-    __syncthreads();
-    // S = TG T^T, exactly symmetric, padded to Ne with the identity
-    for (int e = threadIdx.x; e < Ne * Ne; e += 256) {
-        const int i = e / Ne, j = e % Ne;
-        double v;
-        if (i < N && j < N) {
-            const int a = min(i, j), b = max(i, j);
-            double s = 0.0;
-            for (int k = 0; k < N; ++k) s += TG[a * N + k] * T[b * N + k];
-            v = s;
-            S[i * N + j] = v;
-        } else {
-            v = (i == j) ? 1.0 : 0.0;
-        }
-        A[e] = v;
-        V[e] = (i == j) ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    const int half = Ne / 2;
-    for (int sweep = 0; sweep < 40; ++sweep) {
-        // convergence: off-diagonal vs diagonal mass
-        double off = 0.0, dg = 0.0;
-        for (int e = threadIdx.x; e < Ne * Ne; e += 256) {
-            const int i = e / Ne, j = e % Ne;
-            const double a = A[e];
-            if (i == j) dg += a * a; else off += a * a;
-        }
-        off = block_sum256(off, sred);
-        dg = block_sum256(dg, sred);
-        if (off <= 1e-30 * dg) break;
-        for (int r = 0; r < Ne - 1; ++r) {
-            // round-robin pairing: position 0 holds index 0, positions 1..Ne-1
-            // hold 1..Ne-1 rotated by r; pair position j with Ne-1-j
-            if (threadIdx.x < half) {
-                const int j = threadIdx.x;
-                auto at = [&](int pos) { return pos == 0 ? 0 : ((pos - 1 + r) % (Ne - 1)) + 1; };
-                int p = at(j), q = at(Ne - 1 - j);
-                if (p > q) { const int t = p; p = q; q = t; }
-                const double apq = A[p * Ne + q], app = A[p * Ne + p], aqq = A[q * Ne + q];
-                double c = 1.0, s = 0.0;
-                if (apq != 0.0 && fabs(apq) > 1e-300) {
-                    const double tau = (aqq - app) / (2.0 * apq);
-                    const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                    c = 1.0 / sqrt(1.0 + t * t);
-                    s = t * c;
-                }
-                rp[j] = p; rq[j] = q; rc[j] = c; rs_[j] = s;
-            }
-            __syncthreads();
-            // A <- J^T A J by 2 x 2 blocks (rows of pair i, columns of pair
-            // j: the blocks are disjoint, so each updates in place; rows
-            // first, then columns), the rotated pair's own entry set to
-            // zero; V <- V J by rows
-            const int nA = half * half;
-            for (int e = threadIdx.x; e < nA + Ne * half; e += 256) {
-                if (e < nA) {
-                    const int bi = e / half, bj = e - bi * half;
-                    const int pi = rp[bi], qi = rq[bi], pj = rp[bj], qj = rq[bj];
-                    const double ci = rc[bi], si = rs_[bi], cj = rc[bj], sj = rs_[bj];
-                    const double a_pp = A[pi * Ne + pj], a_pq = A[pi * Ne + qj];
-                    const double a_qp = A[qi * Ne + pj], a_qq = A[qi * Ne + qj];
-                    const double r_pp = ci * a_pp - si * a_qp, r_pq = ci * a_pq - si * a_qq;
-                    const double r_qp = si * a_pp + ci * a_qp, r_qq = si * a_pq + ci * a_qq;
-                    double o_pq = sj * r_pp + cj * r_pq, o_qp = cj * r_qp - sj * r_qq;
-                    if (bi == bj && si != 0.0) o_pq = o_qp = 0.0;
-                    A[pi * Ne + pj] = cj * r_pp - sj * r_pq;
-                    A[pi * Ne + qj] = o_pq;
-                    A[qi * Ne + pj] = o_qp;
-                    A[qi * Ne + qj] = sj * r_qp + cj * r_qq;
-                } else {
-                    const int e2 = e - nA, rw = e2 / half, j = e2 - rw * half;
-                    const int p = rp[j], q = rq[j];
-                    const double c = rc[j], s = rs_[j];
-                    const double vp = V[rw * Ne + p], vq = V[rw * Ne + q];
-                    V[rw * Ne + p] = c * vp - s * vq;
-                    V[rw * Ne + q] = s * vp + c * vq;
-                }
-            }
-            __syncthreads();
-        }
-    }
-    // eigenvalues, condition number, singularity test
-    if (threadIdx.x == 0) sflag = 0;
-    __syncthreads();
-    for (int i = threadIdx.x; i < N; i += 256) lam[i] = A[i * Ne + i];
-    for (int e = threadIdx.x; e < N * N; e += 256) U[e] = V[(e / N) * Ne + (e % N)];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double mn = lam[0], mx = lam[0];
-        for (int i = 1; i < N; ++i) { mn = fmin(mn, lam[i]); mx = fmax(mx, lam[i]); }
-        info[0] = mx / mn;
-        info[1] = mn;
-        if (!(mn > eig_floor)) { atomicOr(status, kStSingular); sflag = 1; }
-    }
-    __syncthreads();
-    if (sflag) return;
-    // Z = U diag(lam^{-1/2}) U^T ; Q = Z T
-    double *W = work + 2 * Ne * Ne;
-    for (int e = threadIdx.x; e < N * N; e += 256) W[e] = U[e] / sqrt(lam[e % N]);
-    __syncthreads();
-    small_gemm(N, W, 0, U, 1, Z, 1.0);
-    __syncthreads();
-    small_gemm(N, Z, 0, T, 0, Qm, 1.0);
-}
-
-__global__ __launch_bounds__(256) void k_lowdin(int N, int Ne, const double *T, const double *G,
-                                                double *S, double *lam, double *U, double *Z,
-                                                double *Qm, double *work, int lds_mode,
-                                                double eig_floor, int *status, double *info) {
-    lowdin_one(N, Ne, T, G, S, lam, U, Z, Qm, work, lds_mode, eig_floor, status, info);
-}
-
-// one workgroup per channel: channel b's arrays sit at small + so[b] + the
-// given offsets, its scratch at work + b * wstride
-__global__ __launch_bounds__(256) void k_lowdin_batch(LowdinBatch lb, double *small, LowdinOffsets off,
-                                                      double *work, long long wstride, int lds_mode,
-                                                      double eig_floor, int *status) {
-    const int b = blockIdx.x;
-    const int N = lb.N[b], Ne = N + (N & 1);
-    double *sm = small + lb.so[b];
-    lowdin_one(N, Ne, sm + off.T, sm + off.G, sm + off.S, sm + off.lam, sm + off.U, sm + off.Z,
-               sm + off.Q, work + (size_t)b * wstride, lds_mode, eig_floor, status, sm + off.info);
-}
-
-// LDS mode of the Loewdin kernels for channels of up to N orbitals: 2 keeps
-// A and V in LDS, 1 only A, 0 neither (then both live in the scratch)
-static int lowdin_lds(int N, size_t &dyn) {
-    const int Ne = N + (N & 1);
-    int dev = 0;
-    hipGetDevice(&dev);
-    int maxsh = 0;
-    hipDeviceGetAttribute(&maxsh, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-    const size_t static_bytes = 4 * 64 * 8 + 64;  // rotation tables, reductions
-    const size_t need1 = (size_t)Ne * Ne * sizeof(double);
-    dyn = 0;
-    if (2 * need1 + static_bytes <= (size_t)maxsh) { dyn = 2 * need1; return 2; }
-    if (need1 + static_bytes <= (size_t)maxsh) { dyn = need1; return 1; }
-    return 0;
-}
-
-hipError_t launch_lowdin(int N, const double *T, const double *G, double *S, double *lam,
-                         double *U, double *Z, double *Qm, double *work, double eig_floor,
-                         int *status, double *info, hipStream_t s) {
-    const int Ne = N + (N & 1);
-    size_t dyn = 0;
-    const int mode = lowdin_lds(N, dyn);
-    if (dyn > 65536) hipFuncSetAttribute((const void *)k_lowdin, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
-    hipLaunchKernelGGL(k_lowdin, dim3(1), dim3(256), dyn, s, N, Ne, T, G, S, lam, U, Z, Qm, work,
-                       mode, eig_floor, status, info);
-    return hipGetLastError();
-}
-
-hipError_t launch_lowdin_batch(const LowdinBatch &lb, double *small, const LowdinOffsets &off,
-                               double *work, long long wstride, double eig_floor, int *status,
-                               hipStream_t s) {
-    if (lb.n <= 0 || lb.n > kLowdinBatch) return hipErrorInvalidValue;
-    int nmax = 1;
-    for (int b = 0; b < lb.n; ++b) nmax = std::max(nmax, lb.N[b]);
-    size_t dyn = 0;
-    const int mode = lowdin_lds(nmax, dyn);
-    if (dyn > 65536)
-        hipFuncSetAttribute((const void *)k_lowdin_batch, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
-    hipLaunchKernelGGL(k_lowdin_batch, dim3(lb.n), dim3(256), dyn, s, lb, small, off, work, wstride, mode,
-                       eig_floor, status);
     return hipGetLastError();
 }
 

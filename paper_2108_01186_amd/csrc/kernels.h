@@ -426,14 +426,14 @@ hipError_t launch_contract(const ProdChan *chans, int n, double *part, size_t ca
 hipError_t launch_transform(const ProdChan *chans, int n, hipStream_t s);
 
 // Loewdin step on one block: S = T G T^T; S = U diag(lam) U^T (parallel
-// Jacobi); Z = S^{-1/2}; Q = Z T.  work: device scratch of >= 2 N^2 doubles.
+// Jacobi); Z = S^{-1/2}; Q = Z T.  work: device scratch of >= N^2 doubles.
 hipError_t launch_lowdin(int N, const double *T, const double *G, double *S, double *lam,
                          double *U, double *Z, double *Qm, double *work, double eig_floor,
                          int *status, double *info, hipStream_t s);
 
 // Loewdin step of up to kLowdinBatch channels in one launch (one workgroup
 // each): channel b has N[b] orbitals and its small arrays at small + so[b]
-// plus the offsets below; scratch of wstride >= 3 N^2 doubles per channel.
+// plus the offsets below; scratch of wstride >= N^2 doubles per channel.
 constexpr int kLowdinBatch = 64;
 struct LowdinBatch {
     int n;
