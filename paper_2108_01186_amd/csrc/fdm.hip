@@ -138,10 +138,10 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_fwd(const Item 
             const bool ymid = 2 * y == ny - 1;
             double a = ra[i], b = rb[i], cc = rc[i], d = rd[i];
             if (SQ) {
-                a = scale * a * a;
-                b = scale * b * b;
-                cc = scale * cc * cc;
-                d = scale * d * d;
+                a = scale * (a * a);
+                b = scale * (b * b);
+                cc = scale * (cc * cc);
+                d = scale * (d * d);
             }
             if (xmid) b = d = 0.0;
             if (ymid) cc = d = 0.0;
@@ -536,8 +536,8 @@ __global__ __launch_bounds__(kFdmThreads<T>) void k_fdm_row(const Item *units, c
             if (MODE == kFdmXFwd) {
                 double a = fe[s], b = fo[s];
                 if (SQ) {
-                    a = scale * a * a;
-                    b = scale * b * b;
+                    a = scale * (a * a);
+                    b = scale * (b * b);
                 }
                 if (2 * k == n - 1) b = 0.0;
                 fe[s] = a + b;

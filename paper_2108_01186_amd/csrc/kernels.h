@@ -204,10 +204,18 @@ bool fdm_xy_fits(int nx, int ny, size_t lds_limit);
 int fdm_occupancy(int pass, int T, int two);
 
 // FP64 residual of the direct solver: res = b + L x with its res.res
-// partials, written to res (null: only the partials; res may be b itself)
+// partials, written to res (null: only the partials; res may be b itself).
+// square: b is an orbital f and the right-hand side scale f^2, its b.b
+// partials at partRU + tot7
 hipError_t launch_residual64(int radius, const Coeffs &c, const Item *items7, int nitems7, const OrbDesc *orb,
-                             const int *done, const double *x, const double *b, double *res, double *partRU,
-                             hipStream_t s);
+                             const int *done, const double *x, const double *b, int square, double scale, double *res,
+                             double *partRU, long long tot7, hipStream_t s);
+// convergence of the direct solver after a residual pass, and the statistics
+// as launch_stage_stats: round 1 sets bb[o] (from the b.b partials bpart, in
+// the residual's layout or the pointwise one) and done[o] of every orbital,
+// later rounds look at those not done, round 0 only stages the residual
+hipError_t launch_direct_check(int norb, const OrbDesc *orb, const double *partRU, const double *bpart, int bstencil,
+                               double tol2, int round, int *done, double *bb, double *stage, hipStream_t s);
 // x += d for the orbitals with done == 0
 hipError_t launch_add_fields(int nitems8, const Item *items8, const OrbDesc *orb, const int *done, double *x,
                              const double *d, hipStream_t s);

@@ -913,7 +913,7 @@ fsic_status prepare_batch(fsic_ctx *c, const Batch &b, int precision) {
     const int nlm = (c->opts.lmax + 1) * (c->opts.lmax + 1);
     HIPCHK(c, c->Gh.ensure((size_t)b.ghosts));
     HIPCHK(c, c->part7.ensure(3 * (size_t)b.tot7));
-    HIPCHK(c, c->partRU.ensure((size_t)b.tot7));
+    HIPCHK(c, c->partRU.ensure(2 * (size_t)b.tot7));
     HIPCHK(c, c->part8.ensure(2 * (size_t)b.tot8));
     HIPCHK(c, c->partH.ensure((size_t)b.hc_elems));
     HIPCHK(c, c->bb.ensure(norb));
@@ -1074,7 +1074,7 @@ fsic_status time_shapes(fsic_ctx *c, const std::vector<Group> &groups, int preci
         auto sweep = [&]() {
             if (direct)
                 return launch_residual64(c->radius, cf, c->d_items7.p, (int)b.items7.size(), c->d_orb.p, nullptr,
-                                         c->R.p, c->B.p, nullptr, c->partRU.p, s);
+                                         c->R.p, c->B.p, 0, 1.0, nullptr, c->partRU.p, b.tot7, s);
             return launch_cg_stencil<T>(c->radius, cf, a, 0, 0, 0, s);
         };
         hipError_t he = sweep();
@@ -1392,13 +1392,17 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
         const fsic_status st = boundary_term(c, b, src, square, qlm_in);
         if (st) return st;
     }
-    HIPCHK(c, launch_rhs(c->radius, c->cf, c->d_items8.p, nit8, c->d_orb.p, src, square, scale,
-                         with_bc ? c->Gh.p : nullptr, c->B.p, nullptr, nullptr, nullptr, c->part8.p, s));
-    HIPCHK(c, launch_reduce_partials(norb, c->d_orb.p, c->part8.p, 0, c->bb.p, s));
-    {
-        const IntFills f{{c->done.p, c->iters.p, c->nact.p, c->ndone.p}, {norb, norb, 6 * norb, 1}, {0, 0, 0, 0}, 4};
-        HIPCHK(c, launch_fill_ints(f, s));
-    }
+    // b = scale f^2 without boundary terms is formed where it is read, by the
+    // first transform pass and the residual pass (same bytes there, and the
+    // pass that wrote b is gone: 32 orbitals at 96^3 1539 -> 1451 us a step);
+    // otherwise it is stored
+    const bool sq = square && !with_bc;
+    const double *const bsrc = sq ? src : c->B.p;
+    const double bscale = sq ? scale : 1.0;
+    if (!sq)
+        HIPCHK(c, launch_rhs(c->radius, c->cf, c->d_items8.p, nit8, c->d_orb.p, src, square, scale,
+                             with_bc ? c->Gh.p : nullptr, c->B.p, nullptr, nullptr, nullptr, c->part8.p, s));
+    HIPCHK(c, c->d_stage.ensure(6 * (size_t)std::max(norb, 1)));
     std::vector<ProfRec> &recs = c->recs;
     recs.clear();
     if (prof)
@@ -1411,34 +1415,42 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
     auto key_of = [&](int v) {
         GraphKey key;
         key.add((long long)(1000 + v));
-        for (const void *p : {(const void *)c->d_orb.p, (const void *)c->d_ftab.p, (const void *)c->B.p,
+        for (const void *p : {(const void *)c->d_orb.p, (const void *)c->d_ftab.p, (const void *)bsrc,
                               (const void *)c->R.p, (const void *)X, (const void *)c->d_fr.p,
-                              (const void *)c->d_items7.p, (const void *)c->partRU.p, (const void *)c->bb.p,
-                              (const void *)c->done.p, (const void *)c->iters.p, (const void *)c->rrfin.p,
-                              (const void *)c->ndone.p})
+                              (const void *)c->d_items7.p, (const void *)c->partRU.p, (const void *)c->part8.p,
+                              (const void *)c->bb.p, (const void *)c->done.p, (const void *)c->d_stage.p})
             key.add(p);
         for (int q = 0; q < kFdmPasses; ++q) key.add((const void *)c->d_fu[q].p);
         for (const FdmClass &cl : b.fcls)
             for (int x : {cl.pass, cl.T, cl.two, cl.blocks, cl.range0}) key.add((long long)x);
         for (long long x : {(long long)nit7, (long long)norb, (long long)c->radius, (long long)c->cf.cpt,
-                            (long long)c->cf.depth})
+                            (long long)c->cf.depth, (long long)sq, (long long)b.tot7})
             key.add(x);
         for (int q = 0; q <= kMaxRadius; ++q) key.add(c->cf.c[q]);
         key.add(tol2);
+        key.add(bscale);
         return key;
     };
     // one application, then the residual check (each captured on its own
     // under FSIC_GRAPHS)
     auto apply = [&](hipStream_t st) -> fsic_status {
-        HIPCHK(c, launch_fdm(plan, c->d_orb.p, nullptr, c->d_ftab.p, c->B.p, 0, 1.0, c->R.p, X, 0, st));
+        HIPCHK(c, launch_fdm(plan, c->d_orb.p, nullptr, c->d_ftab.p, bsrc, sq, bscale, c->R.p, X, 0, st));
+        return FSIC_OK;
+    };
+    // the residual of x, of the orbitals not in dn, written to r if not null
+    auto residual = [&](const int *dn, double *r, hipStream_t st) -> fsic_status {
+        HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, dn, X, bsrc, sq, bscale, r,
+                                    c->partRU.p, b.tot7, st));
+        return FSIC_OK;
+    };
+    auto judge = [&](int round, hipStream_t st) -> fsic_status {
+        HIPCHK(c, launch_direct_check(norb, c->d_orb.p, c->partRU.p, sq ? c->partRU.p + b.tot7 : c->part8.p, sq, tol2,
+                                      round, c->done.p, c->bb.p, c->d_stage.p, st));
         return FSIC_OK;
     };
     auto check = [&](hipStream_t st) -> fsic_status {
-        HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, nullptr, X, c->B.p, nullptr,
-                                    c->partRU.p, st));
-        HIPCHK(c, launch_ru_check(norb, c->d_orb.p, c->partRU.p, c->bb.p, tol2, 1, c->done.p, c->iters.p, c->rrfin.p,
-                                  nullptr, c->ndone.p, nullptr, 0, nullptr, 0, st));
-        return FSIC_OK;
+        const fsic_status rs = residual(nullptr, nullptr, st);
+        return rs ? rs : judge(1, st);
     };
     auto timed = [&](int kind, int v, auto &body) -> fsic_status {
         if (prof) {
@@ -1454,10 +1466,12 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
     if (!st) st = timed(3, 1, check);
     if (st) return st;
     auto count = [&]() -> fsic_status {
-        HIPCHK(c, hipMemcpyAsync(c->h_nd, c->ndone.p, sizeof(int), hipMemcpyDeviceToHost, s));
+        const fsic_status cst = copy_stage(c, norb);
+        if (cst) return cst;
         HIPCHK(c, hipEventRecord(c->evc[0], s));
         HIPCHK(c, hipEventSynchronize(c->evc[0]));
-        all = c->h_nd[0] >= norb;
+        const int *const dn = c->h_si + 7 * (size_t)norb;
+        all = std::all_of(dn, dn + norb, [](int d) { return d == 1; });
         return FSIC_OK;
     };
     if ((st = count())) return st;
@@ -1466,27 +1480,19 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
         const size_t F = (size_t)b.fields;
         HIPCHK(c, c->Q.ensure(F));   // r
         HIPCHK(c, c->P0.ensure(F));  // d = K^{-1} r
-        if (rounds == 1)
-            HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, c->done.p, X, c->B.p,
-                                        c->Q.p, c->partRU.p, s));
+        if (rounds == 1 && (st = residual(c->done.p, c->Q.p, s))) return st;
         HIPCHK(c, launch_fdm(plan, c->d_orb.p, c->done.p, c->d_ftab.p, c->Q.p, 0, 1.0, c->R.p, c->P0.p, 0, s));
         HIPCHK(c, launch_add_fields(nit8, c->d_items8.p, c->d_orb.p, c->done.p, X, c->P0.p, s));
-        HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, c->done.p, c->P0.p, c->Q.p,
-                                    c->Q.p, c->partRU.p, s));
-        HIPCHK(c, launch_ru_check(norb, c->d_orb.p, c->partRU.p, c->bb.p, tol2, rounds + 1, c->done.p, c->iters.p,
-                                  c->rrfin.p, nullptr, c->ndone.p, nullptr, 0, nullptr, 0, s));
-        if ((st = count())) return st;
+        HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, c->done.p, c->P0.p, c->Q.p, 0,
+                                    1.0, c->Q.p, c->partRU.p, b.tot7, s));
+        if ((st = judge(rounds + 1, s)) || (st = count())) return st;
     }
     if (!all && !status_error(c)) return FSIC_OK;
     all = true;
     if (mixed) rep.refinements += rounds;
-    if (rounds > 1)  // the residual that is reported is that of x, not of the recursion
-        HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, nullptr, X, c->B.p, nullptr,
-                                    c->partRU.p, s));
-    HIPCHK(c, launch_reduce_partials(norb, c->d_orb.p, c->partRU.p, 1, c->ptrue.p, s));
-    HIPCHK(c, c->d_stage.ensure(6 * (size_t)std::max(norb, 1)));
-    HIPCHK(c, launch_stage_stats(norb, c->iters.p, c->nact.p, c->done.p, c->ptrue.p, c->bb.p, c->d_stage.p, s));
-    if ((st = copy_stage(c, norb))) return st;
+    if (rounds > 1) {  // the residual that is reported is that of x, not of the recursion
+        if ((st = residual(nullptr, nullptr, s)) || (st = judge(0, s)) || (st = copy_stage(c, norb))) return st;
+    }
     c->pend_prof = prof;
     c->pend_aar = false;
     c->pend_pcg = true;
@@ -2005,7 +2011,7 @@ fsic_status finish_solve(fsic_ctx *c, const Batch &b, SolveReport &rep) {
                 // one application and one residual pass: the fused passes read
                 // and write a value three times, the one-axis passes five
                 // times; each axis is transformed forward and back, n flops a
-                // value; the residual pass reads x and b
+                // value; the residual pass reads x and b (or the orbital)
                 c->precond_bytes += Mo * (od.fd_fused ? 48.0 : 80.0);
                 c->precond_flops += Mo * 2.0 * (od.nx + od.ny + od.nz);
                 c->resid_bytes += Mo * 16.0;
@@ -2862,16 +2868,11 @@ fsic_status fsic_op_poisson(const fsic_grid *grid, int32_t fd_order, int32_t lma
     if (hipStreamSynchronize(c->stream) != hipSuccess) return FSIC_EHIP;
     st = finish_solve(c, b, rep);
     if (st) return st;
-    std::vector<int> it(count);
-    std::vector<double> pt(count), bbh(count);
-    hipMemcpy(it.data(), c->iters.p, count * sizeof(int), hipMemcpyDeviceToHost);
-    hipMemcpy(pt.data(), c->ptrue.p, count * sizeof(double), hipMemcpyDeviceToHost);
-    hipMemcpy(bbh.data(), c->bb.p, count * sizeof(double), hipMemcpyDeviceToHost);
-    std::vector<int> dn(count);
-    hipMemcpy(dn.data(), c->done.p, count * sizeof(int), hipMemcpyDeviceToHost);
+    // the statistics staged for finish_solve
     for (int f = 0; f < count; ++f) {
-        if (iters) iters[f] = dn[f] ? it[f] : max_iter;
-        if (relres) relres[f] = bbh[f] > 0 ? std::sqrt(pt[f] / bbh[f]) : 0.0;
+        const double bb = c->h_sd[count + f];
+        if (iters) iters[f] = c->h_si[7 * (size_t)count + f] ? c->h_si[f] : max_iter;
+        if (relres) relres[f] = bb > 0 ? std::sqrt(c->h_sd[f] / bb) : 0.0;
     }
     return rep.converged ? FSIC_OK : FSIC_ENOCONV;
 }

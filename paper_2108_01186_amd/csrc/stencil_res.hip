@@ -84,20 +84,61 @@ hipError_t launch_true_residual(int radius, const Coeffs &c, const Item *items7,
 }
 
 hipError_t launch_residual64(int radius, const Coeffs &c, const Item *items7, int nitems7, const OrbDesc *orb,
-                             const int *done, const double *x, const double *b, double *res, double *partRU,
-                             hipStream_t s) {
+                             const int *done, const double *x, const double *b, int square, double scale, double *res,
+                             double *partRU, long long tot7, hipStream_t s) {
     if (nitems7 <= 0) return hipSuccess;
-    if (res) {
-        PolRes64<true> pol{items7, orb, done, x, b, res, partRU, false};
-#define CALL(P, C, DD) hipLaunchKernelGGL((k_zmarch<double, P, C, DD, PolRes64<true>>), dim3(nitems7), dim3(256), 0, s, pol, c)
-        FSIC_RADIUS_SWITCH(radius, CALL)
-#undef CALL
-    } else {
-        PolRes64<false> pol{items7, orb, done, x, b, res, partRU, false};
-#define CALL(P, C, DD) hipLaunchKernelGGL((k_zmarch<double, P, C, DD, PolRes64<false>>), dim3(nitems7), dim3(256), 0, s, pol, c)
-        FSIC_RADIUS_SWITCH(radius, CALL)
-#undef CALL
+#define RES(WR, SQ)                                                                                                 \
+    {                                                                                                               \
+        PolRes64<WR, SQ> pol{items7, orb, done, x, b, res, partRU, scale, tot7, false};                             \
+        FSIC_RADIUS_SWITCH(radius, CALL)                                                                            \
     }
+#define CALL(P, C, DD) hipLaunchKernelGGL((k_zmarch<double, P, C, DD, decltype(pol)>), dim3(nitems7), dim3(256), 0, s, pol, c)
+    if (square) {
+        if (res) RES(true, true) else RES(false, true)
+    } else {
+        if (res) RES(true, false) else RES(false, false)
+    }
+#undef CALL
+#undef RES
+    return hipGetLastError();
+}
+
+// Convergence of the direct solver's orbitals and the statistics stage of
+// launch_stage_stats.  round 1: b.b from the partials bpart (stencil layout or
+// pointwise), r.r from partRU, every orbital; later rounds: r.r of those not
+// done; round 0: only the reported residual.
+__global__ __launch_bounds__(256) void k_direct_check(int norb, const OrbDesc *orb, const double *partRU,
+                                                      const double *bpart, int bstencil, double tol2, int round,
+                                                      int *done, double *bb, double *stage) {
+    __shared__ double sred[4];
+    const int o = blockIdx.x;
+    if (round > 1 && done[o] == 1) return;
+    const OrbDesc od = orb[o];
+    const double rr = sum_partials(partRU + od.base7, od.nt7, sred);
+    double b2 = 0.0;
+    if (round == 1)
+        b2 = bstencil ? sum_partials(bpart + od.base7, od.nt7, sred) : sum_partials(bpart + od.base8, od.nt8, sred);
+    if (threadIdx.x) return;
+    int *const si = reinterpret_cast<int *>(stage);
+    double *const sd = stage + 4 * (size_t)norb;
+    sd[o] = rr;
+    if (round == 0) return;
+    if (round == 1) {
+        bb[o] = sd[norb + o] = b2;
+        for (int q = 1; q < 7; ++q) si[q * norb + o] = 0;
+    } else {
+        b2 = bb[o];
+    }
+    const int ok = rr <= tol2 * b2;
+    done[o] = si[7 * norb + o] = ok;
+    si[o] = ok ? round : 0;
+}
+
+hipError_t launch_direct_check(int norb, const OrbDesc *orb, const double *partRU, const double *bpart, int bstencil,
+                               double tol2, int round, int *done, double *bb, double *stage, hipStream_t s) {
+    if (norb <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_direct_check, dim3(norb), dim3(256), 0, s, norb, orb, partRU, bpart, bstencil, tol2, round,
+                       done, bb, stage);
     return hipGetLastError();
 }
 

@@ -597,18 +597,22 @@ struct PolRes {  // res = b + L x, x = x64 (+ x32); X64 null (with x32): x64 = 0
     }
 };
 
-// res = b + L x of the direct solver, FP64 throughout; res null: only the
-// partial sums.  res may be b: a block reads b at its own nodes only.
-template <bool WR>
+// res = b + L x of the direct solver, FP64 throughout; res null (WR false):
+// only the partial sums.  res may be b: a block reads b at its own nodes
+// only.  SQ: b = scale f^2 from the orbital f in b's place, its b.b partials
+// at partRU + tot7.
+template <bool WR, bool SQ>
 struct PolRes64 {
     const Item *items;
     const OrbDesc *orb;
     const int *done;
     const double *x, *b;
     double *res, *partRU;
+    double scale;
+    long long tot7;
     struct Raw { double a; };
     typedef double Ext;
-    typedef double Acc;
+    struct Acc { double rr, bb; };
     bool tile0;
     Rsrc rx, rb, rr;
     __device__ bool setup(int o, const OrbDesc &, double *) { return done == nullptr || done[o] != 1; }
@@ -622,13 +626,19 @@ struct PolRes64 {
     __device__ Ext ext(unsigned i, int zo) const { return bld<double>(rb, i, zo); }
     __device__ double combine(const Raw &v) const { return v.a; }
     __device__ void epilogue(unsigned i, int zo, double, double lap, const Ext &bv, Acc &s) const {
-        const double r = bv + lap;
+        const double b0 = SQ ? scale * (bv * bv) : bv;
+        const double r = b0 + lap;
         if constexpr (WR) bst(rr, i, zo, r);
-        s += r * r;
+        s.rr += r * r;
+        if constexpr (SQ) s.bb += b0 * b0;
     }
     __device__ void finish(const Item &it, const OrbDesc &od, const Acc &s, double *sred) const {
-        const double t = block_sum256(s, sred);
+        const double t = block_sum256(s.rr, sred);
         if (threadIdx.x == 0) partRU[od.base7 + it.tile] = t;
+        if constexpr (SQ) {
+            const double u = block_sum256(s.bb, sred);
+            if (threadIdx.x == 0) partRU[tot7 + od.base7 + it.tile] = u;
+        }
     }
 };
 

@@ -129,3 +129,24 @@ def test_nonfinite_density_does_not_reach_other_orbitals(torch_cuda):
     v = v.cpu().numpy()
     for k in (0, 1, 3, 4, 5):
         assert np.abs(v[k] - good[k]).max() < 1e-8 * np.abs(good[k]).max(), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [33, 40])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_orbital_source_with_corrections(torch_cuda, oracle, n, precision):
+    """A whole step whose tolerance one application does not meet (about 1e-13
+    is left of it): the right-hand side is formed from the orbitals in the
+    transform and residual passes, and the corrections' residual is stored.
+    A residual of 1e-14 moves U_i by 1e-14 times the condition of the grid's
+    operator at most (4 n^2 / pi^2, below 700): 1e-11 of the oracle's."""
+    from paper_2108_01186_amd import fsic as F, synth
+    torch = torch_cuda
+    print(f"corrections n={n} {precision}", flush=True)
+    s = synth.make_molecule("corr", n, 12.0 / (n - 1), 3, 8, (3,), seed=5)
+    ref = oracle.sic_spin(s.psi[0], s.fod[0], s.n, s.h, s.origin)
+    psi = torch.tensor(np.asarray(s.psi[0]), device="cuda")
+    ctx = F.Context(precision=precision, tol=1e-14, solver="pcg")
+    e, U, X, st = ctx.forward([{"n": s.n, "h": s.h, "origin": s.origin, "psi": [psi], "fod": [s.fod[0]]}])
+    ctx.close()
+    assert np.abs(U - ref.U).max() < 1e-11 * np.abs(ref.U).max()
