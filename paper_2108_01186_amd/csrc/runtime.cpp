@@ -19,6 +19,7 @@
 #include "../../include/fsic.h"
 #include "fdm_basis.h"
 #include "kernels.h"
+#include "workspace.h"
 
 using namespace fsic;
 
@@ -31,17 +32,16 @@ template <typename T>
 struct DBuf {
     T *p = nullptr;
     size_t cap = 0;
+    bool own = true;  // false: an OpScope's block
     hipError_t ensure(size_t n) {
         if (n <= cap) return hipSuccess;
-        if (p) hipFree(p);
-        p = nullptr;
-        cap = 0;
-        hipError_t e = hipMalloc((void **)&p, std::max<size_t>(n, 1) * sizeof(T));
+        release();
+        const hipError_t e = device_alloc((void **)&p, std::max<size_t>(n, 1) * sizeof(T), own);
         if (e == hipSuccess) cap = n;
         return e;
     }
     void release() {
-        if (p) hipFree(p);
+        if (p && own) hipFree(p);
         p = nullptr;
         cap = 0;
     }
@@ -929,25 +929,25 @@ fsic_status prepare_batch(fsic_ctx *c, const Batch &b, int precision) {
     HIPCHK(c, c->ndone.ensure(1));
     HIPCHK(c, c->fin.ensure(norb));
     HIPCHK(c, c->pz.ensure(norb));
-    if (!c->h_nd) HIPCHK(c, hipHostMalloc((void **)&c->h_nd, 2 * sizeof(int)));
+    if (!c->h_nd) HIPCHK(c, pinned_alloc((void **)&c->h_nd, 2 * sizeof(int)));
     for (hipEvent_t &e : c->evc)
         if (!e) HIPCHK(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
     if (c->h_done_cap < (size_t)norb) {
-        if (c->h_done) hipHostFree(c->h_done);
+        if (c->h_done) pinned_free(c->h_done);
         c->h_done = nullptr;
-        HIPCHK(c, hipHostMalloc((void **)&c->h_done, std::max(norb, 1) * sizeof(int)));
+        HIPCHK(c, pinned_alloc((void **)&c->h_done, std::max(norb, 1) * sizeof(int)));
         c->h_done_cap = norb;
     }
     if (c->h_s_cap < (size_t)norb) {
-        if (c->h_stage) hipHostFree(c->h_stage);
+        if (c->h_stage) pinned_free(c->h_stage);
         c->h_stage = nullptr;
         c->h_si = nullptr;
         c->h_sd = nullptr;
-        HIPCHK(c, hipHostMalloc((void **)&c->h_stage, 6 * (size_t)std::max(norb, 1) * sizeof(double)));
+        HIPCHK(c, pinned_alloc((void **)&c->h_stage, 6 * (size_t)std::max(norb, 1) * sizeof(double)));
         c->h_s_cap = norb;
     }
     if (!c->h_stat) {
-        HIPCHK(c, hipHostMalloc((void **)&c->h_stat, sizeof(int)));
+        HIPCHK(c, pinned_alloc((void **)&c->h_stat, sizeof(int)));
         *c->h_stat = 0;
     }
     return FSIC_OK;
@@ -2152,16 +2152,17 @@ void fsic_destroy(fsic_ctx *c) {
     for (hipEvent_t e : c->ev) hipEventDestroy(e);
     for (auto &g : c->graphs) hipGraphExecDestroy(g.second);
     if (c->cap_stream) hipStreamDestroy(c->cap_stream);
-    if (c->h_done) hipHostFree(c->h_done);
-    if (c->h_nd) hipHostFree(c->h_nd);
-    if (c->h_stage) hipHostFree(c->h_stage);
-    if (c->h_stat) hipHostFree(c->h_stat);
-    if (c->h_chk) hipHostFree(c->h_chk);
-    if (c->h_eux) hipHostFree(c->h_eux);
-    if (c->h_grad) hipHostFree(c->h_grad);
+    if (c->h_done) pinned_free(c->h_done);
+    if (c->h_nd) pinned_free(c->h_nd);
+    if (c->h_stage) pinned_free(c->h_stage);
+    if (c->h_stat) pinned_free(c->h_stat);
+    if (c->h_chk) pinned_free(c->h_chk);
+    if (c->h_eux) pinned_free(c->h_eux);
+    if (c->h_grad) pinned_free(c->h_grad);
     for (hipEvent_t e : c->evc)
         if (e) hipEventDestroy(e);
     c->ndone.release(); c->fin.release(); c->pz.release();
+    if (!OpScope::current()) BlockCache::get().flush();
     delete c;
 }
 
@@ -2490,10 +2491,10 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     const size_t neux = 2 * (size_t)norb + nchan;
     HIPCHK(c, c->eux.ensure(neux));
     if (c->h_eux_cap < neux) {
-        if (c->h_eux) hipHostFree(c->h_eux);
+        if (c->h_eux) pinned_free(c->h_eux);
         c->h_eux = nullptr;
         c->h_eux_cap = 0;
-        HIPCHK(c, hipHostMalloc((void **)&c->h_eux, neux * sizeof(double)));
+        HIPCHK(c, pinned_alloc((void **)&c->h_eux, neux * sizeof(double)));
         c->h_eux_cap = neux;
     }
     HIPCHK(c, hipMemsetAsync(c->status.p, 0, sizeof(int), s));
@@ -2537,10 +2538,10 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     size_t chk_n = 0;
     for (const Chan &ch : chans) chk_n += (size_t)ch.N * ch.N + 2 + ch.N;
     if (c->h_chk_cap < chk_n) {
-        if (c->h_chk) hipHostFree(c->h_chk);
+        if (c->h_chk) pinned_free(c->h_chk);
         c->h_chk = nullptr;
         c->h_chk_cap = 0;
-        HIPCHK(c, hipHostMalloc((void **)&c->h_chk, chk_n * sizeof(double)));
+        HIPCHK(c, pinned_alloc((void **)&c->h_chk, chk_n * sizeof(double)));
         c->h_chk_cap = chk_n;
     }
     HIPCHK(c, hipMemcpyAsync(c->h_stat, c->status.p, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -2756,6 +2757,7 @@ fsic_status fsic_op_laplacian(const int32_t *n, double h, int32_t fd_order, int3
     Batch b;
     build_batch(groups, P, Shape{2, 2, 4096}, b, kNoPrecond);  // fd_weights: cpt 2, depth 2
     hipStream_t s = (hipStream_t)hip_stream;
+    OpScope scope(s);
     DBuf<OrbDesc> dorb;
     DBuf<Item> dit;
     if (dorb.ensure(b.orb.size()) || dit.ensure(b.items7.size())) return FSIC_ENOMEM;
@@ -2782,6 +2784,7 @@ fsic_status fsic_op_hamiltonian(const int32_t *n, double h, int32_t fd_order, in
     Batch b;
     build_batch(groups, P, Shape{2, 2, 4096}, b, kNoPrecond);  // fd_weights: cpt 2, depth 2
     hipStream_t s = (hipStream_t)hip_stream;
+    OpScope scope(s);
     DBuf<OrbDesc> dorb;
     DBuf<Item> dit;
     if (dorb.ensure(b.orb.size()) || dit.ensure(b.items7.size())) return FSIC_ENOMEM;
@@ -2808,6 +2811,7 @@ fsic_status fsic_op_laplacian_f32(const int32_t *n, double h, int32_t fd_order, 
     Batch b;
     build_batch(groups, P, Shape{2, 2, 4096}, b, kNoPrecond);  // fd_weights: cpt 2, depth 2
     hipStream_t s = (hipStream_t)hip_stream;
+    OpScope scope(s);
     DBuf<OrbDesc> dorb;
     DBuf<Item> dit;
     if (dorb.ensure(b.orb.size()) || dit.ensure(b.items7.size())) return FSIC_ENOMEM;
@@ -2844,6 +2848,7 @@ fsic_status fsic_op_poisson(const fsic_grid *grid, int32_t fd_order, int32_t lma
     o.solver = solver;
     std::string why;
     if (validate_opts(&o, why) || validate_grid(*grid, why)) return FSIC_EINVAL;
+    OpScope scope((hipStream_t)hip_stream);
     OpCtx oc;
     fsic_status st = fsic_create(&oc.c, &o, hip_stream);
     if (st) return st;
@@ -2882,6 +2887,7 @@ fsic_status fsic_op_invsqrt(int32_t N, int32_t count, const double *S, double *Z
     if (N < 1 || N > kMaxOrb || count < 1 || !S || !Z) return FSIC_EINVAL;
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t NN = (size_t)N * N;
+    OpScope scope(s);
     DBuf<double> T, tmp, work, info;
     DBuf<int> status;
     if (T.ensure(NN) || tmp.ensure(5 * NN) || work.ensure(3 * (size_t)kMaxOrb * kMaxOrb) ||
@@ -2925,6 +2931,7 @@ fsic_status fsic_op_interp(const fsic_grid *grid, int32_t N, int32_t K, const do
             cells[i].i0[d] = (int)fl;
             cells[i].t[d] = sc - fl;
         }
+    OpScope scope(s);
     DBuf<double> rhoa, T;
     DBuf<FodCell> dc;
     DBuf<int> status;
@@ -2994,6 +3001,7 @@ fsic_status fsic_op_flo(const fsic_grid *grid, int32_t N, const double *psi, con
     }
     const long long M = (long long)grid->n[0] * grid->n[1] * grid->n[2];
     const double dV = grid->h * grid->h * grid->h;
+    OpScope scope(s);
     DBuf<double> sm, work, partG;
     DBuf<FodCell> dc;
     DBuf<int> status;
@@ -3103,10 +3111,10 @@ static fsic_status backward_enqueue(fsic_ctx *c, bool fused, BwdState &bs) {
     goff.assign(c->chans.size() + 1, 0);
     for (size_t ci = 0; ci < c->chans.size(); ++ci) goff[ci + 1] = goff[ci] + 3 * (size_t)c->chans[ci].N;
     if (c->h_grad_cap < goff.back()) {
-        if (c->h_grad) hipHostFree(c->h_grad);
+        if (c->h_grad) pinned_free(c->h_grad);
         c->h_grad = nullptr;
         c->h_grad_cap = 0;
-        HIPCHK(c, hipHostMalloc((void **)&c->h_grad, std::max<size_t>(goff.back(), 1) * sizeof(double)));
+        HIPCHK(c, pinned_alloc((void **)&c->h_grad, std::max<size_t>(goff.back(), 1) * sizeof(double)));
         c->h_grad_cap = goff.back();
     }
     // per channel B = Gam psi^T into its own block of bmat, then the reverse
