@@ -13,6 +13,16 @@
 // v_mfma_f64_16x16x4_f64; at 96^3 the two are level (16 B at 5.1 TB/s, 192
 // flops at 72 TFLOP/s), longer axes are bound by the matrix cores.
 //
+// An FP64 matrix product holds a SIMD's vector unit for 64 cycles, so what a
+// wave does beside them adds to the time, and memory has to be under way
+// during them.  Hence: descriptors through __restrict__ pointers and
+// readfirstlane (scalar loads, uniform buffer resources; as vector loads each
+// of them waited for all stores before it), raw buffer loads of the next unit
+// issued as soon as registers are free, and stores that are never predicated
+// (positions outside are dropped by the buffer's bounds).  Against plain
+// pointers, 32 orbitals at 96^3: z pass 148 -> 128 us, in-plane pair
+// 375 -> 357 us; 64 at 128^3: 765 -> 660 us, 1630 -> 1530 us.
+//
 // Layout of v_mfma_f64_16x16x4_f64 used throughout: with g = lane / 16 and
 // c = lane % 16, operand A holds (row c, k g), B holds (k g, column c) and
 // accumulator element r holds (row g + 4 r, column c).  Accumulator element
@@ -25,6 +35,7 @@
 
 #include "fdm_basis.h"
 #include "kernels.h"
+#include "zmarch.h"
 
 namespace fsic {
 
@@ -35,6 +46,19 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ dbl4 mfma(double a, double b, dbl4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
+
+// values that are the same in every lane, for scalar registers (the compiler
+// cannot know that of loads beside stores, and a buffer resource in vector
+// registers makes a loop of every access)
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ long long uni(long long v) {
+    return (long long)((unsigned long long)(unsigned)uni((int)(v >> 32)) << 32 | (unsigned)uni((int)v));
+}
+
+// element index of a store that is to be dropped: beyond every buffer.  Stores
+// are issued in any case, so that the number of stores behind a prefetch is
+// known and waiting for the one does not wait for the others
+constexpr unsigned kDrop = 0x1fffffffu;
 
 // LDS row stride of an axis matrix with 16 T columns: operand reads whose
 // row runs with c are free of bank conflicts, the others take two passes
@@ -80,8 +104,8 @@ constexpr int kXyWaves = T == 3 ? 3 : 2;
 // modes before odd ones on both axes) so that the inverse pass reads whole
 // rows in its operand layout.  SQ: b = scale src^2, else b = src.
 template <int T, bool SQ>
-__global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_fwd(const Item *units, const FdmRange *ranges,
-                                                         const OrbDesc *orb, const int *done, const double *tab,
+__global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_fwd(const Item *__restrict__ units, const FdmRange *__restrict__ ranges,
+                                                         const OrbDesc *__restrict__ orb, const int *__restrict__ done, const double *__restrict__ tab,
                                                          int two, const double *src, double scale, double *out) {
     constexpr int L = 16 * T, S = kStr<T>, NT = 128 * T, NQ = 2 * T;
     extern __shared__ __attribute__((aligned(16))) double fsm[];
@@ -97,37 +121,45 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_fwd(const Item 
         if (two) load_table<T, false>(My, tab + od.fd_t[1], od.fd_n[1], NT);
     }
     auto next = [&](int u) {
-        while (u < rg.u1 && done && done[units[u].orb]) ++u;
+        while (u < rg.u1 && done && uni(done[units[u].orb])) ++u;
         return u;
     };
     const int xq = tid % L, yq0 = tid / L;  // fold quads (yq0 + 8 i, xq)
     double ra[NQ], rb[NQ], rc[NQ], rd[NQ];
-    auto issue = [&](int u) {
+    // half of a plane's loads: rows y (h 0) or their mirror rows (h 1)
+    auto issue = [&](int u, int h) {
         const Item it = units[u];
-        const OrbDesc &od = orb[it.orb];
-        const int nx = od.nx, ny = od.ny, hx = (nx + 1) >> 1, hy = (ny + 1) >> 1;
-        const double *p = src + od.off + (long long)it.tile * nx * ny;
+        const OrbDesc &od = orb[uni(it.orb)];
+        const int nx = uni(od.nx), ny = uni(od.ny), hx = (nx + 1) >> 1, hy = (ny + 1) >> 1;
+        const Rsrc r = make_rsrc(src + uni(od.off) + (long long)uni(it.tile) * nx * ny, (unsigned)(nx * ny) * 8u);
         const int x = min(xq, hx - 1), xm = nx - 1 - x;
 #pragma unroll
         for (int i = 0; i < NQ; ++i) {
-            const int y = min(yq0 + 8 * i, hy - 1), ym = ny - 1 - y;
-            ra[i] = p[y * nx + x];
-            rb[i] = p[y * nx + xm];
-            rc[i] = p[ym * nx + x];
-            rd[i] = p[ym * nx + xm];
+            const int y = min(yq0 + 8 * i, hy - 1);
+            if (h == 0) {
+                ra[i] = bld<double>(r, (unsigned)(y * nx + x), 0);
+                rb[i] = bld<double>(r, (unsigned)(y * nx + xm), 0);
+            } else {
+                rc[i] = bld<double>(r, (unsigned)((ny - 1 - y) * nx + x), 0);
+                rd[i] = bld<double>(r, (unsigned)((ny - 1 - y) * nx + xm), 0);
+            }
         }
     };
     int u = next(rg.u0), last = -1;
-    if (u < rg.u1) issue(u);
+    if (u < rg.u1) {
+        issue(u, 1);
+        issue(u, 0);
+    }
     while (u < rg.u1) {
         const Item it = units[u];
-        const OrbDesc &od = orb[it.orb];
-        const int nx = od.nx, ny = od.ny, hx = (nx + 1) >> 1, hy = (ny + 1) >> 1;
+        const int oi = uni(it.orb);
+        const OrbDesc &od = orb[oi];
+        const int nx = uni(od.nx), ny = uni(od.ny), hx = (nx + 1) >> 1, hy = (ny + 1) >> 1;
         const int ox = nx >> 1, oy = ny >> 1;
         const int ksx = (hx + 3) >> 2, ksy = (hy + 3) >> 2;
-        if (it.orb != last) {  // nothing of another orbital stays in the padding
+        if (oi != last) {  // nothing of another orbital stays in the padding
             for (int i = tid; i < 2 * L * L; i += NT) X[i] = 0.0;
-            last = it.orb;
+            last = oi;
             __syncthreads();
         }
         // fold: a centre node enters once
@@ -155,8 +187,11 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_fwd(const Item 
             }
         }
         const int un = next(u + 1);
-        double *const o = out + od.off + (long long)it.tile * nx * ny;
-#pragma unroll 1
+        const Rsrc ro = make_rsrc(out + uni(od.off) + (long long)uni(it.tile) * nx * ny, (unsigned)(nx * ny) * 8u);
+        // the next plane's loads go out in halves, as their registers come free:
+        // blocks run in step, and one burst a plane would wait for the memory
+        if (un < rg.u1) issue(un, 1);
+#pragma unroll
         for (int px = 0; px < 2; ++px) {
             if (px == 1) {
                 lds_barrier();  // the even quadrants are read
@@ -169,7 +204,7 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_fwd(const Item 
                         X[L * L + q] = ra[i] - rb[i];
                     }
                 }
-                if (un < rg.u1) issue(un);
+                if (un < rg.u1) issue(un, 0);
             }
             lds_barrier();
             const double *Xq = X + py * L * L, *By = My + py * L * S, *Ax = Mx + px * L * S;
@@ -193,26 +228,25 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_fwd(const Item 
                 for (int t = 0; t < T; ++t) E[t] = mfma(Ax[(16 * t + c) * S + 4 * s + g], D[s >> 2][s & 3], E[t]);
             }
             const int ky = 16 * kt + c, kmax = px ? ox : hx;
-            if (ky < (py ? oy : hy)) {
-                double *q = o + (py ? hy : 0) + ky + (long long)(px ? hx : 0) * ny;
+            const bool kyok = ky < (py ? oy : hy);
+            const int q = (py ? hy : 0) + ky + (px ? hx : 0) * ny;
 #pragma unroll
-                for (int t = 0; t < T; ++t)
+            for (int t = 0; t < T; ++t)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int kx = 16 * t + g + 4 * r;
-                        if (kx < kmax) q[kx * ny] = E[t][r];
-                    }
-            }
+                for (int r = 0; r < 4; ++r) {
+                    const int kx = 16 * t + g + 4 * r;
+                    bst(ro, kyok && kx < kmax ? (unsigned)(q + kx * ny) : kDrop, 0, E[t][r]);
+                }
         }
         lds_barrier();  // the odd quadrants are read
         u = un;
     }
 }
 
-// in-plane spectral coefficients [z][kx][ky] -> x (ACC: x += the result)
-template <int T, bool ACC>
-__global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_inv(const Item *units, const FdmRange *ranges,
-                                                         const OrbDesc *orb, const int *done, const double *tab,
+// in-plane spectral coefficients [z][kx][ky] -> x
+template <int T>
+__global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_inv(const Item *__restrict__ units, const FdmRange *__restrict__ ranges,
+                                                         const OrbDesc *__restrict__ orb, const int *__restrict__ done, const double *__restrict__ tab,
                                                          int two, const double *in, double *out) {
     constexpr int L = 16 * T, S = kStr<T>, NT = 128 * T, NR = 4 * T;
     extern __shared__ __attribute__((aligned(16))) double fsm[];
@@ -228,7 +262,7 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_inv(const Item 
         if (two) load_table<T, true>(My, tab + od.fd_t[1], od.fd_n[1], NT);
     }
     auto next = [&](int u) {
-        while (u < rg.u1 && done && done[units[u].orb]) ++u;
+        while (u < rg.u1 && done && uni(done[units[u].orb])) ++u;
         return u;
     };
     // staging: two half rows (py) of L modes per row kx, 4 rows per sweep
@@ -236,17 +270,17 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_inv(const Item 
     double rv[NR];
     auto issue = [&](int u, int px) {
         const Item it = units[u];
-        const OrbDesc &od = orb[it.orb];
-        const int nx = od.nx, ny = od.ny, hx = (nx + 1) >> 1, hy = (ny + 1) >> 1;
-        const double *p = in + od.off + (long long)it.tile * nx * ny + (long long)(px ? hx : 0) * ny;
+        const OrbDesc &od = orb[uni(it.orb)];
+        const int nx = uni(od.nx), ny = uni(od.ny), hx = (nx + 1) >> 1, hy = (ny + 1) >> 1;
+        const Rsrc r = make_rsrc(in + uni(od.off) + (long long)uni(it.tile) * nx * ny, (unsigned)(nx * ny) * 8u);
         const int rows = px ? nx >> 1 : hx, cols = sp ? ny >> 1 : hy;
-        const int col = min(sj, cols - 1) + (sp ? hy : 0);
+        const int col = min(sj, cols - 1) + (sp ? hy : 0), row0 = px ? hx : 0;
 #pragma unroll
-        for (int i = 0; i < NR; ++i) rv[i] = p[min(sr + 4 * i, rows - 1) * ny + col];
+        for (int i = 0; i < NR; ++i) rv[i] = bld<double>(r, (unsigned)((row0 + min(sr + 4 * i, rows - 1)) * ny + col), 0);
     };
-    auto stage = [&](const OrbDesc &od, int px) {
-        const int hx = (od.nx + 1) >> 1, hy = (od.ny + 1) >> 1;
-        const int rows = px ? od.nx >> 1 : hx, cols = sp ? od.ny >> 1 : hy;
+    auto stage = [&](int nx, int ny, int px) {
+        const int hx = (nx + 1) >> 1, hy = (ny + 1) >> 1;
+        const int rows = px ? nx >> 1 : hx, cols = sp ? ny >> 1 : hy;
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
             const int k = sr + 4 * i;
@@ -257,15 +291,15 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_inv(const Item 
     if (u < rg.u1) issue(u, 0);
     while (u < rg.u1) {
         const Item it = units[u];
-        const OrbDesc &od = orb[it.orb];
-        const int nx = od.nx, ny = od.ny, hx = (nx + 1) >> 1, hy = (ny + 1) >> 1;
+        const OrbDesc &od = orb[uni(it.orb)];
+        const int nx = uni(od.nx), ny = uni(od.ny), hx = (nx + 1) >> 1, hy = (ny + 1) >> 1;
         const int ox = nx >> 1, oy = ny >> 1;
         const int ksx = (hx + 3) >> 2, ksy = (hy + 3) >> 2;
         const int un = next(u + 1);
         dbl4 D[2][T];
 #pragma unroll
         for (int px = 0; px < 2; ++px) {
-            stage(od, px);
+            stage(nx, ny, px);
             if (px == 0) issue(u, 1);
             else if (un < rg.u1) issue(un, 0);
             lds_barrier();
@@ -312,7 +346,8 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_inv(const Item 
         lds_barrier();
         const int xl = 16 * xt + c;
         const bool xok = xl < (py ? ox : hx);
-        double *const o = out + od.off + (long long)it.tile * nx * ny + (py ? nx - 1 - xl : xl);
+        const Rsrc ro = make_rsrc(out + uni(od.off) + (long long)uni(it.tile) * nx * ny, (unsigned)(nx * ny) * 8u);
+        const int xo = py ? nx - 1 - xl : xl;
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -320,16 +355,8 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_inv(const Item 
                 const double v = theirs[(4 * t + r) * 64 + lane];
                 const double e = py ? v : EL[t][r], d = py ? ER[t][r] : v;
                 const int y = 16 * t + g + 4 * r;
-                if (xok && y < hy) {
-                    const int i1 = y * nx, i2 = (ny - 1 - y) * nx;
-                    if (ACC) {
-                        o[i1] += e + d;
-                        if (y < oy) o[i2] += e - d;
-                    } else {
-                        o[i1] = e + d;
-                        if (y < oy) o[i2] = e - d;
-                    }
-                }
+                bst(ro, xok && y < hy ? (unsigned)(y * nx + xo) : kDrop, 0, e + d);
+                bst(ro, xok && y < oy ? (unsigned)((ny - 1 - y) * nx + xo) : kDrop, 0, e - d);
             }
         lds_barrier();  // the exchange tiles are read
         u = un;
@@ -342,55 +369,48 @@ __global__ __launch_bounds__(128 * T, kXyWaves<T>) void k_fdm_xy_inv(const Item 
 // the axis matrices in LDS.  No barrier and no LDS traffic for the data.
 // ---------------------------------------------------------------------------
 
-enum { kFdmZ = 0, kFdmYFwd = 1, kFdmYInv = 2, kFdmXFwd = 3, kFdmXInv = 4 };
+enum { kFdmYFwd, kFdmYInv, kFdmXFwd, kFdmXInv };
 
 template <int T>
 constexpr int kFdmThreads = T <= 3 ? 256 : 512;
 
 // lines as columns of the B operand (x or y-x neighbours contiguous):
-//   kFdmZ: transform, scale by h^2 / (lam_x + lam_y + lam_z), transform back,
-//          in place; lines: in-plane points;
 //   kFdmYFwd / kFdmYInv: along y, lines (z, x).
 template <int T, int MODE>
-__global__ __launch_bounds__(kFdmThreads<T>) void k_fdm_col(const Item *units, const FdmRange *ranges,
-                                                             const OrbDesc *orb, const int *done,
-                                                             const double *tab, const double *in, double *out) {
+__global__ __launch_bounds__(kFdmThreads<T>) void k_fdm_col(const Item *__restrict__ units, const FdmRange *__restrict__ ranges,
+                                                             const OrbDesc *__restrict__ orb, const int *__restrict__ done,
+                                                             const double *__restrict__ tab, const double *in, double *out) {
     constexpr int L = 16 * T, S = kStr<T>, NT = kFdmThreads<T>, NW = NT / 64;
-    constexpr int AX = MODE == kFdmZ ? 2 : 1;
     extern __shared__ __attribute__((aligned(16))) double fsm[];
     const FdmRange rg = ranges[blockIdx.x];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, c = lane & 15;
     {
         const OrbDesc &od = orb[units[rg.u0].orb];
-        load_table<T, MODE != kFdmYFwd>(fsm, tab + od.fd_t[AX], od.fd_n[AX], NT);
+        load_table<T, MODE != kFdmYFwd>(fsm, tab + od.fd_t[1], od.fd_n[1], NT);
     }
     __syncthreads();
-    // mode 16 t + c, position 4 s + g (forward A operand); position 16 t + c,
-    // mode 4 s + g (inverse A operand)
-    auto F = [&](int par, int t, int s) {
-        const double *M = fsm + par * L * S;
-        return MODE == kFdmYFwd ? M[(16 * t + c) * S + 4 * s + g] : M[(4 * s + g) * S + 16 * t + c];
-    };
-    auto I = [&](int par, int t, int s) { return fsm[par * L * S + (16 * t + c) * S + 4 * s + g]; };
+    // A operand: mode 16 t + c, position 4 s + g (forward); position 16 t + c,
+    // mode 4 s + g (inverse)
+    auto F = [&](int par, int t, int s) { return fsm[par * L * S + (16 * t + c) * S + 4 * s + g]; };
     const int nsub = 4 * (rg.u1 - rg.u0);
     for (int sub = w; sub < nsub; sub += NW) {
         const Item it = units[rg.u0 + (sub >> 2)];
         if (done && done[it.orb]) continue;  // uniform in the wave
         const OrbDesc &od = orb[it.orb];
-        const int n = AX == 2 ? od.nz : od.ny, he = (n + 1) >> 1, ho = n >> 1, ks = (he + 3) >> 2;
+        const int n = od.ny, he = (n + 1) >> 1, ho = n >> 1, ks = (he + 3) >> 2;
         const int M2 = od.nx * od.ny;
-        const int lines = AX == 2 ? M2 : od.nx * od.nz;
+        const int lines = od.nx * od.nz;
         const int l0 = it.tile * 64 + (sub & 3) * 16;
         if (l0 >= lines) continue;
         const int ln = min(l0 + c, lines - 1);
         const bool lok = l0 + c < lines;
-        const int stride = AX == 2 ? M2 : od.nx;
-        const long long base = od.off + (AX == 2 ? (long long)ln : (long long)(ln / od.nx) * M2 + ln % od.nx);
+        const int stride = od.nx;
+        const long long base = od.off + (long long)(ln / od.nx) * M2 + ln % od.nx;
         const double *p = in + base;
         double *q = out + base;
         dbl4 Ce[T], Co[T];
-        if (MODE == kFdmZ || MODE == kFdmYFwd) {
+        if (MODE == kFdmYFwd) {
             double fe[4 * T], fo[4 * T];
 #pragma unroll
             for (int s = 0; s < 4 * T; ++s) {
@@ -443,29 +463,6 @@ __global__ __launch_bounds__(kFdmThreads<T>) void k_fdm_col(const Item *units, c
             }
             continue;
         }
-        if (MODE == kFdmZ) {
-            // spectral position of the line: the fused passes leave [kx][ky],
-            // the one-axis passes [ky][kx]
-            const int inner = od.fd_fused ? od.ny : od.nx;
-            const int a = ln / inner, b = ln - a * inner;
-            const int kx = od.fd_fused ? a : b, ky = od.fd_fused ? b : a;
-            auto lam = [&](int d, int nd, int k) {
-                const int Ld = 16 * od.fd_n[d], hd = (nd + 1) >> 1;
-                return tab[od.fd_t[d] + 2 * Ld * Ld + (k < hd ? k : Ld + k - hd)];
-            };
-            const double lxy = lam(0, od.nx, kx) + lam(1, od.ny, ky);
-            const double h2 = od.h * od.h;
-            const int Lz = 16 * od.fd_n[2];
-            const double *lz = tab + od.fd_t[2] + 2 * Lz * Lz;
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int k = 16 * t + g + 4 * r;
-                    Ce[t][r] *= h2 / (lz[k] + lxy);
-                    Co[t][r] *= h2 / (lz[Lz + k] + lxy);
-                }
-        }
         // back to nodes, one 16-position tile at a time
 #pragma unroll
         for (int t = 0; t < T; ++t) {
@@ -473,8 +470,8 @@ __global__ __launch_bounds__(kFdmThreads<T>) void k_fdm_col(const Item *units, c
 #pragma unroll
             for (int s = 0; s < 4 * T; ++s) {
                 if (s >= 4 * (T - 1) && s >= ks) continue;
-                E = mfma(I(0, t, s), Ce[s >> 2][s & 3], E);
-                O = mfma(I(1, t, s), Co[s >> 2][s & 3], O);
+                E = mfma(F(0, t, s), Ce[s >> 2][s & 3], E);
+                O = mfma(F(1, t, s), Co[s >> 2][s & 3], O);
             }
             if (lok) {
 #pragma unroll
@@ -488,12 +485,187 @@ __global__ __launch_bounds__(kFdmThreads<T>) void k_fdm_col(const Item *units, c
     }
 }
 
+// 1 / x for normal x > 0: the hardware seed (about 2^-23) and one third-order
+// step, about 1 ulp
+__device__ __forceinline__ double rcp2(double x) {
+    const double y = __builtin_amdgcn_rcp(x), e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+// order of the reads and products of a step: kept as written
+#define FDM_ORDER() __builtin_amdgcn_sched_barrier(0)
+
+// z: transform, scale by h^2 / (lam_x + lam_y + lam_z), transform back, in
+// place; lines: in-plane points, 16 to a wave.  The next lines' loads are
+// issued between the two products, the matrix operands read a step ahead.
+// KS: k steps taken, 4 T or (half axes that leave the last half tile empty)
+// 4 T - 2.
+template <int T, int KS>
+__device__ __forceinline__ void fdm_z_lines(const Item *__restrict__ units, const FdmRange rg, const OrbDesc *__restrict__ orb, const int *__restrict__ done,
+                                            const double *__restrict__ tab, double *fsm, double *data) {
+    constexpr int L = 16 * T, S = kStr<T>, NT = kFdmThreads<T>, NW = NT / 64;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, c = lane & 15;
+    const int nsub = 4 * (rg.u1 - rg.u0);
+    // base indices of the operand reads, opaque in each iteration: the reads are
+    // not to be hoisted out of the loop into registers
+    int fb = g * S + c, ib = c * S + g, zb = 2 * L * S + g;
+    auto F = [&](int par, int t, int s) { return fsm[fb + par * L * S + 4 * s * S + 16 * t]; };
+    auto I = [&](int par, int t, int s) { return fsm[ib + par * L * S + 16 * t * S + 4 * s]; };
+    double fe[4 * T], fo[4 * T], la, lb;
+    auto find = [&](int sub) {
+        for (; sub < nsub; sub += NW) {
+            const Item it = units[rg.u0 + (sub >> 2)];
+            const int o = uni(it.orb);
+            if (uni(!(done && done[o]) && it.tile * 64 + (sub & 3) * 16 < orb[o].nx * orb[o].ny)) break;
+        }
+        return sub;
+    };
+    auto issue = [&](int sub) {
+        const Item it = units[rg.u0 + (sub >> 2)];
+        const OrbDesc *const od = orb + uni(it.orb);
+        const int l0 = uni(it.tile) * 64 + (sub & 3) * 16;
+        const int n = uni(od->nz), he = (n + 1) >> 1, nx = uni(od->nx), ny = uni(od->ny), M2 = nx * ny;
+        const int ln = min(l0 + c, M2 - 1), fused = uni(od->fd_fused);
+        const Rsrc r = make_rsrc(data + uni(od->off), (unsigned)(M2 * n) * 8u);
+        const unsigned v0 = (unsigned)(ln + g * M2), v1 = (unsigned)(ln + (3 - g) * M2);
+#pragma unroll
+        for (int s = 0; s < 4 * T; ++s) {
+            if (s < 4 * (T - 1)) {
+                fe[s] = bld<double>(r, v0, 4 * s * M2);
+                fo[s] = bld<double>(r, v1, (n - 4 - 4 * s) * M2);
+            } else {
+                const int j = min(4 * s + g, he - 1);
+                fe[s] = bld<double>(r, (unsigned)(ln + j * M2), 0);
+                fo[s] = bld<double>(r, (unsigned)(ln + (n - 1 - j) * M2), 0);
+            }
+        }
+        const int inner = fused ? ny : nx;
+        const int a = ln / inner, b = ln - a * inner;
+        auto lam = [&](int d, int nd, int k) {
+            const int Ld = 16 * uni(od->fd_n[d]), hd = (nd + 1) >> 1;
+            return tab[uni(od->fd_t[d]) + 2 * Ld * Ld + (k < hd ? k : Ld + k - hd)];
+        };
+        la = lam(0, nx, fused ? a : b);
+        lb = lam(1, ny, fused ? b : a);
+    };
+    int sub = find(w);
+    if (sub >= nsub) return;
+    issue(sub);
+    while (true) {
+        const Item it = units[rg.u0 + (sub >> 2)];
+        const OrbDesc *const od = orb + uni(it.orb);
+        const int l0 = uni(it.tile) * 64 + (sub & 3) * 16;
+        const int n = uni(od->nz), he = (n + 1) >> 1, ho = n >> 1, M2 = uni(od->nx) * uni(od->ny);
+        const double h2 = od->h * od->h;
+        const double lxy = la + lb;
+        asm volatile("" : "+v"(fb), "+v"(ib), "+v"(zb));
+#pragma unroll
+        for (int s = 0; s < 4 * T; ++s) {
+            // the centre node, in the last tile, enters once
+            const double a = fe[s], b = s >= 4 * (T - 1) && 2 * (4 * s + g) == n - 1 ? 0.0 : fo[s];
+            fe[s] = a + b;
+            fo[s] = a - b;
+        }
+        dbl4 Ce[T], Co[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) Ce[t] = Co[t] = dbl4{0.0, 0.0, 0.0, 0.0};
+        double m[2][2 * T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            m[0][t] = F(0, t, 0);
+            m[0][T + t] = F(1, t, 0);
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            if (s + 1 < KS) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    m[(s + 1) & 1][t] = F(0, t, s + 1);
+                    m[(s + 1) & 1][T + t] = F(1, t, s + 1);
+                }
+            }
+            FDM_ORDER();
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                Ce[t] = mfma(m[s & 1][t], fe[s], Ce[t]);
+                Co[t] = mfma(m[s & 1][T + t], fo[s], Co[t]);
+            }
+            FDM_ORDER();
+        }
+        const int nxt = find(sub + NW);
+        if (nxt < nsub) issue(nxt);
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                Ce[t][r] *= h2 * rcp2(fsm[zb + 16 * t + 4 * r] + lxy);
+                Co[t][r] *= h2 * rcp2(fsm[zb + L + 16 * t + 4 * r] + lxy);
+            }
+        const Rsrc r = make_rsrc(data + uni(od->off), (unsigned)(M2 * n) * 8u);
+        const bool lok = l0 + c < M2;
+        const unsigned v0 = lok ? (unsigned)(l0 + c + g * M2) : kDrop, v1 = lok ? (unsigned)(l0 + c + (3 - g) * M2) : kDrop;
+        double p[2][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) p[0][q] = I(q >> 1, 0, q & 1);
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            dbl4 E = {0.0, 0.0, 0.0, 0.0}, O = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < KS / 2; ++u) {
+                const int i = t * (KS / 2) + u, nt = (i + 1) / (KS / 2), nu = (i + 1) % (KS / 2);
+                if (nt < T) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) p[(i + 1) & 1][q] = I(q >> 1, nt, 2 * nu + (q & 1));
+                }
+                FDM_ORDER();
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int s = 2 * u + q;
+                    E = mfma(p[i & 1][q], Ce[s >> 2][s & 3], E);
+                    O = mfma(p[i & 1][2 + q], Co[s >> 2][s & 3], O);
+                }
+                FDM_ORDER();
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (t < T - 1) {
+                    bst(r, v0, (16 * t + 4 * q) * M2, E[q] + O[q]);
+                    bst(r, v1, (n - 4 - 16 * t - 4 * q) * M2, E[q] - O[q]);
+                } else {
+                    const int j = 16 * t + g + 4 * q;
+                    bst(r, lok && j < he ? (unsigned)(l0 + c + j * M2) : kDrop, 0, E[q] + O[q]);
+                    bst(r, lok && j < ho ? (unsigned)(l0 + c + (n - 1 - j) * M2) : kDrop, 0, E[q] - O[q]);
+                }
+            }
+        }
+        if (nxt >= nsub) break;
+        sub = nxt;
+    }
+}
+
+template <int T>
+__global__ __launch_bounds__(kFdmThreads<T>, 2) void k_fdm_z(const Item *__restrict__ units, const FdmRange *__restrict__ ranges,
+                                                           const OrbDesc *__restrict__ orb, const int *__restrict__ done, const double *__restrict__ tab,
+                                                           double *data) {
+    constexpr int L = 16 * T, S = kStr<T>, NT = kFdmThreads<T>;
+    extern __shared__ __attribute__((aligned(16))) double fsm[];
+    const FdmRange rg = ranges[blockIdx.x];
+    const OrbDesc &od = orb[units[rg.u0].orb];
+    load_table<T, true>(fsm, tab + od.fd_t[2], od.fd_n[2], NT);
+    for (int i = threadIdx.x; i < 2 * L; i += NT) fsm[2 * L * S + i] = tab[od.fd_t[2] + 2 * L * L + i];
+    __syncthreads();
+    // k steps of the half axis, up to a step of padding (one axis a block)
+    if ((od.nz + 1) / 2 > 16 * T - 8) fdm_z_lines<T, 4 * T>(units, rg, orb, done, tab, fsm, data);
+    else fdm_z_lines<T, 4 * T - 2>(units, rg, orb, done, tab, fsm, data);
+}
+
 // lines along x (contiguous), as rows of the A operand; lines (z, y)
-//   SQ (forward): b = scale src^2;  ACC (inverse): x += the result
-template <int T, int MODE, bool SQ, bool ACC>
-__global__ __launch_bounds__(kFdmThreads<T>) void k_fdm_row(const Item *units, const FdmRange *ranges,
-                                                             const OrbDesc *orb, const int *done,
-                                                             const double *tab, const double *in, double scale,
+//   SQ (forward): b = scale src^2
+template <int T, int MODE, bool SQ>
+__global__ __launch_bounds__(kFdmThreads<T>) void k_fdm_row(const Item *__restrict__ units, const FdmRange *__restrict__ ranges,
+                                                             const OrbDesc *__restrict__ orb, const int *__restrict__ done,
+                                                             const double *__restrict__ tab, const double *in, double scale,
                                                              double *out) {
     constexpr int L = 16 * T, S = kStr<T>, NT = kFdmThreads<T>, NW = NT / 64;
     extern __shared__ __attribute__((aligned(16))) double fsm[];
@@ -565,9 +737,6 @@ __global__ __launch_bounds__(kFdmThreads<T>) void k_fdm_row(const Item *units, c
                 if (MODE == kFdmXFwd) {
                     if (j < he) o[j] = E[r];
                     if (j < ho) o[he + j] = O[r];
-                } else if (ACC) {
-                    if (j < he) o[j] += E[r] + O[r];
-                    if (j < ho) o[n - 1 - j] += E[r] - O[r];
                 } else {
                     if (j < he) o[j] = E[r] + O[r];
                     if (j < ho) o[n - 1 - j] = E[r] - O[r];
@@ -591,6 +760,8 @@ size_t line_lds(int T) {
     const size_t L = 16 * (size_t)T, S = L + 2;
     return 2 * L * S * sizeof(double);
 }
+
+size_t z_lds(int T) { return line_lds(T) + 32 * (size_t)T * sizeof(double); }
 
 template <class K>
 hipError_t allow_lds(K k, size_t lds) {
@@ -616,9 +787,9 @@ bool fdm_xy_fits(int nx, int ny, size_t lds_limit) {
 
 int fdm_occupancy(int pass, int T, int two) {
 #define XY(TT) case TT: return std::min(occ_of(k_fdm_xy_fwd<TT, true>, 128 * TT, xy_lds(TT, two != 0)), \
-                                        occ_of(k_fdm_xy_inv<TT, false>, 128 * TT, xy_lds(TT, two != 0)));
-#define Z(TT) case TT: return occ_of(k_fdm_col<TT, kFdmZ>, kFdmThreads<TT>, line_lds(TT));
-#define XL(TT) case TT: return occ_of(k_fdm_row<TT, kFdmXFwd, true, false>, kFdmThreads<TT>, line_lds(TT));
+                                        occ_of(k_fdm_xy_inv<TT>, 128 * TT, xy_lds(TT, two != 0)));
+#define Z(TT) case TT: return occ_of(k_fdm_z<TT>, kFdmThreads<TT>, z_lds(TT));
+#define XL(TT) case TT: return occ_of(k_fdm_row<TT, kFdmXFwd, true>, kFdmThreads<TT>, line_lds(TT));
 #define YL(TT) case TT: return occ_of(k_fdm_col<TT, kFdmYFwd>, kFdmThreads<TT>, line_lds(TT));
     if (pass == kFdmPassXY) {
         switch (T) { XY(1) XY(2) XY(3) XY(4) }
@@ -650,18 +821,16 @@ hipError_t fdm_setup() {
 #define XY(TT)                                                                  \
     set(k_fdm_xy_fwd<TT, true>, std::min<size_t>(xy_lds(TT, true), 160 * 1024));  \
     set(k_fdm_xy_fwd<TT, false>, std::min<size_t>(xy_lds(TT, true), 160 * 1024)); \
-    set(k_fdm_xy_inv<TT, true>, std::min<size_t>(xy_lds(TT, true), 160 * 1024));  \
-    set(k_fdm_xy_inv<TT, false>, std::min<size_t>(xy_lds(TT, true), 160 * 1024));
+    set(k_fdm_xy_inv<TT>, std::min<size_t>(xy_lds(TT, true), 160 * 1024));
     XY(1) XY(2) XY(3) XY(4)
 #undef XY
 #define LN(TT)                                                 \
-    set(k_fdm_col<TT, kFdmZ>, line_lds(TT));             \
+    set(k_fdm_z<TT>, z_lds(TT));             \
     set(k_fdm_col<TT, kFdmYFwd>, line_lds(TT));          \
     set(k_fdm_col<TT, kFdmYInv>, line_lds(TT));          \
-    set(k_fdm_row<TT, kFdmXFwd, true, false>, line_lds(TT));    \
-    set(k_fdm_row<TT, kFdmXFwd, false, false>, line_lds(TT));   \
-    set(k_fdm_row<TT, kFdmXInv, false, true>, line_lds(TT));    \
-    set(k_fdm_row<TT, kFdmXInv, false, false>, line_lds(TT));
+    set(k_fdm_row<TT, kFdmXFwd, true>, line_lds(TT));    \
+    set(k_fdm_row<TT, kFdmXFwd, false>, line_lds(TT));   \
+    set(k_fdm_row<TT, kFdmXInv, false>, line_lds(TT));
     LN(1) LN(2) LN(3) LN(4) LN(5) LN(6)
 #undef LN
     if (e == hipSuccess) ready.insert(dev);
@@ -669,7 +838,7 @@ hipError_t fdm_setup() {
 }
 
 hipError_t launch_fdm(const FdmPlan &p, const OrbDesc *orb, const int *done, const double *tab, const double *src,
-                      int square, double scale, double *work, double *out, int accumulate, hipStream_t s) {
+                      int square, double scale, double *work, double *out, hipStream_t s) {
     const FdmClass *const cl = p.cls;
     auto each = [&](int pass, auto &&f) -> hipError_t {
         for (int i = 0; i < p.ncls; ++i) {
@@ -698,8 +867,8 @@ hipError_t launch_fdm(const FdmPlan &p, const OrbDesc *orb, const int *done, con
     e = each(pass, [&](const FdmClass &q) -> hipError_t {
 #define LN(TT)                                                                                                        \
     case TT:                                                                                                          \
-        if (square) GO((k_fdm_row<TT, kFdmXFwd, true, false>), kFdmThreads<TT>, line_lds(TT), src, scale, work);        \
-        else GO((k_fdm_row<TT, kFdmXFwd, false, false>), kFdmThreads<TT>, line_lds(TT), src, scale, work);              \
+        if (square) GO((k_fdm_row<TT, kFdmXFwd, true>), kFdmThreads<TT>, line_lds(TT), src, scale, work);        \
+        else GO((k_fdm_row<TT, kFdmXFwd, false>), kFdmThreads<TT>, line_lds(TT), src, scale, work);              \
         return hipSuccess;
         switch (q.T) { LN(1) LN(2) LN(3) LN(4) LN(5) LN(6) }
 #undef LN
@@ -717,10 +886,12 @@ hipError_t launch_fdm(const FdmPlan &p, const OrbDesc *orb, const int *done, con
     });
     if (e != hipSuccess) return e;
     pass = kFdmPassZ;
+#define ZZ(TT) case TT: GO((k_fdm_z<TT>), kFdmThreads<TT>, z_lds(TT), work); return hipSuccess;
     e = each(pass, [&](const FdmClass &q) -> hipError_t {
-        switch (q.T) { COL(1, kFdmZ) COL(2, kFdmZ) COL(3, kFdmZ) COL(4, kFdmZ) COL(5, kFdmZ) COL(6, kFdmZ) }
+        switch (q.T) { ZZ(1) ZZ(2) ZZ(3) ZZ(4) ZZ(5) ZZ(6) }
         return hipErrorInvalidValue;
     });
+#undef ZZ
     if (e != hipSuccess) return e;
     pass = kFdmPassY;
     e = each(pass, [&](const FdmClass &q) -> hipError_t {
@@ -733,8 +904,7 @@ hipError_t launch_fdm(const FdmPlan &p, const OrbDesc *orb, const int *done, con
     e = each(pass, [&](const FdmClass &q) -> hipError_t {
 #define LN(TT)                                                                                                         \
     case TT:                                                                                                           \
-        if (accumulate) GO((k_fdm_row<TT, kFdmXInv, false, true>), kFdmThreads<TT>, line_lds(TT), (const double *)work, 1.0, out); \
-        else GO((k_fdm_row<TT, kFdmXInv, false, false>), kFdmThreads<TT>, line_lds(TT), (const double *)work, 1.0, out);           \
+        GO((k_fdm_row<TT, kFdmXInv, false>), kFdmThreads<TT>, line_lds(TT), (const double *)work, 1.0, out);           \
         return hipSuccess;
         switch (q.T) { LN(1) LN(2) LN(3) LN(4) LN(5) LN(6) }
 #undef LN
@@ -745,8 +915,7 @@ hipError_t launch_fdm(const FdmPlan &p, const OrbDesc *orb, const int *done, con
     return each(pass, [&](const FdmClass &q) -> hipError_t {
 #define XY(TT)                                                                                                     \
     case TT:                                                                                                       \
-        if (accumulate) GO((k_fdm_xy_inv<TT, true>), 128 * TT, xy_lds(TT, q.two), q.two, (const double *)work, out); \
-        else GO((k_fdm_xy_inv<TT, false>), 128 * TT, xy_lds(TT, q.two), q.two, (const double *)work, out);           \
+        GO((k_fdm_xy_inv<TT>), 128 * TT, xy_lds(TT, q.two), q.two, (const double *)work, out);           \
         return hipSuccess;
         switch (q.T) { XY(1) XY(2) XY(3) XY(4) }
 #undef XY

@@ -191,11 +191,11 @@ hipError_t launch_reduce_partials(int norb, const OrbDesc *orb, const double *pa
 // fdm.hip: direct Poisson solver by fast diagonalisation (FP64)
 // ----------------------------------------------------------------------------
 
-// out (+)= K^{-1} b, b = scale src^2 (square) or src, for every orbital with
+// out = K^{-1} b, b = scale src^2 (square) or src, for every orbital with
 // done == 0 (done null: all).  work: one field array; src, work and out may
 // not overlap.
 hipError_t launch_fdm(const FdmPlan &p, const OrbDesc *orb, const int *done, const double *tab, const double *src,
-                      int square, double scale, double *work, double *out, int accumulate, hipStream_t s);
+                      int square, double scale, double *work, double *out, hipStream_t s);
 // LDS limits of the kernels on the current device (once per device)
 hipError_t fdm_setup();
 // whether the fused in-plane passes serve planes of nx x ny nodes

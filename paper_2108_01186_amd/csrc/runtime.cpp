@@ -1168,7 +1168,7 @@ fsic_status time_dst_layout(fsic_ctx *c, const std::vector<Group> &groups, int p
         // (b is overwritten: its values do not matter to the time)
         HIPCHK(c, hipMemsetAsync(c->B.p, 0, F * sizeof(double), s));
         auto solve = [&]() {
-            return launch_fdm(fdm_plan(c, b), c->d_orb.p, nullptr, c->d_ftab.p, c->B.p, 0, 1.0, c->R.p, c->B.p, 0, s);
+            return launch_fdm(fdm_plan(c, b), c->d_orb.p, nullptr, c->d_ftab.p, c->B.p, 0, 1.0, c->R.p, c->B.p, s);
         };
         hipError_t he = solve();
         if (he == hipSuccess) he = hipEventRecord(e0, s);
@@ -1434,7 +1434,7 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
     // one application, then the residual check (each captured on its own
     // under FSIC_GRAPHS)
     auto apply = [&](hipStream_t st) -> fsic_status {
-        HIPCHK(c, launch_fdm(plan, c->d_orb.p, nullptr, c->d_ftab.p, bsrc, sq, bscale, c->R.p, X, 0, st));
+        HIPCHK(c, launch_fdm(plan, c->d_orb.p, nullptr, c->d_ftab.p, bsrc, sq, bscale, c->R.p, X, st));
         return FSIC_OK;
     };
     // the residual of x, of the orbitals not in dn, written to r if not null
@@ -1481,7 +1481,7 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
         HIPCHK(c, c->Q.ensure(F));   // r
         HIPCHK(c, c->P0.ensure(F));  // d = K^{-1} r
         if (rounds == 1 && (st = residual(c->done.p, c->Q.p, s))) return st;
-        HIPCHK(c, launch_fdm(plan, c->d_orb.p, c->done.p, c->d_ftab.p, c->Q.p, 0, 1.0, c->R.p, c->P0.p, 0, s));
+        HIPCHK(c, launch_fdm(plan, c->d_orb.p, c->done.p, c->d_ftab.p, c->Q.p, 0, 1.0, c->R.p, c->P0.p, s));
         HIPCHK(c, launch_add_fields(nit8, c->d_items8.p, c->d_orb.p, c->done.p, X, c->P0.p, s));
         HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, c->done.p, c->P0.p, c->Q.p, 0,
                                     1.0, c->Q.p, c->partRU.p, b.tot7, s));
