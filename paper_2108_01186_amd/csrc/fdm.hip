@@ -35,7 +35,7 @@
 
 #include "fdm_basis.h"
 #include "kernels.h"
-#include "zmarch.h"
+#include "buffer.h"
 
 namespace fsic {
 
@@ -46,19 +46,6 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ dbl4 mfma(double a, double b, dbl4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
-
-// values that are the same in every lane, for scalar registers (the compiler
-// cannot know that of loads beside stores, and a buffer resource in vector
-// registers makes a loop of every access)
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ long long uni(long long v) {
-    return (long long)((unsigned long long)(unsigned)uni((int)(v >> 32)) << 32 | (unsigned)uni((int)v));
-}
-
-// element index of a store that is to be dropped: beyond every buffer.  Stores
-// are issued in any case, so that the number of stores behind a prefetch is
-// known and waiting for the one does not wait for the others
-constexpr unsigned kDrop = 0x1fffffffu;
 
 // LDS row stride of an axis matrix with 16 T columns: operand reads whose
 // row runs with c are free of bank conflicts, the others take two passes

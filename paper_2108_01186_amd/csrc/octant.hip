@@ -22,6 +22,7 @@
 #include <map>
 #include <mutex>
 
+#include "buffer.h"
 #include "kernels.h"
 #include "lsda.h"
 
@@ -301,19 +302,21 @@ __global__ __launch_bounds__(1024) void k_oct_final(const OctTile *tiles, int nt
 // orbital tiles paid two more barriers a tile.
 // ---------------------------------------------------------------------------
 template <int L, int MODE>
-__global__ __launch_bounds__(MODE == 2 ? 512 : 256, 2) void k_sic_octant(const OctItem *items, const OctGroup *groups,
-                                                        const ChanDesc *chans, int ntiles, const double *frag,
-                                                        const double *PHI, double *W, double floor, int want_v,
-                                                        double *partU, double *partX) {
+__global__ __launch_bounds__(MODE == 2 ? 512 : 256, 2) void k_sic_octant(
+    const OctItem *__restrict__ items, const OctGroup *__restrict__ groups, const ChanDesc *__restrict__ chans,
+    int ntiles, const double *__restrict__ frag, const double *__restrict__ PHI, double *W, double floor, int want_v,
+    double *partU, double *partX) {
     constexpr int KS = kSteps<L>, NB = (2 * KS * 4 * 16 + 255) / 256;
     constexpr bool LF = MODE != 0;
     constexpr int SUB = MODE == 2 ? 2 : 1, NT = 256 * SUB, NW = 4 * SUB;
     extern __shared__ __attribute__((aligned(16))) double osm[];
-    const OctItem it = items[blockIdx.x];
+    const OctItem *const ip = items + blockIdx.x;
+    const OctItem it{uni(ip->group), 0, uni(ip->t0), uni(ip->t1), uni(ip->slot)};
     const OctGroup *const gp = groups + it.group;
-    const int nx = gp->nx, ny = gp->ny, nz = gp->nz, nchan = gp->nchan, tile0 = gp->tile0[0];
-    const int nt0 = (chans[gp->chan0].N + 15) >> 4;
-    const int nt = nt0 + (nchan > 1 ? (chans[gp->chan0 + 1].N + 15) >> 4 : 0);  // fragment tiles of the group
+    const int nx = uni(gp->nx), ny = uni(gp->ny), nz = uni(gp->nz), nchan = uni(gp->nchan), tile0 = uni(gp->tile0[0]);
+    const int c0 = uni(gp->chan0);
+    const int nt0 = (uni(chans[c0].N) + 15) >> 4;
+    const int nt = nt0 + (nchan > 1 ? (uni(chans[c0 + 1].N) + 15) >> 4 : 0);  // fragment tiles of the group
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = w >> 2, t256 = tid & 255;
     double *const B = osm + sub * 2 * KS * 4 * 16;   // [2][4 KS][16]: U and H of these four waves' nodes
@@ -334,13 +337,15 @@ __global__ __launch_bounds__(MODE == 2 ? 512 : 256, 2) void k_sic_octant(const O
         int q = 0;
 #pragma unroll
         for (int cl = 0; cl < 8; ++cl)
-            if (e >= 4 * kCls<L>.ks[cl] && e < 4 * kCls<L>.ks[cl + 1]) q = kCls<L>.row[cl][e - 4 * kCls<L>.ks[cl]];
+#pragma unroll
+            for (int i = 0; i < 4 * (kCls<L>.ks[cl + 1] - kCls<L>.ks[cl]); ++i)
+                if (e == 4 * kCls<L>.ks[cl] + i) q = kCls<L>.row[cl][i];
         qrow[e] = (short)q;
     }
     const double *const U = gp->U, *const H = gp->H;
-    const ChanDesc &ch0 = chans[gp->chan0], &ch1 = chans[gp->chan0 + nchan - 1];
-    const int N0 = ch0.N, N1 = ch1.N;
-    const long long M = gp->M, off0 = ch0.off, off1 = ch1.off;
+    const ChanDesc &ch0 = chans[c0], &ch1 = chans[c0 + nchan - 1];
+    const int N0 = uni(ch0.N), N1 = uni(ch1.N);
+    const long long M = uni(gp->M), off0 = uni(ch0.off), off1 = uni(ch1.off);
     const double dV2 = 2.0 * ch0.h * ch0.h * ch0.h;
     // operand rows of the next nodes (16 rows a sweep, 16 nodes a row)
     double bn[NB];
@@ -405,7 +410,7 @@ __global__ __launch_bounds__(MODE == 2 ? 512 : 256, 2) void k_sic_octant(const O
         for (int e = 0; e < NB; ++e)
             if (t256 + 256 * e < 2 * KS * 4 * 16) B[t256 + 256 * e] = bn[e];
         lds_barrier();
-        if (t + SUB < it.t1) stage(t + SUB);
+        stage(min(t + SUB, it.t1 - 1));
         i0 = n0;
         i1 = n1;
         in = inn;
@@ -432,12 +437,10 @@ __global__ __launch_bounds__(MODE == 2 ? 512 : 256, 2) void k_sic_octant(const O
                 lds_barrier();
                 pieces(tl + 1 < nt ? tl + 1 : 0);
             }
-            if (tl + 1 < nt) {
-                fields(tl + 1);
-            } else if (t + SUB < it.t1) {
-                place(t + SUB);
-                fields(0);
-            }
+            // unconditional (past the last nodes: some nodes again): a load in a
+            // branch ends in a copy, and a wait, where the branches meet
+            if (tl + 1 == nt) place(t + SUB);
+            fields(tl + 1 < nt ? tl + 1 : 0);
             // x-even (a[0]) and x-odd (a[1]) sums on this wave's side
             dbl4 aU[2], aH[2];
 #pragma unroll
@@ -504,7 +507,7 @@ __global__ __launch_bounds__(MODE == 2 ? 512 : 256, 2) void k_sic_octant(const O
     __syncthreads();
     int tl = 0;
     for (int cc = 0; cc < nchan; ++cc) {
-        const ChanDesc &ch = chans[gp->chan0 + cc];
+        const ChanDesc &ch = chans[c0 + cc];
         const int N = ch.N, q = 16 * nt;
         for (int e = tid; e < N; e += NT) {
             const size_t p = (size_t)(ch.blk_base + it.slot) * kMaxOrb + e;

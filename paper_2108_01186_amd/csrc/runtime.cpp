@@ -2407,7 +2407,9 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     Batch b;
     // zero-boundary solves plus the boundary basis when a backward pass will
     // need the zero-boundary (adjoint) solutions anyway
-    const bool use_basis = (o.flags & FSIC_KEEP_TAPE) && !(o.flags & (FSIC_EQ9_FORCES | FSIC_DIRECT_BC));
+    // (the octant kernel addresses four orbitals with 32 bits)
+    const bool use_basis = (o.flags & FSIC_KEEP_TAPE) && !(o.flags & (FSIC_EQ9_FORCES | FSIC_DIRECT_BC)) &&
+                           std::all_of(chans.begin(), chans.end(), [](const Chan &ch) { return ch.M < (1LL << 27); });
     std::vector<const double *> basisU(nchan, nullptr);
     c->basis_solves = 0;
     c->basis_ms = 0.0;

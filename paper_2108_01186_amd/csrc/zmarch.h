@@ -20,6 +20,7 @@
 
 #include <type_traits>
 
+#include "buffer.h"
 #include "kernels.h"
 
 namespace fsic {
@@ -27,28 +28,6 @@ namespace fsic {
 // ---------------------------------------------------------------------------
 // z-marching stencil driver
 // ---------------------------------------------------------------------------
-
-// Raw buffer access: a uniform resource (base, size) plus a 32-bit vector
-// byte offset and a 32-bit scalar byte offset, so no per-lane 64-bit address
-// arithmetic is needed.  Every access here is in range by construction.
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-__device__ __forceinline__ Rsrc make_rsrc(const void *base, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00020000);
-}
-template <class X> __device__ __forceinline__ X bld(Rsrc r, unsigned vidx, int sidx);
-template <> __device__ __forceinline__ float bld<float>(Rsrc r, unsigned vidx, int sidx) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vidx * 4u, sidx * 4, 0));
-}
-template <> __device__ __forceinline__ double bld<double>(Rsrc r, unsigned vidx, int sidx) {
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, vidx * 8u, sidx * 8, 0));
-}
-__device__ __forceinline__ void bst(Rsrc r, unsigned vidx, int sidx, float v) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, vidx * 4u, sidx * 4, 0);
-}
-__device__ __forceinline__ void bst(Rsrc r, unsigned vidx, int sidx, double v) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, vidx * 8u, sidx * 8, 0);
-}
 
 // calls f(integral_constant<int, U>, arg) for U = 0..N-1 (forced unrolling)
 template <int N, int U = 0>
