@@ -26,41 +26,63 @@ __device__ __forceinline__ int gram_slot(int i, int j, int nh) {
 // per-tile partial sums of F^T F and F^T f.
 //   hist: f_k - f_{k-1} goes into slot (k-1) % m (needs k >= 1);
 //   fprev := f_k.
+// Bound by memory latency unless a thread has many bytes under way: four
+// consecutive nodes a step in 16-byte loads, none of them in a branch (15
+// orbitals of 64^3, seven columns: 67 -> 38 us against one node a step).  Fields that
+// are no multiple of four nodes take them one by one.
+template <int VN>
+__device__ __forceinline__ void aar_dots_tile(const AarBufs &a, const OrbDesc &od, int tile, int k, int nh, int hist,
+                                              int dots, double (&acc)[kAarD]) {
+    typedef float VF __attribute__((ext_vector_type(VN)));
+    const long long M = (long long)od.nx * od.ny * od.nz;
+    const int hs = (k + a.m - 1) % a.m;
+#pragma unroll 1
+    for (int e = 0; e < kPW / (256 * VN); ++e) {
+        const long long i = (long long)tile * kPW + (long long)(e * 256 + threadIdx.x) * VN;
+        const bool in = i < M;
+        const long long g = od.off + (in ? i : M - VN);
+        const VF f = *reinterpret_cast<const VF *>(a.F + g);
+        const VF fp = *reinterpret_cast<const VF *>(a.Fprev + g);
+        VF col[kAarM];
+        if (dots) {
+#pragma unroll
+            for (int j = 0; j < kAarM; ++j)
+                col[j] = *reinterpret_cast<const VF *>(a.Fh + (size_t)min(j, nh - 1) * a.fields + g);
+        }
+        const VF d = f - fp;
+        if (hist && in) {
+            *reinterpret_cast<VF *>(a.Fh + (size_t)hs * a.fields + g) = d;
+            *reinterpret_cast<VF *>(a.Fprev + g) = f;
+        }
+        if (dots) {
+#pragma unroll
+            for (int v = 0; v < VN; ++v) {
+                double c[kAarM];
+#pragma unroll
+                for (int j = 0; j < kAarM; ++j)
+                    c[j] = in && j < nh ? (double)(hist && j == hs ? d[v] : col[j][v]) : 0.0;
+#pragma unroll
+                for (int ii = 0; ii < kAarM; ++ii)
+#pragma unroll
+                    for (int jj = ii; jj < kAarM; ++jj) acc[gram_slot(ii, jj, kAarM)] += c[ii] * c[jj];
+#pragma unroll
+                for (int ii = 0; ii < kAarM; ++ii) acc[kAarG + ii] += c[ii] * (in ? (double)f[v] : 0.0);
+            }
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void k_aar_dots(AarBufs a, int k, int nh, int hist, int dots) {
     __shared__ double swave[4][kAarD];
     const Item it = a.items8[blockIdx.x];
     if (it.orb < 0) return;
     if (a.done[it.orb] == 1) return;
     const OrbDesc od = a.orb[it.orb];
-    const long long M = (long long)od.nx * od.ny * od.nz;
-    const long long base = (long long)it.tile * kPW;
-    const int hs = (k + a.m - 1) % a.m;
     double acc[kAarD];
 #pragma unroll
     for (int q = 0; q < kAarD; ++q) acc[q] = 0.0;
-    for (int e = 0; e < kPW / 256; ++e) {
-        const long long i = base + e * 256 + threadIdx.x;
-        if (i >= M) continue;
-        const long long g = od.off + i;
-        const float f = a.F[g];
-        if (hist) {
-            a.Fh[(size_t)hs * a.fields + g] = f - a.Fprev[g];
-            a.Fprev[g] = f;
-        }
-        if (dots) {
-            float col[kAarM];
-#pragma unroll
-            for (int j = 0; j < kAarM; ++j) col[j] = (j < nh) ? a.Fh[(size_t)j * a.fields + g] : 0.f;
-#pragma unroll
-            for (int ii = 0; ii < kAarM; ++ii)
-#pragma unroll
-                for (int jj = ii; jj < kAarM; ++jj)
-                    if (jj < nh) acc[gram_slot(ii, jj, kAarM)] += (double)col[ii] * (double)col[jj];
-#pragma unroll
-            for (int ii = 0; ii < kAarM; ++ii)
-                if (ii < nh) acc[kAarG + ii] += (double)col[ii] * (double)f;
-        }
-    }
+    if (((od.off | a.fields | ((long long)od.nx * od.ny * od.nz)) & 3) == 0) aar_dots_tile<4>(a, od, it.tile, k, nh, hist, dots, acc);
+    else aar_dots_tile<1>(a, od, it.tile, k, nh, hist, dots, acc);
     if (!dots) return;
     // every accumulator index is a compile-time constant (a runtime index
     // would put the array in scratch memory): wave sums into LDS, one
@@ -81,52 +103,67 @@ __global__ __launch_bounds__(256) void k_aar_dots(AarBufs a, int k, int nh, int 
 // Per orbital: sum the tile partials (fixed order) and solve the nh x nh
 // normal equations for gamma by Gaussian elimination with partial pivoting;
 // a tiny multiple of the largest diagonal entry is added to the diagonal so
-// nearly dependent history columns give a bounded gamma.
+// nearly dependent history columns give a bounded gamma.  A chain of
+// latencies: all entries are summed at once, a wave per run of tiles, and
+// the matrix is eliminated in the registers of one wave, entry (r, j) in lane
+// 8 r + j (15 orbitals of 64^3: 44 -> below 9 us against a reduction per entry
+// and one thread with the matrix in memory).
 __global__ __launch_bounds__(256) void k_aar_solve(AarBufs a, int nh) {
-    __shared__ double sred[4];
+    static_assert(kAarD <= 64 && kAarM < 8, "lanes of a run, columns of a row");
+    __shared__ double run[4][64];
     __shared__ double d[kAarD];
     const int o = blockIdx.x;
     if (a.done[o] == 1) return;
     const OrbDesc od = a.orb[o];
-    for (int q = 0; q < kAarD; ++q) {
-        double s = 0.0;
-        for (int t = threadIdx.x; t < od.nt8; t += 256) s += a.partD[(size_t)(od.base8 + t) * kAarD + q];
-        s = block_sum256(s, sred);
-        if (threadIdx.x == 0) d[q] = s;
-    }
+    const int q = threadIdx.x & 63, rn = threadIdx.x >> 6;
+    double s = 0.0;
+    if (q < kAarD)
+#pragma unroll 8
+        for (int t = rn; t < od.nt8; t += 4) s += a.partD[(size_t)(od.base8 + t) * kAarD + q];
+    run[rn][q] = s;
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    double G[kAarM][kAarM + 1];
-    double dmax = 0.0;
-    for (int i = 0; i < nh; ++i) {
-        for (int j = i; j < nh; ++j) G[i][j] = G[j][i] = d[gram_slot(i, j, kAarM)];
-        G[i][nh] = d[kAarG + i];
-        dmax = fmax(dmax, G[i][i]);
+    if (threadIdx.x < kAarD)
+        d[q] = (run[0][q] + run[1][q]) + (run[2][q] + run[3][q]);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int r = threadIdx.x >> 3, j = threadIdx.x & 7;
+    double v = 0.0, dmax = 0.0;
+    for (int i = 0; i < nh; ++i) dmax = fmax(dmax, d[gram_slot(i, i, kAarM)]);
+    if (r < nh && j < nh) {
+        v = d[gram_slot(min(r, j), max(r, j), kAarM)];
+        if (r == j) v += 1e-13 * dmax;
+    } else if (r < nh && j == nh) {
+        v = d[kAarG + r];
     }
-    for (int i = 0; i < nh; ++i) G[i][i] += 1e-13 * dmax;
     for (int col = 0; col < nh; ++col) {
         int piv = col;
-        for (int r = col + 1; r < nh; ++r)
-            if (fabs(G[r][col]) > fabs(G[piv][col])) piv = r;
-        if (piv != col)
-            for (int j = 0; j <= nh; ++j) {
-                const double tmp = G[col][j];
-                G[col][j] = G[piv][j];
-                G[piv][j] = tmp;
+        double best = fabs(__shfl(v, 9 * col));
+        for (int i = col + 1; i < nh; ++i) {
+            const double x = fabs(__shfl(v, 8 * i + col));
+            if (x > best) {
+                best = x;
+                piv = i;
             }
-        const double pv = G[col][col];
-        for (int r = col + 1; r < nh; ++r) {
-            const double fct = (pv != 0.0) ? G[r][col] / pv : 0.0;
-            for (int j = col; j <= nh; ++j) G[r][j] -= fct * G[col][j];
         }
+        v = __shfl(v, 8 * (r == col ? piv : r == piv ? col : r) + j);
+        const double pv = __shfl(v, 9 * col), lead = __shfl(v, 8 * r + col), top = __shfl(v, 8 * col + j);
+        const double fct = pv != 0.0 ? lead / pv : 0.0;
+        if (r > col && j >= col) v -= fct * top;
     }
     double gam[kAarM];
-    for (int i = nh - 1; i >= 0; --i) {
-        double s = G[i][nh];
-        for (int j = i + 1; j < nh; ++j) s -= G[i][j] * gam[j];
-        gam[i] = (G[i][i] != 0.0) ? s / G[i][i] : 0.0;
+#pragma unroll
+    for (int i = kAarM - 1; i >= 0; --i) {
+        double t = __shfl(v, 8 * i + nh);
+#pragma unroll
+        for (int c = i + 1; c < kAarM; ++c)
+            if (c < nh) t -= __shfl(v, 8 * i + c) * gam[c];
+        const double p = __shfl(v, 9 * i);
+        gam[i] = i < nh && p != 0.0 ? t / p : 0.0;
     }
-    for (int i = 0; i < kAarM; ++i) a.gamma[(size_t)o * kAarM + i] = (i < nh && isfinite(gam[i])) ? gam[i] : 0.0;
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int i = 0; i < kAarM; ++i)
+            a.gamma[(size_t)o * kAarM + i] = isfinite(gam[i]) ? gam[i] : 0.0;
 }
 
 // The step: Richardson (omega f) or Anderson (beta f - sum_j gamma_j (X_j +
