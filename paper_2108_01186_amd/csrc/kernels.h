@@ -402,9 +402,21 @@ struct FodCell {
 };
 
 // u[i][a] = psi_a(a_i), du[i][a][3]; rhoa[i]; T[i][a]; sets status on vacuum
-hipError_t launch_interp(int K, int N, int nx, int ny, int nz, double h, const double *psi,
-                         const FodCell *cells, double floor, double *u, double *du,
-                         double *rhoa, double *T, int *status, bool fd_gradient, hipStream_t s);
+// (K query points of one channel each: K = N for the FODs)
+struct InterpChan {
+    int K, N, nx, ny, nz;
+    int block0;  // set by the launcher
+    double h;
+    const double *psi;
+    const FodCell *cells;
+    double *u, *du, *rhoa, *T;
+};
+constexpr int kInterpBatch = 24;
+struct InterpBatch {
+    int n;
+    InterpChan c[kInterpBatch];
+};
+hipError_t launch_interp(const InterpChan *chans, int n, double floor, int *status, bool fd_gradient, hipStream_t s);
 
 // ----------------------------------------------------------------------------
 // products.hip: tall-skinny products over the grid, all channels of a batch

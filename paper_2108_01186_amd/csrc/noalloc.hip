@@ -90,9 +90,9 @@ hipError_t noalloc_flo(int N, const int n[3], double h, const double *psi, const
         hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, status);
         e = hipGetLastError();
     }
+    const InterpChan ic{N, N, n[0], n[1], n[2], 0, h, psi, dcells, small + oU, small + oDU, small + oRHOA, small + oT};
     if (e == hipSuccess)
-        e = launch_interp(N, N, n[0], n[1], n[2], h, psi, dcells, rho_floor, small + oU, small + oDU,
-                          small + oRHOA, small + oT, status, false, s);
+        e = launch_interp(&ic, 1, rho_floor, status, false, s);
     ProdChan pc{};
     pc.N = N;
     pc.M = M;

@@ -2407,9 +2407,7 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     Batch b;
     // zero-boundary solves plus the boundary basis when a backward pass will
     // need the zero-boundary (adjoint) solutions anyway
-    // (the octant kernel addresses four orbitals with 32 bits)
-    const bool use_basis = (o.flags & FSIC_KEEP_TAPE) && !(o.flags & (FSIC_EQ9_FORCES | FSIC_DIRECT_BC)) &&
-                           std::all_of(chans.begin(), chans.end(), [](const Chan &ch) { return ch.M < (1LL << 27); });
+    const bool use_basis = (o.flags & FSIC_KEEP_TAPE) && !(o.flags & (FSIC_EQ9_FORCES | FSIC_DIRECT_BC));
     std::vector<const double *> basisU(nchan, nullptr);
     c->basis_solves = 0;
     c->basis_ms = 0.0;
@@ -2505,13 +2503,12 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     // ---- (a) Fermi orbitals, (b) Loewdin: per channel ----
     int cell_base = 0;
     std::vector<ProdChan> prod(nchan);
+    std::vector<InterpChan> interp(nchan);
     for (int ci = 0; ci < nchan; ++ci) {
         const Chan &ch = chans[ci];
         double *sm = c->small.p + ch.so;
-        HIPCHK(c, launch_interp(ch.N, ch.N, ch.n[0], ch.n[1], ch.n[2], ch.h, ch.psi, c->d_cells.p + cell_base,
-                                o.rho_floor, sm + small_off(sU_), sm + small_off(sDU),
-                                sm + small_off(sRHOA), sm + small_off(sT), c->status.p,
-                                (o.flags & FSIC_PAPER_GRADIENT) != 0, s));
+        interp[ci] = InterpChan{ch.N, ch.N, ch.n[0], ch.n[1], ch.n[2], 0, ch.h, ch.psi, c->d_cells.p + cell_base,
+                                sm + small_off(sU_), sm + small_off(sDU), sm + small_off(sRHOA), sm + small_off(sT)};
         ProdChan &pc = prod[ci];
         pc.N = ch.N;
         pc.M = ch.M;
@@ -2520,6 +2517,7 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
         pc.scale = ch.h * ch.h * ch.h;
         cell_base += ch.N;
     }
+    HIPCHK(c, launch_interp(interp.data(), nchan, o.rho_floor, c->status.p, (o.flags & FSIC_PAPER_GRADIENT) != 0, s));
     HIPCHK(c, launch_gram(prod.data(), nchan, c->partG.p, c->partG.cap, s));
     // Loewdin steps of all channels, kLowdinBatch per launch (one workgroup each)
     const LowdinOffsets loff{(long long)small_off(sT), (long long)small_off(sG), (long long)small_off(sS),
@@ -2945,8 +2943,8 @@ fsic_status fsic_op_interp(const fsic_grid *grid, int32_t N, int32_t K, const do
     if (rhoa.ensure(K) || T.ensure((size_t)K * N) || dc.ensure(K) || status.ensure(1)) return FSIC_ENOMEM;
     hipError_t e = hipMemcpyAsync(dc.p, cells.data(), K * sizeof(FodCell), hipMemcpyHostToDevice, s);
     if (!e) e = hipMemsetAsync(status.p, 0, sizeof(int), s);
-    if (!e) e = launch_interp(K, N, grid->n[0], grid->n[1], grid->n[2], grid->h, psi, dc.p, -1.0, u, du,
-                              rhoa.p, T.p, status.p, fd_gradient != 0, s);
+    const InterpChan ic{K, N, grid->n[0], grid->n[1], grid->n[2], 0, grid->h, psi, dc.p, u, du, rhoa.p, T.p};
+    if (!e) e = launch_interp(&ic, 1, -1.0, status.p, fd_gradient != 0, s);
     hipError_t e2 = hipStreamSynchronize(s);
     rhoa.release(); T.release(); dc.release(); status.release();
     return (e || e2) ? FSIC_EHIP : FSIC_OK;
@@ -3018,9 +3016,9 @@ fsic_status fsic_op_flo(const fsic_grid *grid, int32_t N, const double *psi, con
     hipError_t e = hipMemcpyAsync(dc.p, cells.data(), N * sizeof(FodCell), hipMemcpyHostToDevice, s);
     if (!e) e = hipMemsetAsync(status.p, 0, sizeof(int), s);
     double *b = sm.p;
-    if (!e) e = launch_interp(N, N, grid->n[0], grid->n[1], grid->n[2], grid->h, psi, dc.p, rho_floor,
-                              b + small_off(sU_), b + small_off(sDU), b + small_off(sRHOA),
-                              b + small_off(sT), status.p, false, s);
+    const InterpChan ic{N, N, grid->n[0], grid->n[1], grid->n[2], 0, grid->h, psi, dc.p, b + small_off(sU_),
+                        b + small_off(sDU), b + small_off(sRHOA), b + small_off(sT)};
+    if (!e) e = launch_interp(&ic, 1, rho_floor, status.p, false, s);
     ProdChan pc{};
     pc.N = N;
     pc.M = M;
