@@ -5,14 +5,15 @@ Loewdin, the Poisson problems of every FLO density (with its multipole
 boundary values: the Hartree potential), LSDA, Slater-averaged V_SIC and
 E_SIC (forward), then the FOD gradient (the adjoint Poisson problem of every
 orbital, with zero boundary values, and reverse mode through Loewdin and the
-interpolation).  The library solves the zero-boundary problems by CG in the
-forward pass and forms the multipole-boundary solutions from them and a
-per-grid basis of unit-moment boundary solutions (solved once per grid, in
-the warm-up); so a step answers 2 N Poisson problems with N CG solves.  The
-headline value is orbital Poisson problems answered per second of the
-mixed-precision path (FP32 CG sweeps recovered to the FP64 tolerance); CG
-solves per second and the step time are reported beside it, and the plain
-FP64 path is timed on the same inputs.
+interpolation).  The library solves the zero-boundary problems in the
+forward pass, directly and checked on their FP64 residual, and forms the
+multipole-boundary solutions from them and a per-grid basis of unit-moment
+boundary solutions (solved once per grid, in the warm-up); so a step answers
+2 N Poisson problems with N solves.  The headline value is orbital Poisson
+problems answered per second of the mixed-precision setting, whose direct
+solver is FP64 throughout (--solver cg: FP32 CG sweeps recovered to the FP64
+tolerance); solves per second and the step time are reported beside it, and
+the FP64 setting is timed on the same inputs.
 
 Prints ONE JSON line.  Usage: python bench.py [--gpus 1] [--steps K] [--warmup W]
 """
@@ -28,7 +29,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
-BF16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix
+FP64_MFMA_PEAK_TFLOPS = 78.6  # MI355X FP64 matrix
 
 
 def parse():
@@ -41,7 +42,7 @@ def parse():
                     help="relative FP64 residual of every solve (1e-11 keeps E_SIC within 1e-8 Ha "
                          "on every workload here)")
     ap.add_argument("--solver", default="pcg", choices=["pcg", "cg"],
-                    help="pcg: CG with the sine-transform preconditioner; cg: plain CG")
+                    help="pcg: the direct solver (axes up to 192 nodes); cg: plain CG")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-fp64", action="store_true")
     ap.add_argument("--no-graphs", action="store_true",
@@ -174,7 +175,7 @@ def single_thread_small_case():
             "seconds": d["seconds"], "threads": d["threads"], "E_SIC": d["E_SIC"]}
 
 
-KERNEL_SOURCES = ("zmarch.h", "stencil_pcg.hip", "stencil_res.hip", "dst.hip", "common.h")
+KERNEL_SOURCES = ("zmarch.h", "buffer.h", "fdm.hip", "stencil_cg.hip", "stencil_res.hip", "dst.hip", "common.h")
 
 
 def kernel_source_hash():
@@ -240,31 +241,27 @@ def kernel_rates(agg):
 
 
 KERNEL_NAMES = {
-    "sweep": "k_zmarch<PolPQ> (CG stencil sweep: q = -L p, p.q)",
-    "update": "k_pcg_rupd (r -= alpha q)",
-    "precond": "k_dst_xy + k_dst_fast(z) + k_dst_xy<PO> (sine-transform preconditioner, split-bf16 MFMA; its last pass writes p = z + beta p_old; five per-axis passes where a plane does not fit in LDS)",
-    "resid": "k_zmarch<PolResP> (FP64 residual b + L x closing a restart cycle, x = x64 + alpha_a p_a + alpha_b p_b)",
+    "sweep": "k_zmarch<PolCG> (CG stencil sweep: q = -L p; p.q, r.q, q.q)",
+    "update": "k_cg_update (x += alpha p, r -= alpha q, p = r + beta p)",
+    "precond": "k_fdm_xy_fwd + k_fdm_z + k_fdm_xy_inv (direct solution by fast diagonalisation, FP64 MFMA; five one-axis passes where a plane does not fit in LDS)",
+    "resid": "k_zmarch<PolRes64> (FP64 residual b + L x, b formed from the orbital)",
 }
 
 
 def roofline(args, agg):
-    """Roofline line for the dominant kernel.  Every timed kernel (sweep,
-    update and, with the preconditioned solver, the preconditioner) runs once
-    per iteration of every active orbital, so the one with the longest
-    average launch takes the most time (the sampled launch counts differ:
-    the first launch of a solve or restart is never sampled).  The
-    preconditioner is bound by HBM; its matrix-core use is shown beside."""
+    """Roofline line for the dominant of the timed parts of a solve: the
+    direct solver's transform passes (one application each) and its residual
+    pass, or a plain CG sweep and update.  The transforms move 48 B per node
+    in the fused form and do 2 (nx + ny + nz) FP64 flops; the two roofs are
+    level at 96^3, so the matrix-core use is shown beside the bandwidth."""
     rates = kernel_rates(agg)
     dom = max(rates, key=lambda k: rates[k]["avg_launch_us"])
     r = rates[dom]
     out = {"bound": "hbm", "kernel": KERNEL_NAMES[dom], "achieved": r["gbs"], "peak": HBM_PEAK_GBS,
            "unit": "GB/s", "frac": r["gbs"] / HBM_PEAK_GBS}
     if dom == "precond" and "tflops" in r:
-        # the split-bf16 transforms issue three bf16 products per fp32 multiply-add:
-        # about 3 x 1152 / 44 = 78 flop/B at 96^3, under the bf16 ridge of
-        # 2500 / 8 = 312 flop/B, so HBM is the roof; matrix-core use is shown beside
-        out["mfma_bf16_tflops"] = 3.0 * r["tflops"]
-        out["mfma_bf16_frac"] = 3.0 * r["tflops"] / BF16_MFMA_PEAK_TFLOPS
+        out["mfma_fp64_tflops"] = r["tflops"]
+        out["mfma_fp64_frac"] = r["tflops"] / FP64_MFMA_PEAK_TFLOPS
     # measured HBM bytes over algorithmic bytes of a full launch, applied to
     # this run's sampled launches (the same per launch as `achieved`)
     st = stored_traffic(args.workload, dom, args.solver)
@@ -281,7 +278,7 @@ def roofline(args, agg):
 
 def workload_config(args, systems, solves_per_step):
     common = {"fd_order": 12, "lmax": 6, "tol": args.tol, "solves_per_step": solves_per_step,
-              "solver": {"pcg": "CG preconditioned by type-I sine transforms",
+              "solver": {"pcg": "direct (fast diagonalisation, FP64) with residual check",
                          "cg": "plain CG"}[args.solver]}
     if len(systems) == 1:
         s = systems[0]
@@ -339,7 +336,7 @@ def main():
               file=sys.stderr, flush=True)
 
     # beside the profiled legs: the mixed leg without events, eager and with
-    # each chunk of CG iterations replayed as a captured HIP graph
+    # the solver's launches replayed as captured HIP graphs
     extra = {}
     if not args.no_graphs:
         for name, fl in (("mixed_unprofiled_solves_per_s", F.FSIC_WANT_VSIC | F.FSIC_KEEP_TAPE),
@@ -353,7 +350,7 @@ def main():
             extra[name] = agg["solves"] / dt
 
     # beside them: the same steps with the alternating Anderson-Richardson
-    # solver (FP64, same preconditioner, unprofiled)
+    # solver (FP64, sine-transform preconditioner, unprofiled)
     if not args.no_aar:
         ctx = F.Context(precision="fp64", tol=args.tol, flags=F.FSIC_WANT_VSIC | F.FSIC_KEEP_TAPE,
                         solver="aar")
@@ -385,7 +382,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32+f64",
+        "dtype": "f64" if args.solver == "pcg" else "f32+f64",
         "data": "synthetic",
         "config": workload_config(args, systems, solves_per_step),
         "e_sic_force_ms_mixed": mx["dt"] / steps * 1e3,

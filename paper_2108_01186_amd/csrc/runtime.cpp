@@ -1443,14 +1443,14 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
                                     c->partRU.p, b.tot7, st));
         return FSIC_OK;
     };
-    auto judge = [&](int round, hipStream_t st) -> fsic_status {
+    auto decide = [&](int round, hipStream_t st) -> fsic_status {
         HIPCHK(c, launch_direct_check(norb, c->d_orb.p, c->partRU.p, sq ? c->partRU.p + b.tot7 : c->part8.p, sq, tol2,
                                       round, c->done.p, c->bb.p, c->d_stage.p, st));
         return FSIC_OK;
     };
     auto check = [&](hipStream_t st) -> fsic_status {
         const fsic_status rs = residual(nullptr, nullptr, st);
-        return rs ? rs : judge(1, st);
+        return rs ? rs : decide(1, st);
     };
     auto timed = [&](int kind, int v, auto &body) -> fsic_status {
         if (prof) {
@@ -1485,13 +1485,13 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
         HIPCHK(c, launch_add_fields(nit8, c->d_items8.p, c->d_orb.p, c->done.p, X, c->P0.p, s));
         HIPCHK(c, launch_residual64(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, c->done.p, c->P0.p, c->Q.p, 0,
                                     1.0, c->Q.p, c->partRU.p, b.tot7, s));
-        if ((st = judge(rounds + 1, s)) || (st = count())) return st;
+        if ((st = decide(rounds + 1, s)) || (st = count())) return st;
     }
     if (!all && !status_error(c)) return FSIC_OK;
     all = true;
     if (mixed) rep.refinements += rounds;
     if (rounds > 1) {  // the residual that is reported is that of x, not of the recursion
-        if ((st = residual(nullptr, nullptr, s)) || (st = judge(0, s)) || (st = copy_stage(c, norb))) return st;
+        if ((st = residual(nullptr, nullptr, s)) || (st = decide(0, s)) || (st = copy_stage(c, norb))) return st;
     }
     c->pend_prof = prof;
     c->pend_aar = false;
