@@ -65,45 +65,10 @@ __global__ __launch_bounds__(256, 2) void k_nt(ProdBatch prod, double *part) {
     for (int i = 0; i < T; ++i)
 #pragma unroll
         for (int j = 0; j < T; ++j) acc[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
-    auto load = [&](const double *F, int t0, long long grp, double (&f)[T][4]) {
-        const long long m = 16 * grp + 4 * g;
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int r = 16 * (t0 + t) + c;
-            const double *p = F + (long long)r * M + m;
-            if (r < N && m + 4 <= M) {
-                const dbl2u lo = *reinterpret_cast<const dbl2u *>(p), hi = *reinterpret_cast<const dbl2u *>(p + 2);
-                f[t][0] = lo.x;
-                f[t][1] = lo.y;
-                f[t][2] = hi.x;
-                f[t][3] = hi.y;
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) f[t][j] = r < N && m + j < M ? p[j] : 0.0;
-            }
-        }
-    };
     const double *const Y = SYM ? ch.X : ch.Y;
-    double x[T][4], y[T][4], xn[T][4], yn[T][4];
     const int step = GW == 2 ? 1 : 4;
-    long long q = g0 + (GW == 2 ? 0 : w);
     const bool idle = SYM && GW == 2 && wi > wj;
-    if (q < g1 && !idle) {
-        load(ch.X, T * wi, q, xn);
-        if (!same) load(Y, T * wj, q, yn);
-    }
-    for (; q < g1 && !idle; q += step) {
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                x[t][j] = xn[t][j];
-                y[t][j] = same ? xn[t][j] : yn[t][j];
-            }
-        if (q + step < g1) {
-            load(ch.X, T * wi, q + step, xn);
-            if (!same) load(Y, T * wj, q + step, yn);
-        }
+    auto products = [&](const double (&x)[T][4], const double (&y)[T][4]) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -111,6 +76,71 @@ __global__ __launch_bounds__(256, 2) void k_nt(ProdBatch prod, double *part) {
 #pragma unroll
                 for (int t = 0; t < T; ++t)
                     if (!(SYM && GW == 1 && t < a)) acc[a][t] = mfma(x[a][j], y[t][j], acc[a][t]);
+    };
+    // Whole groups: PD of them in flight, in loads that no branch holds (one in
+    // a branch is waited for where the branches meet).  Rows past N read row
+    // N - 1; their sums are not used.  With this and four groups a wave
+    // instead of sixteen, 5 orbitals on 40^3: B 20.4 -> 5.0 us, G 11.3 -> 4.4;
+    // 45 on 80^3: G 47 -> 34; large fields are at their bytes either way (four
+    // groups in flight instead of two: 96^3 G 41 -> 46 us).
+    constexpr int PD = T <= 2 ? 2 : 1;
+    const double *px[T], *py[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        px[t] = ch.X + (long long)min(16 * (T * wi + t) + c, N - 1) * M + 4 * g;
+        py[t] = Y + (long long)min(16 * (T * wj + t) + c, N - 1) * M + 4 * g;
+    }
+    auto load = [&](const double *const (&p)[T], long long grp, double (&f)[T][4]) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const dbl2u lo = *reinterpret_cast<const dbl2u *>(p[t] + 16 * grp);
+            const dbl2u hi = *reinterpret_cast<const dbl2u *>(p[t] + 16 * grp + 2);
+            f[t][0] = lo.x;
+            f[t][1] = lo.y;
+            f[t][2] = hi.x;
+            f[t][3] = hi.y;
+        }
+    };
+    const long long g1f = std::min(g1, M >> 4);
+    const long long first = g0 + (GW == 2 ? 0 : w);
+    if (first < g1f && !idle) {
+        const long long last = g1f - 1;
+        double x[PD][T][4], y[PD][T][4];
+#pragma unroll
+        for (int u = 0; u < PD; ++u) {
+            load(px, std::min(first + u * step, last), x[u]);
+            if (!same) load(py, std::min(first + u * step, last), y[u]);
+        }
+        for (long long q = first; q < g1f; q += PD * step) {
+#pragma unroll
+            for (int u = 0; u < PD; ++u) {
+                double xc[T][4], yc[T][4];
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        xc[t][j] = x[u][t][j];
+                        yc[t][j] = same ? x[u][t][j] : y[u][t][j];
+                    }
+                const long long nq = std::min(q + (PD + u) * step, last);
+                load(px, nq, x[u]);
+                if (!same) load(py, nq, y[u]);
+                if (q + u * step < g1f) products(xc, yc);
+            }
+        }
+    }
+    // the nodes after the last whole group
+    if (g1 > g1f && (GW == 2 ? !idle : (int)((g1f - g0) & 3) == w)) {
+        double x[T][4], y[T][4];
+        const long long m = 16 * g1f + 4 * g;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                x[t][j] = m + j < M ? px[t][16 * g1f + j] : 0.0;
+                y[t][j] = m + j < M ? py[t][16 * g1f + j] : 0.0;
+            }
+        products(x, y);
     }
     double *out = part + ch.poff + (size_t)b * NP * NP;
     if (GW == 2) {
@@ -289,7 +319,8 @@ void nt_shape(int N, int &T, int &GW) {
 // gives the same S alone and in a batch.
 long long nt_blocks(int T, int GW, long long M, size_t fit) {
     const long long occ = GW == 1 && T <= 2 ? 4 : 2;
-    const long long most = std::max<long long>(1, M / (GW == 1 ? 1024 : 256));
+    // four groups a wave at least: fields of few nodes are bound by latency
+    const long long most = std::max<long long>(1, M / (GW == 1 ? 256 : 64));
     return std::max<long long>(1, std::min({most, occ * cu_count(), (long long)fit}));
 }
 
