@@ -299,7 +299,10 @@ __global__ __launch_bounds__(1024) void k_oct_final(const OctTile *tiles, int nt
 // orbitals fit in half the LDS; 2: in all of it, so one block of eight waves
 // (two sets of 16 nodes) takes the compute unit; 0: they come 16 orbitals at
 // a time.  With one mode of 256 threads for all, groups of three to six
-// orbital tiles paid two more barriers a tile.
+// orbital tiles paid two more barriers a tile.  31 orbitals at 96^3: 263 us
+// (the fields' bytes 130) where the boundary combination, the average, the
+// adjoint field's expansion and source took 199 + 198 + 133 + 155; the
+// descriptors in scalar registers and the unconditional prefetch are 17 of it.
 // ---------------------------------------------------------------------------
 template <int L, int MODE>
 __global__ __launch_bounds__(MODE == 2 ? 512 : 256, 2) void k_sic_octant(

@@ -1,6 +1,6 @@
 // Host runtime of the FLOSIC SIC library: argument validation, batched work
 // plans (one Poisson problem per orbital, all orbitals of all spin channels
-// and systems in the same CG launches), workspace management, the forward
+// and systems in the same launches), workspace management, the forward
 // and backward passes and the operator-level entry points of fsic.h.
 #include <hip/hip_runtime.h>
 
