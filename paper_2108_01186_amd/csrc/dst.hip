@@ -29,6 +29,7 @@
 #include <tuple>
 
 #include "kernels.h"
+#include "lds.h"
 
 namespace fsic {
 
@@ -718,11 +719,6 @@ __global__ __launch_bounds__(kFT, OCC2 ? 4 : 2) void k_dst_xy(const Item *units,
     }
 }
 
-template <class K>
-void set_lds_limit(K kern, size_t bytes) {
-    if (bytes > 65536) hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
 namespace {
 
 // The passes of one preconditioner application.  T: type of r; PO: the last
@@ -839,6 +835,10 @@ hipError_t dst_setup(int np, int variant, int npxy, bool two) {
     static std::set<std::tuple<int, int, int, int, bool>> done;
     std::lock_guard<std::mutex> lk(mu);
     if (done.count(key)) return hipSuccess;
+    hipError_t e = hipSuccess;
+    auto set_lds_limit = [&](auto kern, size_t bytes) {
+        if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void *>(kern), bytes);
+    };
     if (npxy > 0) {
         const size_t lxy = dst_xy_lds(npxy, two);
         set_lds_limit(k_dst_xy<true, float, float, false>, lxy);
@@ -878,7 +878,6 @@ hipError_t dst_setup(int np, int variant, int npxy, bool two) {
     else if (variant == 2) FSIC_DST_LIMITS(64, true, 160);
     else if (variant == 3) FSIC_DST_LIMITS(64, false, 192);
 #undef FSIC_DST_LIMITS
-    const hipError_t e = hipGetLastError();
     if (e == hipSuccess) done.insert(key);
     return e;
 }

@@ -35,6 +35,7 @@
 
 #include "fdm_basis.h"
 #include "kernels.h"
+#include "lds.h"
 #include "buffer.h"
 
 namespace fsic {
@@ -750,16 +751,11 @@ size_t line_lds(int T) {
 
 size_t z_lds(int T) { return line_lds(T) + 32 * (size_t)T * sizeof(double); }
 
-template <class K>
-hipError_t allow_lds(K k, size_t lds) {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
 // blocks of a kernel that one compute unit holds
 template <class K>
 int occ_of(K k, int threads, size_t lds) {
     int n = 0;
-    if (allow_lds(k, lds) != hipSuccess) return 0;
+    if (allow_lds(reinterpret_cast<const void *>(k), lds) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(k), threads, lds) != hipSuccess)
         return 0;
     return n;
@@ -803,7 +799,7 @@ hipError_t fdm_setup() {
     std::lock_guard<std::mutex> lk(mu);
     if (ready.count(dev)) return hipSuccess;
     auto set = [&](auto k, size_t lds) {
-        if (e == hipSuccess) e = allow_lds(k, lds);
+        if (e == hipSuccess) e = allow_lds(reinterpret_cast<const void *>(k), lds);
     };
 #define XY(TT)                                                                  \
     set(k_fdm_xy_fwd<TT, true>, std::min<size_t>(xy_lds(TT, true), 160 * 1024));  \

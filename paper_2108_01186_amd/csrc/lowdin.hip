@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "kernels.h"
+#include "lds.h"
 
 namespace fsic {
 
@@ -338,10 +339,6 @@ __global__ __launch_bounds__(kLwThreads) void k_lowdin(int N, const double *T, c
 static size_t lowdin_lds(int N) {
     const size_t Ne = N + (N & 1);
     return (N <= 64 ? 2 : 1) * Ne * (Ne + 1) * sizeof(double);
-}
-
-static hipError_t allow_lds(const void *f, size_t dyn) {
-    return dyn > 65536 ? hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) : hipSuccess;
 }
 
 hipError_t launch_lowdin(int N, const double *T, const double *G, double *S, double *lam,

@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "lds.h"
 
 namespace fsic {
 
@@ -582,7 +583,7 @@ int harm_slots(int kind, int lmax) {
         default: FN(8); break;
     }
 #undef FN
-    if (lds > 32768) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    (void)allow_lds(fn, lds);
     int per = 0, cus = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, 256, lds) != hipSuccess || per < 1) per = 1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 1;
@@ -625,7 +626,7 @@ hipError_t launch_harm_expand(int mode, int lmax, const HarmTables &ht, int radi
 #define CALL(L)                                                                                        \
     do {                                                                                               \
         const void *fn = mode == 0 ? (const void *)k_harm_expand<L, 0> : (const void *)k_harm_expand<L, 1>; \
-        if (lds > 32768) (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
+        if (const hipError_t e = allow_lds(fn, lds)) return e;                                         \
         if (mode == 0)                                                                                 \
             hipLaunchKernelGGL((k_harm_expand<L, 0>), dim3(nitems), dim3(256), lds, s, ht, radius, orb, \
                                ghost_count, items, C, out);                                            \

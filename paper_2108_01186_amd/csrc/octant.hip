@@ -24,6 +24,7 @@
 
 #include "buffer.h"
 #include "kernels.h"
+#include "lds.h"
 #include "lsda.h"
 
 namespace fsic {
@@ -605,8 +606,7 @@ hipError_t launch_sic_octant(int lmax, const OctItem *items, int nitems, const O
 #define GO(L, M) hipLaunchKernelGGL((k_sic_octant<L, M>), dim3(nitems), dim3(M == 2 ? 512 : 256), lds, s, items, groups, \
                                     chans, ntiles, frag, PHI, W, floor, want_v, partU, partX)
 #define F(L)                                                                                             \
-    if (lds > 65536)                                                                                     \
-        hipFuncSetAttribute(sic_kernel<L>(mode), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);   \
+    if (const hipError_t e = allow_lds(sic_kernel<L>(mode), lds)) return e;                              \
     if (mode == 0) GO(L, 0);                                                                             \
     else if (mode == 1) GO(L, 1);                                                                        \
     else GO(L, 2)
@@ -642,8 +642,10 @@ int oct_slots(int kind, int lmax, int group_tiles) {
     }
 #undef F
     if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cu < 1) cu = 256;
-    if (lds > 65536) hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, mode == 2 ? 512 : 256, lds) != hipSuccess || n < 1) n = 1;
+    if (allow_lds(fn, lds) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, mode == 2 ? 512 : 256, lds) != hipSuccess || n < 1)
+        n = 1;
+    (void)hipGetLastError();  // a failed query leaves no error behind for the next launch
     return cache[key] = cu * n;
 }
 

@@ -19,6 +19,7 @@
 #include <mutex>
 
 #include "kernels.h"
+#include "lds.h"
 
 namespace fsic {
 
@@ -428,8 +429,7 @@ hipError_t launch_transform(const ProdChan *chans, int n, hipStream_t s) {
             }
 #define GO(TT)                                                                                                  \
     case TT:                                                                                                    \
-        if (lds > 65536)                                                                                        \
-            hipFuncSetAttribute((const void *)k_nn<TT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);  \
+        if (const hipError_t e = allow_lds((const void *)k_nn<TT>, lds)) return e;                              \
         hipLaunchKernelGGL((k_nn<TT>), dim3(blocks), dim3(256), lds, s, p);                                     \
         break;
             switch (T) { GO(1) GO(2) GO(3) GO(4) GO(5) GO(6) GO(7) GO(8) }
