@@ -83,11 +83,11 @@ enum { FSIC_FP64 = 0, FSIC_MIXED = 1 };
  *             operator itself: the eigenvectors of its one-axis factors
  *             diagonalise it, so the first iteration is the solution up to
  *             FP64 rounding and the FP64 residual only has to confirm it
- *             (tolerances near the rounding level take a second one).  An
- *             orbital that does not get there (non-finite data) goes to
- *             conjugate gradients preconditioned by type-I sine transforms.
- *             A batch with a grid axis above 192 nodes is solved with plain
- *             CG instead.  The default.
+ *             (tolerances near the rounding level take a second one, three at
+ *             most and no more than max_iter).  An orbital that does not get
+ *             there (non-finite data) makes the call return FSIC_ENOCONV; the
+ *             others keep their solutions.  A batch with a grid axis above 192
+ *             nodes is solved with plain CG instead.  The default.
  *   FSIC_AAR  alternating Anderson-Richardson (the solver of the paper's
  *             real-space code, Sec. II.A) with the inverse of the same
  *             stencil under odd reflection at the faces, applied with type-I

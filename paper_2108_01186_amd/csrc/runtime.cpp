@@ -1377,17 +1377,17 @@ constexpr int kDirectRounds = 3;
 // FSIC_PCG by the direct solver: x = K^{-1} b, then the FP64 residual.  One
 // application leaves about 1e-13 (40^3) to 1e-12 (192^3) of ||b||; an
 // orbital still above tol gets x += K^{-1} r and the residual recursion
-// r += L d, as in conjugate gradients.  all: every orbital met tol.
+// r += L d, as in conjugate gradients.  An orbital that is above tol after the
+// last round (NaN or infinities in its data; max_iter below the rounds it needs)
+// is reported as not converged; the others' solutions do not depend on it.
 fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int square, double scale, bool with_bc,
-                         double *X, int precision, double tol, int max_iter, SolveReport &rep, const double *qlm_in,
-                         bool &all) {
+                         double *X, int precision, double tol, int max_iter, SolveReport &rep, const double *qlm_in) {
     hipStream_t s = c->stream;
     const int norb = (int)b.orb.size();
     const int nit7 = (int)b.items7.size(), nit8 = (int)b.items8.size();
     const bool mixed = precision == FSIC_MIXED, prof = (c->opts.flags & FSIC_PROFILE) != 0;
     const bool graphs = mixed && (c->opts.flags & FSIC_GRAPHS) && !prof;
     const double tol2 = tol * tol;
-    all = false;
     if (with_bc) {
         const fsic_status st = boundary_term(c, b, src, square, qlm_in);
         if (st) return st;
@@ -1465,6 +1465,7 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
     fsic_status st = timed(2, 0, apply);
     if (!st) st = timed(3, 1, check);
     if (st) return st;
+    bool all = false;
     auto count = [&]() -> fsic_status {
         const fsic_status cst = copy_stage(c, norb);
         if (cst) return cst;
@@ -1487,8 +1488,6 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
                                     1.0, c->Q.p, c->partRU.p, b.tot7, s));
         if ((st = decide(rounds + 1, s)) || (st = count())) return st;
     }
-    if (!all && !status_error(c)) return FSIC_OK;
-    all = true;
     if (mixed) rep.refinements += rounds;
     if (rounds > 1) {  // the residual that is reported is that of x, not of the recursion
         if ((st = residual(nullptr, nullptr, s)) || (st = decide(0, s)) || (st = copy_stage(c, norb))) return st;
@@ -1504,19 +1503,8 @@ fsic_status solve_direct(fsic_ctx *c, const Batch &b, const double *src, int squ
 fsic_status solve_batch(fsic_ctx *c, const Batch &b, const double *src, int square, double scale, bool with_bc,
                         double *X, int precision, double tol, int max_iter, SolveReport &rep,
                         const double *qlm_in = nullptr) {
-    if (!b.direct) return solve_krylov(c, b, src, square, scale, with_bc, X, precision, tol, max_iter, rep, qlm_in);
-    bool all = false;
-    fsic_status st = solve_direct(c, b, src, square, scale, with_bc, X, precision, tol, max_iter, rep, qlm_in, all);
-    if (st || all) return st;
-    // an orbital the direct solver does not bring to tol (non-finite data):
-    // conjugate gradients with the sine-transform preconditioner decide
-    Batch bk = b;
-    bk.direct = false;
-    build_sine(bk, c->radius, DstTune{});
-    if ((st = prepare_batch(c, bk, precision))) return st;
-    if ((st = solve_krylov(c, bk, src, square, scale, with_bc, X, precision, tol, max_iter, rep, qlm_in))) return st;
-    HIPCHK(c, hipStreamSynchronize(c->stream));  // bk's tables are in flight until here
-    return FSIC_OK;
+    const auto solve = b.direct ? solve_direct : solve_krylov;
+    return solve(c, b, src, square, scale, with_bc, X, precision, tol, max_iter, rep, qlm_in);
 }
 
 fsic_status solve_krylov(fsic_ctx *c, const Batch &b, const double *src, int square, double scale,

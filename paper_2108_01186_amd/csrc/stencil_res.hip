@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256) void k_direct_check(int norb, const OrbDesc *o
     }
     const int ok = rr <= tol2 * b2;
     done[o] = si[7 * norb + o] = ok;
-    si[o] = ok ? round : 0;
+    si[o] = round;
 }
 
 hipError_t launch_direct_check(int norb, const OrbDesc *orb, const double *partRU, const double *bpart, int bstencil,
