@@ -532,19 +532,6 @@ const std::vector<float> &dst_block(int n, int radius) {
     return cache.emplace(std::make_pair(n, radius), std::move(v)).first->second;
 }
 
-// Axis table of the direct solver (fdm_basis.h), cached per process; at most
-// 32 axes are kept (a new one then drops the others).
-std::vector<double> fdm_block(int n, int radius) {
-    static std::mutex mu;
-    static std::map<std::pair<int, int>, std::vector<double>> cache;
-    std::lock_guard<std::mutex> lk(mu);
-    auto f = cache.find({n, radius});
-    if (f != cache.end()) return f->second;
-    if (cache.size() >= 32) cache.clear();
-    const Coeffs cw = fd_weights(radius);
-    return cache.emplace(std::make_pair(n, radius), fdm_axis_table(n, radius, cw.c)).first->second;
-}
-
 // LDS bytes one workgroup may use on the current device
 size_t device_lds_limit() {
     int dev = 0, v = 0;
@@ -584,12 +571,13 @@ void build_direct(Batch &b, int radius, bool xy) {
     const size_t ldsmax = device_lds_limit();
     const char *env = std::getenv("FSIC_DST_XY");
     if (env && std::atoi(env) == 0) xy = false;
+    const Coeffs cw = fd_weights(radius);
     std::map<int, int> at;  // axis length -> table offset
     auto table = [&](int n) {
         auto f = at.find(n);
         if (f != at.end()) return f->second;
         const int o = (int)b.ftab.size();
-        const std::vector<double> t = fdm_block(n, radius);
+        const std::vector<double> &t = fdm_axis(n, radius, cw.c);
         b.ftab.insert(b.ftab.end(), t.begin(), t.end());
         return at[n] = o;
     };
