@@ -12,6 +12,7 @@
 //               x_{n-1-j} = the same with a minus.
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 #include <map>
 #include <mutex>
@@ -29,92 +30,129 @@ inline int fdm_table_doubles(int n) {
     return 2 * L * L + 2 * L;
 }
 
-// c[0 .. p]: second-difference weights on unit spacing.
-inline std::vector<double> fdm_axis_table(int n, int p, const double *c) {
+// The even (par 0) or odd (par 1) half of an axis table; c[0 .. p]:
+// second-difference weights on unit spacing.
+inline void fdm_axis_parity(int n, int p, const double *c, int par, double *tab) {
     typedef long double ld;
     const int L = 16 * fdm_tiles(n);
-    std::vector<double> tab((size_t)fdm_table_doubles(n), 0.0);
-    for (int q = 2 * L * L; q < 2 * L * L + 2 * L; ++q) tab[q] = 1.0;
+    const ld pi = 3.141592653589793238462643383279502884L, r2 = sqrtl(2.0L);
+    const int h = par == 0 ? (n + 1) / 2 : n / 2;
+    const int mid = (par == 0 && (n & 1)) ? h - 1 : -1;
+    if (h == 0) return;
+    // the parity block of K in the orthonormal basis (e_j +- e_{n-1-j}) / sqrt 2
+    // (e_mid alone), by columns: its few nonzero entries
     auto K = [&](int i, int j) -> ld {
         const int d = i > j ? i - j : j - i;
         return d <= p ? -(ld)c[d] : 0.0L;
     };
-    const ld pi = 3.141592653589793238462643383279502884L, r2 = sqrtl(2.0L);
-    for (int par = 0; par < 2; ++par) {
-        const int h = par == 0 ? (n + 1) / 2 : n / 2;
-        const int mid = (par == 0 && (n & 1)) ? h - 1 : -1;
-        if (h == 0) continue;
-        // parity block in the orthonormal basis (e_j +- e_{n-1-j}) / sqrt 2
-        // (e_mid alone), then in the basis of the type-I sines of that parity,
-        // which is nearly diagonal already
-        std::vector<ld> A((size_t)h * h), V((size_t)h * h), W((size_t)h * h);
-        for (int i = 0; i < h; ++i)
-            for (int j = 0; j < h; ++j) {
-                ld v;
-                if (i == mid && j == mid) v = K(i, j);
-                else if (i == mid || j == mid) v = r2 * K(i, j);
-                else v = par == 0 ? K(i, j) + K(i, n - 1 - j) : K(i, j) - K(i, n - 1 - j);
-                A[(size_t)i * h + j] = v;
-            }
-        const ld sn = sqrtl(2.0L / (n + 1));
-        for (int k = 0; k < h; ++k)
-            for (int j = 0; j < h; ++j) {
-                const long long a = ((long long)(2 * k + par + 1) * (j + 1)) % (2LL * (n + 1));
-                V[(size_t)k * h + j] = (j == mid ? sn : sn * r2) * sinl(pi * (ld)a / (ld)(n + 1));
-            }
-        for (int k = 0; k < h; ++k)  // W = V A
-            for (int j = 0; j < h; ++j) {
-                ld s = 0;
-                for (int i = 0; i < h; ++i) s += V[(size_t)k * h + i] * A[(size_t)i * h + j];
-                W[(size_t)k * h + j] = s;
-            }
-        for (int k = 0; k < h; ++k)  // A = W V^T
-            for (int l = 0; l <= k; ++l) {
-                ld s = 0;
-                for (int i = 0; i < h; ++i) s += W[(size_t)k * h + i] * V[(size_t)l * h + i];
-                A[(size_t)k * h + l] = A[(size_t)l * h + k] = s;
-            }
-        // cyclic Jacobi, rows of V rotated along
-        for (int sweep = 0; sweep < 40; ++sweep) {
-            bool any = false;
-            for (int i = 0; i + 1 < h; ++i)
-                for (int j = i + 1; j < h; ++j) {
-                    const ld aij = A[(size_t)i * h + j], aii = A[(size_t)i * h + i], ajj = A[(size_t)j * h + j];
-                    if (fabsl(aij) <= 1e-19L * sqrtl(fabsl(aii * ajj))) continue;
-                    any = true;
-                    const ld th = (ajj - aii) / (2 * aij);
-                    const ld t = (th >= 0 ? 1 : -1) / (fabsl(th) + sqrtl(1 + th * th));
-                    const ld cs = 1 / sqrtl(1 + t * t), ss = t * cs;
-                    for (int q = 0; q < h; ++q) {  // rows i, j
-                        const ld x = A[(size_t)i * h + q], y = A[(size_t)j * h + q];
-                        A[(size_t)i * h + q] = cs * x - ss * y;
-                        A[(size_t)j * h + q] = ss * x + cs * y;
-                    }
-                    for (int q = 0; q < h; ++q) {  // columns i, j
-                        const ld x = A[(size_t)q * h + i], y = A[(size_t)q * h + j];
-                        A[(size_t)q * h + i] = cs * x - ss * y;
-                        A[(size_t)q * h + j] = ss * x + cs * y;
-                    }
-                    A[(size_t)i * h + j] = A[(size_t)j * h + i] = 0;
-                    for (int q = 0; q < h; ++q) {
-                        const ld x = V[(size_t)i * h + q], y = V[(size_t)j * h + q];
-                        V[(size_t)i * h + q] = cs * x - ss * y;
-                        V[(size_t)j * h + q] = ss * x + cs * y;
-                    }
-                }
-            if (!any) break;
+    std::vector<std::vector<std::pair<int, ld>>> col(h);
+    for (int j = 0; j < h; ++j)
+        for (int i = 0; i < h; ++i) {
+            ld v;
+            if (i == mid && j == mid) v = K(i, j);
+            else if (i == mid || j == mid) v = r2 * K(i, j);
+            else v = par == 0 ? K(i, j) + K(i, n - 1 - j) : K(i, j) - K(i, n - 1 - j);
+            if (v != 0.0L) col[j].push_back({i, v});
         }
-        for (int k = 0; k < h; ++k) {
-            tab[(size_t)2 * L * L + (size_t)par * L + k] = (double)A[(size_t)k * h + k];
-            for (int j = 0; j < h; ++j)
-                tab[((size_t)par * L + k) * L + j] = (double)(j == mid ? V[(size_t)k * h + j] : V[(size_t)k * h + j] / r2);
+    auto dot = [&](const double *f, const double *g) {
+        double s = 0.0;
+        for (int q = 0; q < h; ++q) s += f[q] * g[q];
+        return s;
+    };
+    // rows of V: the type-I sines of that parity, which make the block nearly
+    // diagonal already (A = V K V^T), then eigenvectors by cyclic Jacobi in
+    // FP64; A stays symmetric, so a rotation forms rows i and j and stores them
+    // as columns too.  (In extended precision the rotations took 12 ms for a
+    // 96-node axis and 96 ms for a 192-node one, in a program's first call.)
+    std::vector<double> V((size_t)h * h), W((size_t)h * h), A((size_t)h * h);
+    const ld sn = sqrtl(2.0L / (n + 1));
+    std::vector<ld> sine(2 * (size_t)(n + 1));
+    for (int a = 0; a < 2 * (n + 1); ++a) sine[a] = sinl(pi * (ld)a / (ld)(n + 1));
+    for (int k = 0; k < h; ++k)
+        for (int j = 0; j < h; ++j)
+            V[(size_t)k * h + j] = (double)((j == mid ? sn : sn * r2) * sine[((long long)(2 * k + par + 1) * (j + 1)) % (2 * (n + 1))]);
+    for (int k = 0; k < h; ++k)
+        for (int j = 0; j < h; ++j) {
+            double s = 0.0;
+            for (const auto &e : col[j]) s += V[(size_t)k * h + e.first] * (double)e.second;
+            W[(size_t)k * h + j] = s;
+        }
+    for (int k = 0; k < h; ++k)
+        for (int l = 0; l <= k; ++l) A[(size_t)k * h + l] = A[(size_t)l * h + k] = dot(&W[(size_t)k * h], &V[(size_t)l * h]);
+    for (int sweep = 0; sweep < 40; ++sweep) {
+        bool any = false;
+        for (int i = 0; i + 1 < h; ++i)
+            for (int j = i + 1; j < h; ++j) {
+                double *const Ai = &A[(size_t)i * h], *const Aj = &A[(size_t)j * h];
+                const double aij = Ai[j], aii = Ai[i], ajj = Aj[j];
+                if (std::fabs(aij) <= 1e-14 * std::sqrt(std::fabs(aii * ajj))) continue;
+                any = true;
+                const double th = (ajj - aii) / (2 * aij);
+                const double t = (th >= 0 ? 1 : -1) / (std::fabs(th) + std::sqrt(1 + th * th));
+                const double cs = 1 / std::sqrt(1 + t * t), ss = t * cs;
+                double *const Vi = &V[(size_t)i * h], *const Vj = &V[(size_t)j * h];
+                for (int q = 0; q < h; ++q) {
+                    const double x = Ai[q], y = Aj[q], u = Vi[q], v = Vj[q];
+                    Ai[q] = cs * x - ss * y;
+                    Aj[q] = ss * x + cs * y;
+                    Vi[q] = cs * u - ss * v;
+                    Vj[q] = ss * u + cs * v;
+                }
+                Ai[i] = aii - t * aij;
+                Aj[j] = ajj + t * aij;
+                Ai[j] = Aj[i] = 0;
+                for (int q = 0; q < h; ++q) {
+                    A[(size_t)q * h + i] = Ai[q];
+                    A[(size_t)q * h + j] = Aj[q];
+                }
+            }
+        if (!any) break;
+    }
+    // One step of the refinement of Ogita and Aishima (2018): with the residual
+    // r_k = K v_k - lam_k v_k of each FP64 eigenvector formed in extended
+    // precision, V += C V, C_kl = r_k . v_l / (lam_k - lam_l),
+    // C_kk = (1 - v_k . v_k) / 2, takes the error (1e-14 over the eigenvalues'
+    // gaps) to its square.
+    std::vector<ld> lam(h), x(h), y(h);
+    for (int k = 0; k < h; ++k) {
+        ld xy = 0, xx = 0;
+        for (int q = 0; q < h; ++q) x[q] = V[(size_t)k * h + q];
+        for (int q = 0; q < h; ++q) {
+            y[q] = 0;
+            for (const auto &e : col[q]) y[q] += x[e.first] * e.second;
+            xy += x[q] * y[q];
+            xx += x[q] * x[q];
+        }
+        lam[k] = xy / xx;
+        for (int q = 0; q < h; ++q) W[(size_t)k * h + q] = (double)(y[q] - lam[k] * x[q]);
+        A[(size_t)k * h + k] = (double)((1 - xx) / 2);
+    }
+    for (int k = 0; k < h; ++k)
+        for (int l = 0; l < h; ++l)
+            if (l != k) A[(size_t)k * h + l] = dot(&W[(size_t)k * h], &V[(size_t)l * h]) / (double)(lam[k] - lam[l]);
+    std::fill(W.begin(), W.end(), 0.0);
+    for (int k = 0; k < h; ++k)
+        for (int l = 0; l < h; ++l)
+            for (int j = 0; j < h; ++j) W[(size_t)k * h + j] += A[(size_t)k * h + l] * V[(size_t)l * h + j];
+    for (int k = 0; k < h; ++k) {
+        tab[(size_t)2 * L * L + (size_t)par * L + k] = (double)lam[k];
+        for (int j = 0; j < h; ++j) {
+            const ld v = (ld)V[(size_t)k * h + j] + (ld)W[(size_t)k * h + j];
+            tab[((size_t)par * L + k) * L + j] = (double)(j == mid ? v : v / r2);
         }
     }
+}
+
+inline std::vector<double> fdm_axis_table(int n, int p, const double *c) {
+    const int L = 16 * fdm_tiles(n);
+    std::vector<double> tab((size_t)fdm_table_doubles(n), 0.0);
+    for (int q = 2 * L * L; q < 2 * L * L + 2 * L; ++q) tab[q] = 1.0;
+    for (int par = 0; par < 2; ++par) fdm_axis_parity(n, p, c, par, tab.data());
     return tab;
 }
 
-// The table of (n, p), made once per process (a 96-node axis takes 12 ms, a
-// 192-node one 96 ms) and never dropped: a batch may hold any number of axis
+// The table of (n, p), made once per process (a 96-node axis takes 3 ms, a
+// 192-node one 27 ms) and never dropped: a batch may hold any number of axis
 // lengths, and rebuilding those past a limit would cost that time in every
 // call.  n <= 192 bounds them to 12 MB per order.
 inline const std::vector<double> &fdm_axis(int n, int p, const double *c) {

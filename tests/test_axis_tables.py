@@ -1,7 +1,9 @@
-"""The direct solver's axis tables are made once per process, however many
-axis lengths are in use."""
+"""The direct solver's axis tables: made once per process, however many axis
+lengths are in use, and as accurate as their rounding."""
 import os
 import subprocess
+
+import numpy as np
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2108_01186_amd", "csrc")
@@ -43,3 +45,37 @@ def test_tables_are_made_once(tmp_path):
     src.write_text(PROGRAM)
     subprocess.run(["g++", "-O2", "-std=c++17", "-pthread", "-I" + CSRC, str(src), "-o", exe], check=True)
     assert subprocess.run([exe], timeout=60).returncode == 0
+
+
+TABLE = r"""
+#include "fdm_basis.h"
+#include <cstdio>
+#include <cstdlib>
+int main(int, char **a) {
+    const double c[2] = {-2.0, 1.0};
+    const auto t = fsic::fdm_axis_table(atoi(a[1]), 1, c);
+    fwrite(t.data(), 8, t.size(), stdout);
+}
+"""
+
+
+def test_second_order_axes_are_the_sines(tmp_path):
+    """At order 2 the eigenvectors are known, sqrt(2 / (n + 1)) times sines: the
+    table holds them to half a unit in the last place of the largest entry
+    (the rounding of the table) and as much again for what forms them."""
+    src, exe = tmp_path / "t.cpp", str(tmp_path / "t")
+    src.write_text(TABLE)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I" + CSRC, str(src), "-o", exe], check=True)
+    ld = np.longdouble
+    for n in (8, 9, 31, 32, 33, 64, 96, 127, 160, 192):
+        t = np.frombuffer(subprocess.run([exe, str(n)], check=True, capture_output=True, timeout=60).stdout)
+        L = 16 * (((n + 1) // 2 + 15) // 16)
+        for par in range(2):
+            h = (n + 1) // 2 if par == 0 else n // 2
+            lam = t[2 * L * L + par * L:][:h]
+            C = t[:2 * L * L].reshape(2, L, L)[par, :h, :h][np.argsort(lam)]
+            k, j = np.arange(h)[:, None], np.arange(h)[None]
+            ref = np.sqrt(ld(2) / (n + 1)) * np.sin(ld("3.14159265358979323846264338327950288") * ld(1) / (n + 1)
+                                                    * ((2 * k + par + 1) * (j + 1) % (2 * (n + 1))))
+            sign = np.sign((C * ref).sum(1))[:, None]
+            assert np.abs(sign * C - ref).max() <= np.spacing(float(np.abs(ref).max())), (n, par)
