@@ -296,7 +296,19 @@ void fsic_destroy(fsic_ctx *ctx);
  * Operator-level entry points (the same kernels the path runs), for
  * component checks.  All pointers are DEVICE memory unless stated; each
  * call is synchronous on the given stream (NULL = default stream).
+ *
+ * The work memory of these calls (fsic_op_flo_noalloc has none) is kept for
+ * the next one: at most 1 GiB per device and 16 MiB of pinned host memory, in
+ * at most 256 blocks, the least recently used given back first.  A block that
+ * no call has used for 30 s is given back by the next call of the library
+ * that creates a context, runs a forward pass or is one of these; all are when
+ * an allocation of the library fails, when a context is destroyed, and by
+ * fsic_release_workspace.
  * -------------------------------------------------------------------- */
+
+/* Gives back the work memory kept for the calls below, of every device.  Calls
+ * that run meanwhile in other threads keep theirs until they end. */
+void fsic_release_workspace(void);
 
 /* Lu[f] = L u[f] for count fields on grid n with spacing h: the
  * fd_order-th order centred star Laplacian (Sec. II.A), zero Dirichlet

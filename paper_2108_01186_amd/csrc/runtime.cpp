@@ -2076,6 +2076,7 @@ fsic_status fsic_create(fsic_ctx **ctx, const fsic_opts *opts, void *hip_stream)
     std::string why;
     fsic_status st = validate_opts(opts, why);
     if (st) return st;
+    BlockCache::get().trim();
     fsic_ctx *c = new (std::nothrow) fsic_ctx();
     if (!c) return FSIC_ENOMEM;
     c->opts = *opts;
@@ -2322,6 +2323,7 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     const double t0 = now_ms();
     if (nsys < 1 || !sys || !e_sic) return set_err(c, FSIC_EINVAL, "nsys >= 1, sys and e_sic are required");
     c->tape = false;
+    BlockCache::get().trim();
     const fsic_opts &o = c->opts;
     const int P = c->radius;
     std::string why;
@@ -2718,6 +2720,8 @@ struct OpCtx {
     ~OpCtx() { fsic_destroy(c); }
 };
 }  // namespace
+
+void fsic_release_workspace(void) { BlockCache::get().flush(); }
 
 fsic_status fsic_op_laplacian(const int32_t *n, double h, int32_t fd_order, int32_t count,
                               const double *u, double *Lu, void *hip_stream) {

@@ -10,9 +10,11 @@
 // Nothing in a block survives a call: every kernel writes what it reads.
 //
 // The cache holds at most kKeepBytes per device (kKeepPinned pinned) and
-// kKeepBlocks blocks; the least recently used go first, blocks unused for
-// kKeepSeconds go at the next call, and all go when an allocation fails or a
-// context is destroyed.
+// kKeepBlocks blocks; the least recently used go first.  Blocks unused for
+// kKeepSeconds go at the next call that gives blocks back or trims, and all go
+// when an allocation fails, a context is destroyed or the program asks for it.
+// (No timer gives them back: hipFree from a thread of its own would end a
+// stream capture of the program.)
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -64,9 +66,9 @@ class BlockCache {
     // blocks no work is pending on (list nodes move: nothing is allocated)
     void give(std::list<Block> &blocks) {
         std::list<Block> drop;
+        const double now = seconds();
         {
             std::lock_guard<std::mutex> lk(mu_);
-            const double now = seconds();
             for (Block &b : blocks) b.t = now;
             kept_.splice(kept_.end(), blocks);
             // newest first, so that the oldest of a device are over its limit
@@ -85,6 +87,11 @@ class BlockCache {
             }
         }
         for (const Block &b : drop) raw_free(b);
+    }
+    // blocks past their time
+    void trim() {
+        std::list<Block> none;
+        give(none);
     }
     void flush() {
         std::list<Block> all;

@@ -104,6 +104,7 @@ fsic_forward_backward = _sig("fsic_forward_backward", ctypes.c_int,
 fsic_status_string = _sig("fsic_status_string", ctypes.c_char_p, [ctypes.c_int])
 fsic_last_error = _sig("fsic_last_error", ctypes.c_char_p, [_vp])
 fsic_destroy = _sig("fsic_destroy", None, [_vp])
+fsic_release_workspace = _sig("fsic_release_workspace", None, [])
 fsic_op_laplacian = _sig("fsic_op_laplacian", ctypes.c_int,
                          [_ip, ctypes.c_double, ctypes.c_int32, ctypes.c_int32, _vp, _vp, _vp])
 fsic_op_laplacian_f32 = _sig("fsic_op_laplacian_f32", ctypes.c_int,
@@ -130,7 +131,7 @@ fsic_op_interp = _sig("fsic_op_interp", ctypes.c_int,
 
 EXPORTED = ["fsic_default_opts", "fsic_create", "fsic_set_opts", "fsic_forward", "fsic_backward",
             "fsic_forward_backward",
-            "fsic_status_string", "fsic_last_error", "fsic_destroy", "fsic_op_laplacian",
+            "fsic_status_string", "fsic_last_error", "fsic_destroy", "fsic_release_workspace", "fsic_op_laplacian",
             "fsic_op_laplacian_f32", "fsic_op_xc", "fsic_op_poisson", "fsic_op_invsqrt",
             "fsic_op_hamiltonian", "fsic_op_interp",
             "fsic_op_flo", "fsic_op_flo_noalloc"]
@@ -331,6 +332,12 @@ class Context:
 # --------------------------------------------------------------------------
 # operator-level calls
 # --------------------------------------------------------------------------
+
+def release_workspace():
+    """Gives back the device memory (at most 1 GiB per device) that the op_*
+    calls keep for the next one."""
+    fsic_release_workspace()
+
 
 def op_laplacian(u, h: float, fd_order: int = 12, stream=None):
     """L u for u of shape (count, nz, ny, nx) (or (nz, ny, nx)), zero ghosts."""
