@@ -128,7 +128,12 @@ enum { FSIC_CG = 0, FSIC_PCG = 1, FSIC_AAR = 2 };
                                     Poisson solve) and forms v_i = w_i + sum_lm Q_lm,i U_lm from the
                                     moments and a per-grid basis U of unit-moment boundary solutions
                                     (the map is linear in the boundary values); the basis is solved
-                                    once per grid and context in FP64 to relative residual 1e-13 */
+                                    once per grid and context in FP64 to relative residual 1e-13 and
+                                    kept, 2 (lmax + 1)^2 doubles per node of an octant (86 MB for a
+                                    96^3 grid at lmax 6, 0.69 GB for 192^3).  A context keeps as many
+                                    as fit in an eighth of the device's memory (or FSIC_BASIS_MB
+                                    megabytes), those of the last forward pass in any case; the least
+                                    recently used go first and are solved again when needed */
 
 typedef struct {
     int32_t n[3];       /* nodes per axis, 8..4096, fewer than 2^29 nodes in all */
@@ -230,7 +235,7 @@ typedef struct {
      * basis (FSIC_KEEP_TAPE without FSIC_DIRECT_BC or FSIC_EQ9_FORCES), those
      * potentials too; fsic_backward then reports 0 for both.  basis_solves,
      * basis_ms: unit-moment boundary solutions solved in this call for grids
-     * new to the context, and the time they took */
+     * whose basis the context does not hold, and the time they took */
     int32_t npoisson;
     int32_t basis_solves;
     double  basis_ms;

@@ -337,8 +337,14 @@ struct fsic_ctx {
     DBuf<double> octpart, octfrag;
     int n_octs = 0, n_octt = 0, oct_gtiles = 0;
     // octants of the unit-moment boundary solutions and of the harmonics per
-    // grid (n, h bits, lmax, radius), solved once
-    std::map<std::array<long long, 6>, DBuf<double>> bbasis;
+    // grid (n, h bits, lmax, radius), solved once and kept while they fit
+    // (basis_room); used: the forward pass that last did
+    struct Basis {
+        DBuf<double> u;
+        long long used = 0;
+    };
+    std::map<std::array<long long, 6>, Basis> bbasis;
+    long long forwards = 0;
     DBuf<double> qident;  // identity moments of the basis solves
     int basis_solves = 0;
     double basis_ms = 0.0;
@@ -2104,7 +2110,7 @@ fsic_status fsic_set_opts(fsic_ctx *c, const fsic_opts *opts) {
 void fsic_destroy(fsic_ctx *c) {
     if (!c) return;
     hipStreamSynchronize(c->stream);
-    for (auto &kv : c->bbasis) kv.second.release();
+    for (auto &kv : c->bbasis) kv.second.u.release();
     c->bbasis.clear();
     c->qident.release();
     c->PHI.release(); c->V.release(); c->W.release(); c->B.release(); c->R.release();
@@ -2147,10 +2153,41 @@ static size_t octant_nodes(const int *n) {
     return (size_t)((n[0] + 1) / 2) * ((n[1] + 1) / 2) * ((n[2] + 1) / 2);
 }
 
+// Bytes of boundary bases a context keeps: an eighth of the device's memory (52
+// grids of 192^3 at lmax 6, 400 of 96^3), or FSIC_BASIS_MB.
+static size_t basis_limit() {
+    if (const char *e = getenv("FSIC_BASIS_MB")) return (size_t)std::max(0, atoi(e)) << 20;
+    size_t fr = 0, total = 0;
+    if (hipMemGetInfo(&fr, &total) != hipSuccess) return (size_t)32 << 30;
+    return total / 8;
+}
+
+static std::array<long long, 6> basis_key(const fsic_ctx *c, const Chan &ch) {
+    long long hb = 0;
+    std::memcpy(&hb, &ch.h, sizeof(hb));
+    return {ch.n[0], ch.n[1], ch.n[2], hb, c->opts.lmax, c->radius};
+}
+
+// Gives back the bases least recently used, none of this forward pass, until
+// the others take at most `bytes`.
+static void basis_room(fsic_ctx *c, size_t bytes) {
+    size_t sum = 0;
+    for (const auto &kv : c->bbasis) sum += kv.second.u.cap * sizeof(double);
+    while (sum > bytes) {
+        auto old = c->bbasis.end();
+        for (auto i = c->bbasis.begin(); i != c->bbasis.end(); ++i)
+            if (i->second.used != c->forwards && (old == c->bbasis.end() || i->second.used < old->second.used)) old = i;
+        if (old == c->bbasis.end()) return;
+        sum -= old->second.u.cap * sizeof(double);
+        old->second.u.release();
+        c->bbasis.erase(old);
+    }
+}
+
 // The unit-moment boundary solutions U_q (q < (lmax + 1)^2) of a grid:
 // K U_q = the boundary term of the ghost values of moment vector e_q (no
 // source), solved in FP64 to relative residual 1e-13 with the batch's stencil
-// shape and preconditioner layout, once per grid for the context.  Since the
+// shape and preconditioner layout, kept per grid in the context.  Since the
 // map from moments to ghost values to right-hand side is linear, the
 // multipole-boundary solution of any source is its zero-boundary solution
 // plus sum_q Q_q U_q.  Uses the context's solve buffers (the caller prepares
@@ -2158,12 +2195,10 @@ static size_t octant_nodes(const int *n) {
 static fsic_status boundary_basis(fsic_ctx *c, const Chan &ch, const Shape &sh, const DstTune &dt,
                                   const double **U) {
     const int lmax = c->opts.lmax, nlm = (lmax + 1) * (lmax + 1);
-    long long hb = 0;
-    std::memcpy(&hb, &ch.h, sizeof(hb));
-    const std::array<long long, 6> key{ch.n[0], ch.n[1], ch.n[2], hb, lmax, c->radius};
+    const std::array<long long, 6> key = basis_key(c, ch);
     auto f = c->bbasis.find(key);
     if (f != c->bbasis.end()) {
-        *U = f->second.p;
+        *U = f->second.u.p;
         return FSIC_OK;
     }
     const double t0 = now_ms();
@@ -2177,8 +2212,20 @@ static fsic_status boundary_basis(fsic_ctx *c, const Chan &ch, const Shape &sh, 
     std::vector<double> ident((size_t)nlm * nlm, 0.0);
     for (int q = 0; q < nlm; ++q) ident[(size_t)q * nlm + q] = 1.0;
     if ((st = upload(c, c->qident, ident))) return st;
-    DBuf<double> Ub;
-    HIPCHK(c, Ub.ensure((size_t)nlm * ch.M));
+    const size_t Mo = octant_nodes(ch.n), keep = 2 * (size_t)nlm * Mo * sizeof(double), lim = basis_limit();
+    basis_room(c, lim > keep ? lim - keep : 0);
+    DBuf<double> Ub, Uc;
+    if (Ub.ensure((size_t)nlm * ch.M) != hipSuccess || Uc.ensure(2 * (size_t)nlm * Mo) != hipSuccess) {
+        (void)hipGetLastError();
+        basis_room(c, 0);
+        hipError_t he = Ub.ensure((size_t)nlm * ch.M);
+        if (he == hipSuccess) he = Uc.ensure(2 * (size_t)nlm * Mo);
+        if (he != hipSuccess) {
+            Ub.release();
+            Uc.release();
+            return set_err(c, he == hipErrorOutOfMemory ? FSIC_ENOMEM : FSIC_EHIP, hipGetErrorString(he));
+        }
+    }
     SolveReport rep;
     st = solve_batch(c, bb, nullptr, 0, 0.0, true, Ub.p, FSIC_FP64, 1e-13, c->opts.max_iter, rep, c->qident.p);
     if (!st) {
@@ -2188,14 +2235,12 @@ static fsic_status boundary_basis(fsic_ctx *c, const Chan &ch, const Shape &sh, 
     if (!st && !rep.converged) st = set_err(c, FSIC_ENOCONV, "boundary basis solve did not converge");
     if (st) {
         Ub.release();
+        Uc.release();
         return st;
     }
     // kept: the first octant (the reflection parities give the rest), and
     // behind it that of the harmonics, dV r^l Y_lm
-    DBuf<double> Uc;
-    const size_t Mo = octant_nodes(ch.n);
-    hipError_t he = Uc.ensure(2 * (size_t)nlm * Mo);
-    if (he == hipSuccess) he = launch_octant_pack(nlm, ch.n, Ub.p, Uc.p, c->stream);
+    hipError_t he = launch_octant_pack(nlm, ch.n, Ub.p, Uc.p, c->stream);
     if (he == hipSuccess) he = hipMemsetAsync(Ub.p, 0, (size_t)nlm * ch.M * sizeof(double), c->stream);
     if (he == hipSuccess)
         he = launch_harm_expand(1, lmax, c->ht, c->radius, c->d_orb.p, c->d_gcount.p, c->d_hcNx.p,
@@ -2209,9 +2254,10 @@ static fsic_status boundary_basis(fsic_ctx *c, const Chan &ch, const Shape &sh, 
     }
     c->basis_solves += nlm;
     c->basis_ms += now_ms() - t0;
-    DBuf<double> &slot = c->bbasis[key];
-    std::swap(slot, Uc);
-    *U = slot.p;
+    fsic_ctx::Basis &slot = c->bbasis[key];
+    std::swap(slot.u, Uc);
+    slot.used = c->forwards;
+    *U = slot.u.p;
     return FSIC_OK;
 }
 
@@ -2387,6 +2433,7 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
     // need the zero-boundary (adjoint) solutions anyway
     const bool use_basis = (o.flags & FSIC_KEEP_TAPE) && !(o.flags & (FSIC_EQ9_FORCES | FSIC_DIRECT_BC));
     std::vector<const double *> basisU(nchan, nullptr);
+    ++c->forwards;
     c->basis_solves = 0;
     c->basis_ms = 0.0;
     {
@@ -2400,9 +2447,14 @@ static fsic_status forward_impl(fsic_ctx *c, int32_t nsys, const fsic_system *sy
         c->shape_target = sh.target;
         DstTune dt;
         if ((tst = choose_dst(c, groups, o.precision, sh, dt))) return tst;
-        if (use_basis)
+        if (use_basis) {
+            for (const Chan &ch : chans) {
+                auto f = c->bbasis.find(basis_key(c, ch));
+                if (f != c->bbasis.end()) f->second.used = c->forwards;
+            }
             for (int ci = 0; ci < nchan; ++ci)
                 if ((tst = boundary_basis(c, chans[ci], sh, dt, &basisU[ci]))) return tst;
+        }
         build_batch(groups, P, sh, b, precond_of(c, o.precision), dt, o.lmax);
         c->dst_layout = dst_layout_bits(b);
     }
