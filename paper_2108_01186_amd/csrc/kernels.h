@@ -29,10 +29,8 @@ struct CGIter {
     const OrbDesc *orb;
     T *R;               // residual
     T *P;               // search direction: p_k before the update of iteration k, p_{k+1} after
-                        // (preconditioned CG: p_k written by the sweep of iteration k)
-    T *Pold;            // preconditioned CG: p_{k-1}
-    float *Z;           // preconditioned CG: z_k = M^{-1} r_k
-    double *partRZ;     // preconditioned CG: [2*tot9] r.z partial sums, by iteration parity
+                        // (restart cycles: p_k)
+    double *partRZ;     // restart cycles: [2*tot9] r.z partial sums, by iteration parity
     int tot9;
     T *Q;               // K p
     T *X;               // solution (FP64 path) or FP32 correction (mixed path)
@@ -69,19 +67,6 @@ hipError_t launch_cg_stencil(int radius, const Coeffs &c, const CGIter<T> &a, in
 template <typename T>
 hipError_t launch_cg_update(const CGIter<T> &a, int k, int cur_from_ru, int x_first,
                             hipStream_t s);
-
-// Preconditioned CG sweep: p_k = z_k + beta p_{k-1} (beta = r_k.z_k /
-// r_{k-1}.z_{k-1}; 0 when k == 0 or restart), q = -L p_k, p.q partials.
-//   cur_from_ru: r_k.r_k is in partRU; pause: a converged FP32 recursion
-//   waits for the FP64 check (done = 2) instead of finishing.
-template <typename T>
-hipError_t launch_pcg_stencil(int radius, const Coeffs &c, const CGIter<T> &a, int k,
-                              int cur_from_ru, int restart, int pause, hipStream_t s);
-
-// Preconditioned CG update: alpha = r_k.z_k / p.q; x += alpha p; r -= alpha q;
-// r.r partials.  x_first: x is not read (x = alpha p).
-template <typename T>
-hipError_t launch_pcg_update(const CGIter<T> &a, int k, int x_first, hipStream_t s);
 
 // Mixed-precision preconditioned CG (restart cycles of FP32 iterations
 // checked on the FP64 residual).  Sweep of iteration k: q_k = -L p_k with the

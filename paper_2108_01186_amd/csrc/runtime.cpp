@@ -248,7 +248,7 @@ struct fsic_ctx {
     std::string err;
 
     // field buffers
-    DBuf<double> PHI, V, W, B, R, P0, P1, Q, X64b;
+    DBuf<double> PHI, V, W, B, R, P0, Q, X64b;
     DBuf<float> R32, P32a, P32b, Q32, X32;
     DBuf<float> Z32, T32, dtab;     // preconditioned CG: z, transform work array, spectral table
     DBuf<double> partRZ;
@@ -880,8 +880,7 @@ fsic_status prepare_batch(fsic_ctx *c, const Batch &b, int precision) {
         HIPCHK(c, c->Z32.ensure(F));
         HIPCHK(c, c->T32.ensure(F));
         HIPCHK(c, c->partRZ.ensure(2 * (size_t)b.tot9));
-        if (precision == FSIC_FP64) HIPCHK(c, c->P1.ensure(F));
-        else HIPCHK(c, c->P32b.ensure(F));
+        if (precision == FSIC_MIXED) HIPCHK(c, c->P32b.ensure(F));
     }
     if (use_aar(c, b)) {
         HIPCHK(c, c->R32.ensure(F));
@@ -1572,69 +1571,7 @@ fsic_status solve_krylov(fsic_ctx *c, const Batch &b, const double *src, int squ
                 (int)b.dz.size(), b.dst_fast, (b.max_n + 31) & ~31, dst_blocks(c),
                 b.dst_xy ? c->d_dxy.p : nullptr, b.dst_xy ? (int)b.dxy.size() : 0, b.dst_two ? 1 : 0,
                 b.dst_vec ? 1 : 0, b.npxy, b.dst_zocc2 ? 1 : 0, b.dst_xyocc2 ? 1 : 0, b.dst_pv ? 1 : 0};
-    if (pcg && !mixed) {
-        // FP64 CG preconditioned by the FP32 sine-transform inverse.  The host
-        // enqueues two iterations at a time and then reads the converged-
-        // orbital counter of the pair before (one pair stays in flight), so
-        // the device never waits for the host and at most one pair of
-        // launches finds every orbital converged.
-        CGIter<double> a{};
-        a.items7 = c->d_items7.p; a.nitems7 = nit7;
-        a.items8 = c->d_items8.p; a.nitems8 = nit8;
-        a.orb = c->d_orb.p;
-        a.R = c->R.p; a.Q = c->Q.p; a.X = X; a.Z = c->Z32.p;
-        a.part7 = c->part7.p; a.part8 = c->part8.p; a.partRU = c->partRU.p; a.partRZ = c->partRZ.p;
-        a.tot7 = b.tot7; a.tot8 = b.tot8; a.tot9 = b.tot9;
-        a.done = c->done.p; a.iters = c->iters.p; a.rrfin = c->rrfin.p; a.bb = c->bb.p;
-        a.rs_iter = nullptr; a.nact = c->nact.p; a.norb = norb; a.ndone = c->ndone.p;
-        a.tol2 = tol2;
-        const CGIter<double> a0 = a;
-        HIPCHK(c, hipMemsetAsync(c->ndone.p, 0, sizeof(int), s));
-        HIPCHK(c, launch_dst_precond<double>(di, c->d_orb.p, c->done.p, c->dtab.p, a.R, c->T32.p,
-                                             a.Z, a.partRZ, nullptr, s));
-        const int pair = 2;
-        const int npairs = (max_iter + 1 + pair - 1) / pair;
-        auto issue = [&](int j) -> fsic_status {
-            CGIter<double> a = a0;
-            const int kend = std::min((j + 1) * pair, max_iter + 1);
-            for (int k = j * pair; k < kend; ++k) {
-                a.P = (k & 1) ? c->P1.p : c->P0.p;
-                a.Pold = (k & 1) ? c->P0.p : c->P1.p;
-                {
-                    PROF_BEGIN(0, k, k == 0)
-                    HIPCHK(c, launch_pcg_stencil<double>(c->radius, c->cf, a, k, 0, 0, 0, s));
-                    PROF_END()
-                }
-                if (k < max_iter) {
-                    {
-                        PROF_BEGIN(1, k, k == 0)
-                        HIPCHK(c, launch_pcg_update<double>(a, k, k == 0, s));
-                        PROF_END()
-                    }
-                    PROF_BEGIN(2, k + 1, 0)  // z of iteration k + 1
-                    HIPCHK(c, launch_dst_precond<double>(di, c->d_orb.p, c->done.p, c->dtab.p, a.R,
-                                                         c->T32.p, a.Z,
-                                                         a.partRZ + (size_t)((k + 1) & 1) * b.tot9,
-                                                         _sp ? nsamp + 2 * norb : nullptr, s));
-                    PROF_END()
-                }
-            }
-            HIPCHK(c, hipMemcpyAsync(c->h_nd + (j & 1), c->ndone.p, sizeof(int), hipMemcpyDeviceToHost, s));
-            HIPCHK(c, hipEventRecord(c->evc[j & 1], s));
-            return FSIC_OK;
-        };
-        fsic_status ist = issue(0);
-        if (ist) return ist;
-        for (int j = 0;; ++j) {
-            const bool more = j + 1 < npairs;
-            if (more && (ist = issue(j + 1))) return ist;
-            HIPCHK(c, hipEventSynchronize(c->evc[j & 1]));
-            if (c->h_nd[j & 1] >= norb || !more || status_error(c)) break;
-        }
-        HIPCHK(c, launch_true_residual(c->radius, c->cf, c->d_items7.p, nit7, c->d_orb.p, nullptr,
-                                       X, nullptr, c->B.p, nullptr, nullptr, c->partRU.p, s));
-        HIPCHK(c, launch_reduce_partials(norb, c->d_orb.p, c->partRU.p, 1, c->ptrue.p, s));
-    } else if (use_aar(c, b)) {
+    if (use_aar(c, b)) {
         // alternating Anderson-Richardson: FP64 iterate and residual, FP32
         // preconditioned residual f = M^{-1} r
         AarBufs aa{c->d_items8.p, c->d_orb.p, c->done.p, c->Z32.p, c->Fprev.p, c->Fh.p, c->Xh.p, X,
@@ -1681,7 +1618,7 @@ fsic_status solve_krylov(fsic_ctx *c, const Batch &b, const double *src, int squ
         a.items7 = c->d_items7.p; a.nitems7 = nit7;
         a.items8 = c->d_items8.p; a.nitems8 = nit8;
         a.orb = c->d_orb.p;
-        a.R = c->R32.p; a.Q = c->Q32.p; a.X = c->X32.p; a.Z = nullptr; a.B64 = c->B.p;
+        a.R = c->R32.p; a.Q = c->Q32.p; a.X = c->X32.p; a.B64 = c->B.p;
         a.part7 = c->part7.p; a.part8 = c->part8.p; a.partRU = c->partRU.p; a.partRZ = c->partRZ.p;
         a.tot7 = b.tot7; a.tot8 = b.tot8; a.tot9 = b.tot9;
         a.done = c->done.p; a.iters = c->iters.p; a.rrfin = c->rrfin.p; a.bb = c->bb.p;
@@ -1978,13 +1915,6 @@ fsic_status finish_solve(fsic_ctx *c, const Batch &b, SolveReport &rep) {
             else if (r.kind == 2) { c->precond_launches += 1; c->precond_ms += ms; }
             else { c->resid_launches += 1; c->resid_ms += ms; }
         }
-        // preconditioned CG: sweep reads z (float) and p_old, writes p, q;
-        // update reads x, p, r, q, writes x, r; the preconditioner reads r
-        // and passes the float work array through its transform passes (each
-        // reads and writes it once) until the last writes z: three passes
-        // with the in-plane pair fused (r.z from the spectral coefficients of
-        // the z pass), else five, the last reading r again for r.z; its flops
-        // are 2 n per value per transform along an axis of n nodes
         for (int o = 0; o < norb; ++o) {
             const OrbDesc &od = b.orb[o];
             const double Mo = (double)od.nx * od.ny * od.nz;
@@ -1997,7 +1927,7 @@ fsic_status finish_solve(fsic_ctx *c, const Batch &b, SolveReport &rep) {
                 c->precond_bytes += Mo * (od.fd_fused ? 48.0 : 80.0);
                 c->precond_flops += Mo * 2.0 * (od.nx + od.ny + od.nz);
                 c->resid_bytes += Mo * 16.0;
-            } else if (pcg && mixed) {
+            } else if (pcg) {
                 // restart cycles (sampled: the last iteration of every cycle
                 // but the first, and its residual pass): the sweep reads p and
                 // writes q; the update reads r, q and writes r; the
@@ -2012,12 +1942,6 @@ fsic_status finish_solve(fsic_ctx *c, const Batch &b, SolveReport &rep) {
                 c->precond_bytes += Mo * (c->pend_dst_xy ? 28.0 : 44.0) * npc;
                 c->precond_flops += Mo * 4.0 * (od.nx + od.ny + od.nz) * npc;
                 c->resid_bytes += Mo * (36.0 + (cyc > 2 ? 4.0 : 0.0)) * nr;
-            } else if (pcg) {
-                const double npc = na[4 * (size_t)norb + o];
-                c->sweep_bytes += Mo * (4.0 + 3.0 * esz) * ns;
-                c->update_bytes += Mo * esz * 6.0 * nu;
-                c->precond_bytes += Mo * (c->pend_dst_xy ? 20.0 + esz : 36.0 + esz) * npc;
-                c->precond_flops += Mo * 4.0 * (od.nx + od.ny + od.nz) * npc;
             } else {
                 c->sweep_bytes += Mo * esz * 3.0 * ns;
                 c->update_bytes += Mo * esz * 7.0 * nu;
@@ -2114,7 +2038,7 @@ void fsic_destroy(fsic_ctx *c) {
     c->bbasis.clear();
     c->qident.release();
     c->PHI.release(); c->V.release(); c->W.release(); c->B.release(); c->R.release();
-    c->P0.release(); c->P1.release(); c->Q.release(); c->X64b.release();
+    c->P0.release(); c->Q.release(); c->X64b.release();
     c->R32.release(); c->P32a.release(); c->P32b.release(); c->Q32.release(); c->X32.release();
     c->Z32.release(); c->T32.release(); c->dtab.release(); c->partRZ.release();
     c->Fprev.release(); c->Fh.release(); c->Xh.release(); c->aar_gamma.release(); c->partD.release();

@@ -103,8 +103,6 @@ __global__ __launch_bounds__(256) void k_cg_update(CGIter<T> a, int k, int cur_r
     }
 }
 
-// preconditioned CG: x += alpha p; r -= alpha q; alpha = r.z / p.q
-
 template <typename T>
 hipError_t launch_cg_stencil(int radius, const Coeffs &c, const CGIter<T> &a, int k,
                              int cur_from_ru, int check, hipStream_t s) {

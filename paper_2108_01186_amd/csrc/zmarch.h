@@ -361,73 +361,6 @@ __device__ __forceinline__ double rz_of(const CGIter<T> &a, const OrbDesc &od, i
     return sum_partials(a.partRZ + (size_t)(j & 1) * a.tot9 + od.base9, od.nt9, sbuf);
 }
 
-template <typename T>
-struct PolPCG {  // p_k = z_k + beta p_{k-1}; q = K p_k = -L p_k; p.q partials
-    const Item *items;
-    const OrbDesc *orb;
-    CGIter<T> a;
-    int k, cur_ru, restart, pause;
-    double beta;
-    bool tile0;
-    __device__ bool setup(int o, const OrbDesc &od, double *sbuf) {
-        if (threadIdx.x == 0) sbuf[0] = (double)a.done[o];
-        __syncthreads();
-        const bool dn = sbuf[0] != 0.0;
-        __syncthreads();
-        if (dn) return false;
-        const double rr = rr_of(a, od, k, cur_ru, sbuf);
-        if (rr <= a.tol2 * a.bb[o]) {
-            if (threadIdx.x == 0) {
-                if (pause) {
-                    a.done[o] = 2;  // mixed: confirm on the FP64 residual first
-                } else if (atomicCAS(a.done + o, 0, 1) == 0) {  // first block of o to see it
-                    a.iters[o] = k;
-                    a.rrfin[o] = rr;
-                    if (a.ndone) atomicAdd(a.ndone, 1);
-                }
-            }
-            return false;
-        }
-        if (k == 0 || restart) {
-            beta = 0.0;
-        } else {
-            beta = rz_of(a, od, k, sbuf) / rz_of(a, od, k - 1, sbuf);
-        }
-        if (threadIdx.x == 0 && tile0) {
-            a.nact[o] += 1;
-            if (a.nsamp) a.nsamp[o] += 1;
-        }
-        return true;
-    }
-    struct Raw { float z; T p; };
-    struct Ext {};
-    typedef double Acc;
-    Rsrc rz_, rpo, rpn, rq;
-    __device__ void init(const OrbDesc &od) {
-        const long long M = (long long)od.nx * od.ny * od.nz;
-        rz_ = make_rsrc(a.Z + od.off, (unsigned)(M * 4));
-        rpo = make_rsrc(a.Pold + od.off, (unsigned)(M * sizeof(T)));
-        rpn = make_rsrc(a.P + od.off, (unsigned)(M * sizeof(T)));
-        rq = make_rsrc(a.Q + od.off, (unsigned)(M * sizeof(T)));
-    }
-    __device__ Raw raw(unsigned i, int zo) const {
-        // beta = 0 at a (re)start and the host points p_old at finite data
-        return Raw{bld<float>(rz_, i, zo), bld<T>(rpo, i, zo)};
-    }
-    __device__ Ext ext(unsigned, int) const { return Ext{}; }
-    __device__ T combine(const Raw &v) const { return (T)v.z + (T)beta * v.p; }
-    __device__ void epilogue(unsigned i, int zo, T c, T lap, const Ext &, Acc &s) const {
-        const T qv = -lap;
-        bst(rpn, i, zo, c);
-        bst(rq, i, zo, qv);
-        s += (double)c * (double)qv;
-    }
-    __device__ void finish(const Item &it, const OrbDesc &od, const Acc &s, double *sred) const {
-        const double t = block_sum256(s, sred);
-        if (threadIdx.x == 0) a.part7[od.base7 + it.tile] = t;
-    }
-};
-
 // sweep of the mixed restart cycles: q_k = -L p_k, p_k.q_k partials by parity
 struct PolPQ {
     const Item *items;
