@@ -84,7 +84,8 @@ __device__ __forceinline__ int swz(int row, int col) {
 // ---------------------------------------------------------------------------
 
 // waves per SIMD the registers have to leave room for: two blocks of six
-// waves share a compute unit at T = 3
+// waves share a compute unit at T = 3 (168 registers; the forward pass spills
+// 12 B a lane, 20 B where it squares the orbital)
 template <int T>
 constexpr int kXyWaves = T == 3 ? 3 : 2;
 

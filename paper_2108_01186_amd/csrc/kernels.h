@@ -177,8 +177,8 @@ hipError_t launch_reduce_partials(int norb, const OrbDesc *orb, const double *pa
 // ----------------------------------------------------------------------------
 
 // out = K^{-1} b, b = scale src^2 (square) or src, for every orbital with
-// done == 0 (done null: all).  work: one field array; src, work and out may
-// not overlap.
+// done == 0 (done null: all).  work: one field array that overlaps neither src
+// nor out; src may be out.
 hipError_t launch_fdm(const FdmPlan &p, const OrbDesc *orb, const int *done, const double *tab, const double *src,
                       int square, double scale, double *work, double *out, hipStream_t s);
 // LDS limits of the kernels on the current device (once per device)

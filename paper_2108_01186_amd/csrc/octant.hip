@@ -8,7 +8,9 @@
 // its eight parity classes (24 additions per eight nodes), and only the
 // harmonics of a class meet that class: 49 products per eight nodes at
 // lmax 6 instead of 392.  Likewise sum_q a_q H_q at the eight images of an
-// octant node are eight sums over a class each, then 24 additions.
+// octant node are eight sums over a class each, then 24 additions; the Slater
+// step forms them once for each of the four images in y and z (a wave each, the
+// signs on the operand), so 196 products per eight nodes and field.
 //
 // Two contractions with rho_i feed the rest of a step:
 //   Q_q,i  = dV sum_n H_q rho_i      (the multipole moments),
@@ -138,7 +140,9 @@ __device__ __forceinline__ void oct_coords(int o, int hx, int hy, int &i, int &j
 // orbital node) and of H and U (98 B a node and 16 orbitals at lmax 6, mostly
 // from L2 when a grid has more than 16 orbitals).  Loading operands straight
 // from memory (lanes along the orbitals) took 128 us at 96^3 with 31
-// orbitals: 64 separate requests per load.
+// orbitals: 64 separate requests per load.  Orders 7 and 8 hold more
+// accumulator tiles than there are registers (124 and 340 B a lane spilled; a
+// whole step of these orbitals 1.46 and 1.77 ms, 1.38 at order 6).
 // ---------------------------------------------------------------------------
 constexpr int kOmNodes = kOctMomentNodes, kOmStr = kOmNodes + 2;  // LDS row stride: operand reads without bank conflicts
 

@@ -46,7 +46,8 @@ __device__ __forceinline__ int channel_of(const ProdBatch &p, int b) {
 // 16 x 16 tiles.  T: row tiles of a wave; GW = 1: N <= 16 T, every wave forms
 // all tiles over its own groups and the four sums are added in LDS; GW = 2:
 // N <= 32 T, wave (w / 2, w % 2) forms its quarter over all the block's
-// groups.  SYM: Y = X, only tile pairs t1 <= t2.
+// groups.  SYM: Y = X, only tile pairs t1 <= t2.  Above 96 orbitals (T = 4) the
+// 16 accumulator tiles spill 92 B a lane (SYM) and 32 B.
 template <int T, int GW, bool SYM>
 __global__ __launch_bounds__(256, 2) void k_nt(ProdBatch prod, double *part) {
     const int ci = channel_of(prod, blockIdx.x);
@@ -204,7 +205,8 @@ __global__ __launch_bounds__(1024) void k_nt_final(ProdBatch prod, int NP, const
 // 2 c and 2 c + 1 of its k rows, so loads and stores are 16 bytes a lane and
 // 256 bytes a row.  The fragments of A stay in registers (T <= 2) or LDS.
 // (One 16-node strip at a time with A read through the cache took 526 us for
-// 32 orbitals at 128^3; the fields' bytes take 210.)
+// 32 orbitals at 128^3; the fields' bytes take 210.)  12 to 28 B a lane are
+// spilled at T = 3, 7 and 8.
 template <int T>
 __global__ __launch_bounds__(256, 2) void k_nn(ProdBatch prod) {
     extern __shared__ __attribute__((aligned(16))) double af_lds[];
@@ -318,10 +320,13 @@ void nt_shape(int N, int &T, int &GW) {
 }
 
 // Blocks of a channel's reduction: what the device holds at once (more would
-// only add partial tiles), at least sixteen 16-node groups for each wave.  They
-// depend on the channel alone, not on the batch: S of nearly dependent
-// orbitals carries the order of these sums into the forces, and a system
-// gives the same S alone and in a batch.
+// only add partial tiles), at least four 16-node groups for each wave.  They
+// depend on the channel, the device and the room for partial tiles (fit), not
+// on the batch: S of nearly dependent orbitals carries the order of these sums
+// into the forces, and a system gives the same S alone and in a batch.  A
+// context has room for all blocks it could use at any N; above 64 orbitals
+// fsic_op_flo and fsic_op_flo_noalloc have less, so the last bits of their G
+// may differ from a context's.
 long long nt_blocks(int T, int GW, long long M, size_t fit) {
     const long long occ = GW == 1 && T <= 2 ? 4 : 2;
     // four groups a wave at least: fields of few nodes are bound by latency
