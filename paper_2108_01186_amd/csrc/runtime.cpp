@@ -1516,8 +1516,11 @@ fsic_status solve_krylov(fsic_ctx *c, const Batch &b, const double *src, int squ
     HIPCHK(c, launch_rhs(c->radius, c->cf, c->d_items8.p, nit8, c->d_orb.p, src, square, scale,
                          with_bc ? c->Gh.p : nullptr, c->B.p, mixed ? nullptr : c->R.p,
                          mixed ? c->R32.p : nullptr,
-                         // the mixed preconditioned solve starts x64 at 0 without storing it
-                         (mixed && !use_pcg(c, b)) ? X : nullptr, c->part8.p, s));
+                         // plain CG starts x at 0 in memory: an orbital with b = 0 runs no
+                         // iteration that would store it (the restart cycles need no stored
+                         // start, AAR clears its own)
+                         use_pcg(c, b) || use_aar(c, b) ? nullptr : X, c->part8.p, s));
+    if (mixed && !use_pcg(c, b)) HIPCHK(c, hipMemsetAsync(c->X32.p, 0, (size_t)b.fields * sizeof(float), s));
     HIPCHK(c, launch_reduce_partials(norb, c->d_orb.p, c->part8.p, 0, c->bb.p, s));
     {
         // done = 0, iters = 0, rs_iter = -1 (no restart), activity counters 0
